@@ -894,34 +894,34 @@ __device__ __forceinline__ void emit_cell_part(const PlanView& v, int64_t c0, in
 
 
 // ---------------------------------------------------------------------------
-// Emission of 16 cells over one block of LW = 64 / ROWS wavelengths by one
+// Emission of NC cells over one block of LW = 64 / ROWS wavelengths by one
 // wave: lane (row r = lane / LW, i = lane mod LW) takes wavelength LW lb + i
 // and, of every 16 grains, grains 16p + GR r .. 16p + GR r + GR - 1
 // (GR = 16 / ROWS); the rows' partial sums are added across lanes at the end:
 // with two rows, row r then holds the sum of cell 2k + r in acc[2k], with
-// more rows every lane holds all 16 sums.
+// more rows every lane holds all NC sums.
 // A block of fewer than 64 wavelengths spans a smaller range of t, so more
 // (16 grains, cell) choices take a cheap form.  The form is chosen as in
 // emit_accumulate, per 16 grains, from their smallest 1/T (sPair; the odd
 // last group of TAIL from sChunk; TCS the row stride of both, already offset
-// to the first of the 16 cells) and the block's smallest u.  Requires
+// to the first of the NC cells) and the block's smallest u.  Requires
 // LW lb < NLp.
 // ---------------------------------------------------------------------------
 constexpr int EMIT_ROWS = 2;  // rows of a wave in the block emission
 
 // One choice step of emit_block: the calling lane's GRr grains starting at
-// its row's first grain (emp, itp already offset to it), all 16 cells, the
+// its row's first grain (emp, itp already offset to it), all NC cells, the
 // form chosen from the smallest 1/T bits cmA[c] (and cmB[c] when given).
-template <int GRr>
+template <int GRr, int NC>
 __device__ __forceinline__ void emit_step(const float* emp, int NLp, const float* itp, int Sp,
                                           float nu, const uint32_t* cmA, const uint32_t* cmB,
                                           uint32_t thr_skip, uint32_t thr_y, uint32_t thr_y2,
-                                          float (&acc)[16]) {
+                                          float (&acc)[NC]) {
     float e[GRr];
 #pragma unroll
     for (int g = 0; g < GRr; ++g) e[g] = emp[(int64_t)g * NLp];
 #pragma unroll
-    for (int c4 = 0; c4 < 16; c4 += 4) {
+    for (int c4 = 0; c4 < NC; c4 += 4) {
         uint4 a4 = *reinterpret_cast<const uint4*>(cmA + c4);
         if (cmB) {
             // uint min: a NaN group (0) forces the exact form for both groups
@@ -970,10 +970,10 @@ __device__ __forceinline__ void emit_step(const float* emp, int NLp, const float
     }
 }
 
-template <int ROWS, int TCS, bool TAIL>
+template <int ROWS, int TCS, int NC, bool TAIL>
 __device__ __forceinline__ void emit_block(const PlanView& v, int lb, const float* sInvT,
                                            const uint32_t* sChunk, const uint32_t* sPair,
-                                           float (&acc)[16]) {
+                                           float (&acc)[NC]) {
     constexpr int LW = 64 / ROWS, GR = 16 / ROWS;
     static_assert(GR % 8 == 0 || GR == 4, "a row takes whole float4s of grains");
     const int lane = threadIdx.x & 63;
@@ -989,7 +989,7 @@ __device__ __forceinline__ void emit_block(const PlanView& v, int lb, const floa
     const float* emp = v.em + (int64_t)(GR * r) * v.NLp + l;
     const float* itp = sInvT + GR * r;
 #pragma unroll
-    for (int cc = 0; cc < 16; ++cc) acc[cc] = 0.0f;
+    for (int cc = 0; cc < NC; ++cc) acc[cc] = 0.0f;
     // 16-grain steps over the groups that hold real grains; with TAIL an odd
     // last group is left to the step below instead of being paired with
     // padding (a separate instantiation: the tail's code alone costs the
@@ -1002,7 +1002,7 @@ __device__ __forceinline__ void emit_block(const PlanView& v, int lb, const floa
         for (int g = 0; g < GR; ++g) e[g] = emp[(int64_t)(s + g) * v.NLp];
         const uint32_t* cmp = sPair + (s / (2 * EMIT_GROUP)) * TCS;
 #pragma unroll
-        for (int c4 = 0; c4 < 16; c4 += 4) {
+        for (int c4 = 0; c4 < NC; c4 += 4) {
             const uint4 a4 = *reinterpret_cast<const uint4*>(cmp + c4);
             float it[4][GR];
 #pragma unroll
@@ -1048,7 +1048,7 @@ __device__ __forceinline__ void emit_block(const PlanView& v, int lb, const floa
     if (TAIL && (G & 1)) {
         constexpr int GT = EMIT_GROUP / ROWS;
         const int s_row = s_pairs + GT * r;
-        emit_step<GT>(v.em + l + (int64_t)s_row * v.NLp, v.NLp, sInvT + s_row, v.Sp, nu,
+        emit_step<GT, NC>(v.em + l + (int64_t)s_row * v.NLp, v.NLp, sInvT + s_row, v.Sp, nu,
                       sChunk + (s_pairs / EMIT_GROUP) * TCS, nullptr, thr_skip, thr_y, thr_y2,
                       acc);
     }
@@ -1059,7 +1059,7 @@ __device__ __forceinline__ void emit_block(const PlanView& v, int lb, const floa
         // those of cell 2k + 1 in lanes 32-63: one add gives row r the sum of
         // cell 2k + r in acc[2k], with no trip through LDS
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
+        for (int k = 0; k < NC / 2; ++k) {
             const auto sw = __builtin_amdgcn_permlane32_swap(
                 __float_as_uint(acc[2 * k]), __float_as_uint(acc[2 * k + 1]), false, false);
             acc[2 * k] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
@@ -1068,12 +1068,12 @@ __device__ __forceinline__ void emit_block(const PlanView& v, int lb, const floa
 #pragma unroll
         for (int off = 32; off >= LW; off >>= 1) {
 #pragma unroll
-            for (int cc = 0; cc < 16; ++cc) acc[cc] += __shfl_xor(acc[cc], off, 64);
+            for (int cc = 0; cc < NC; ++cc) acc[cc] += __shfl_xor(acc[cc], off, 64);
         }
     }
 }
 
-// SED of a tile of TC cells (a multiple of 16) over the blocks of
+// SED of a tile of TC cells (4, 8 or a multiple of 16) over the blocks of
 // LW = 64 / ROWS wavelengths lb_first, lb_first + lb_step, ... < lb_end of
 // the calling wave, from the tile's LDS (sInvT [TC][Sp], then sChunk [Sp/8][TC]
 // and sPair [Sp/16][TC] as fill_chunk_min writes them).
@@ -1083,7 +1083,8 @@ __device__ __forceinline__ void emit_tile(const PlanView& v, int64_t c0, int64_t
                                           const float* __restrict__ m, float* __restrict__ L,
                                           int64_t ldl, const float* sInvT, const uint32_t* sChunk,
                                           int lb_first, int lb_step, int lb_end) {
-    static_assert(TC % 16 == 0, "cells per tile must be a multiple of 16");
+    constexpr int NC = TC < 16 ? TC : 16;  // cells of one emit_block
+    static_assert(TC % NC == 0 && NC % 4 == 0, "cells per tile: 4, 8 or a multiple of 16");
     constexpr int LW = 64 / ROWS;
     const int lane = threadIdx.x & 63;
     const int r = lane / LW;
@@ -1091,9 +1092,9 @@ __device__ __forceinline__ void emit_tile(const PlanView& v, int64_t c0, int64_t
     for (int lb = lb_first; lb < lb_end; lb += lb_step) {
         const int l = lb * LW + (lane % LW);
 #pragma unroll 1
-        for (int h = 0; h < TC; h += 16) {
-            float acc[16];
-            emit_block<ROWS, TC, TAIL>(v, lb, sInvT + h * v.Sp, sChunk + h, sPair + h, acc);
+        for (int h = 0; h < TC; h += NC) {
+            float acc[NC];
+            emit_block<ROWS, TC, NC, TAIL>(v, lb, sInvT + h * v.Sp, sChunk + h, sPair + h, acc);
             if (l >= v.NL) continue;
             if constexpr (ROWS == 2) {
                 // row r holds the sum of cell 2k + r in acc[2k]; the two cells'
@@ -1101,7 +1102,7 @@ __device__ __forceinline__ void emit_tile(const PlanView& v, int64_t c0, int64_t
                 const int64_t cb = c0 + h;
                 float* Lp = L + (cb + r) * ldl + l;  // cell cb + r; cells 2k further on
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
+                for (int k = 0; k < NC / 2; ++k) {
                     const int64_t ce = cb + 2 * k < C ? cb + 2 * k : C - 1;
                     const int64_t co = cb + 2 * k + 1 < C ? cb + 2 * k + 1 : C - 1;
                     const float me = m ? m[ce] : 1.0f, mo = m ? m[co] : 1.0f;
@@ -1114,7 +1115,7 @@ __device__ __forceinline__ void emit_tile(const PlanView& v, int64_t c0, int64_t
                 for (int rr = 0; rr < ROWS; ++rr) {
                     if (r != rr) continue;
 #pragma unroll
-                    for (int k = 0; k < 16 / ROWS; ++k) {
+                    for (int k = 0; k < NC / ROWS; ++k) {
                         const int64_t c = c0 + h + ROWS * k + rr;
                         if (c < C)
                             L[c * ldl + l] = acc[ROWS * k + rr] * ((m ? m[c] : 1.0f) * v.escale);

@@ -1,0 +1,45 @@
+"""The launch forms that a call's size selects give the same bits.
+
+Every sum of a cell is taken in the same order whatever the tile, so the rows
+of a small call must equal those rows of a large one exactly (tolerance 0).
+The large call's form is checked against the oracle by the parity tests.
+"""
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_0907_3768_amd as dust  # noqa: E402
+
+
+def _inputs(n_cells, n_lambda, n_species, n_sizes, mode, seed, pad=0, **options):
+    g = synth.make_grid(n_lambda, n_species, n_sizes)
+    p = synth.cell_params(n_cells, seed)
+    J = torch.empty((n_cells, n_lambda + pad), dtype=torch.float32, device="cuda")[:, :n_lambda]
+    synth.radiation_field(p, g.lam, device="cuda", out=J)
+    m = torch.as_tensor(p.m_dust, dtype=torch.float32, device="cuda")
+    return dust.Plan(g, mode, **options), J, m
+
+
+@pytest.mark.parametrize("n_lambda,n_species,n_sizes", [
+    (96, 2, 20),     # three blocks: always 16-cell tiles
+    (129, 1, 33),    # five blocks, an odd last group of grains
+    (301, 2, 40),    # ten blocks
+    (1000, 1, 45),   # 32 blocks
+    (250, 1, 32),    # few grains: always 16-cell tiles
+])
+def test_emission_forms_agree(n_lambda, n_species, n_sizes):
+    nb = (n_lambda + 31) // 32
+    n = 16 * (73728 // nb) + 37            # more (16 cells, block) tasks than any small form takes
+    plan, J, m = _inputs(n, n_lambda, n_species, n_sizes, "table", 11)
+    T = plan.solve(plan.absorb(J))
+    T[5, :3] = 0.0
+    T[9, 1] = float("nan")
+    L = plan.emit(T, m)
+    for rows in (1, 5, 63, 1000, 16 * (9216 // nb), 16 * (9216 // nb) + 1, n - 40):
+        part = torch.full((rows + 1, n_lambda + 3), -1.0, device="cuda")
+        plan.emit(T[:rows], m[:rows], part[:rows, :n_lambda])
+        assert torch.equal(part[:rows, :n_lambda].nan_to_num(-3.0), L[:rows].nan_to_num(-3.0)), rows
+        assert bool((part[rows] == -1.0).all()) and bool((part[:, n_lambda:] == -1.0).all())
