@@ -39,7 +39,7 @@
  *      n_unconverged   pairs where the iteration cap was reached
  *                      (the last iterate is kept)
  *      n_out_of_table  pairs of the mixed solve whose T lies outside the
- *                      tabulated range (solved exactly instead)
+ *                      tabulated range (see DUST_MIXED)
  *    H == 0 gives T = 0, and a grain at T = 0 emits nothing.
  *  - Calls that share a plan may run concurrently on different streams,
  *    except those that rewrite its device tables (dust_plan_prepare, and
@@ -73,8 +73,10 @@ typedef enum {
        a cubic Hermite of the inverse evaluated in FP64 between FP64 nodes
        (interpolation error about 1e-9; relative T error about 5e-7,
        dominated by the heating); with `f32_lookup` the same Hermite in FP32
-       from FP32 nodes (about 2e-6).  Pairs outside the tabulated range are
-       solved exactly in FP64.  FP32 emission. */
+       from FP32 nodes (about 2e-6).  Below the tabulated range, down to a
+       third of its lowest T, a second FP64 table of the same kind gives T to
+       the same error; other pairs outside the range are solved exactly in
+       FP64.  FP32 emission. */
     DUST_MIXED = 1,
     /* The production variant of the temperature step (Sections 2 and 5):
        per grain, the power of Eq. 7 tabulated in FP64 at ltab_n temperatures

@@ -111,7 +111,8 @@ void free_plan(dust_plan* p) {
                     p->d_hscale, p->d_hinv, p->d_gs, p->d_kf,  p->d_kb,   p->d_em,   p->d_khi,
                     p->d_klo, p->d_kdb,  p->d_c2l,  p->d_fwd, p->d_ylo,  p->d_yhi,
                     p->d_dyinv, p->d_texp, p->d_lntab, p->d_kidx, p->d_invd, p->d_invf,
-                    p->d_ylof, p->d_dyinvf, p->d_ku};
+                    p->d_ylof, p->d_dyinvf, p->d_ku, p->d_fwd_c, p->d_ylo_c, p->d_dyinv_c,
+                    p->d_inv_c};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete p;
@@ -237,6 +238,10 @@ dust_status dust_plan_create(const dust_grid_desc* g, const dust_options* opt, d
             ALLOC(p->d_invf, (size_t)S * (p->M - 1));
             ALLOC(p->d_ylof, S);
             ALLOC(p->d_dyinvf, S);
+            ALLOC(p->d_fwd_c, (size_t)S * COLD_N);
+            ALLOC(p->d_inv_c, (size_t)S * COLD_M);
+            ALLOC(p->d_ylo_c, S);
+            ALLOC(p->d_dyinv_c, S);
         }
         ALLOC(p->d_ylo, S);
         ALLOC(p->d_yhi, S);
@@ -316,6 +321,9 @@ dust_status dust_plan_create(const dust_grid_desc* g, const dust_options* opt, d
     v.invf = p->d_invf;
     v.ylof = p->d_ylof;
     v.dyinvf = p->d_dyinvf;
+    v.ylo_c = p->d_ylo_c;
+    v.dyinv_c = p->d_dyinv_c;
+    v.inv_c = p->d_inv_c;
     v.f32_lookup = o.f32_lookup;
     v.polish = o.newton_polish;
     v.tstep = tstep;

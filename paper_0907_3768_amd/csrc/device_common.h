@@ -427,29 +427,6 @@ __device__ __forceinline__ float inv_hermite_f32(const PlanView& v, int s, float
 }
 
 // ---------------------------------------------------------------------------
-// FP32 mixed solve of Eq. 7: the grain's inverse table ln T(y), y = ln H',
-// as a cubic Hermite in FP32 between the two nodes around y (one 16-byte
-// entry holds both).  FP32 rounding of y (|y| up to about 50) and of the
-// table leaves a relative T error of about 2e-6; the Hermite itself is far
-// below that.  Returns 0 with *T set, or nonzero for a pair outside the
-// table (then solved exactly).
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ int table_lookup_f32(const PlanView& v, int s, float hs, float* T,
-                                                dust_counters* cnt) {
-    if (!(hs >= 0.0f) || __builtin_isinf(hs)) {
-        if (cnt) count(&cnt->n_nonfinite);
-        *T = __builtin_nanf("");
-        return 0;
-    }
-    if (hs == 0.0f) { *T = 0.0f; return 0; }
-    const float u = inv_pos_f32(v, s, hs);
-    if (!(u >= 0.0f && u <= (float)(v.M - 1))) return 1;  // outside, or the table is not finite
-    const int j = (int)u < v.M - 2 ? (int)u : v.M - 2;
-    *T = inv_hermite_f32(v, s, u, j);
-    return 0;
-}
-
-// ---------------------------------------------------------------------------
 // ln x of a positive normal FP32 value, as an FP64 value with an absolute
 // error of about 4e-8: the binary exponent enters exactly and only log2 of
 // the mantissa (in [0.5, 1)) goes through v_log_f32.  The temperature step
@@ -469,8 +446,7 @@ __device__ __forceinline__ double inv_pos_f64(const PlanView& v, int s, float hs
     return (ln_normal_f32(hs) - v.ylo[s]) * v.dyinv[s];
 }
 
-__device__ __forceinline__ float inv_hermite_f64(const PlanView& v, int s, double u, int j) {
-    const double2* g = v.invd + (int64_t)s * v.M + j;
+__device__ __forceinline__ float hermite_T(const double2* __restrict__ g, double u, int j) {
     const double2 g0 = g[0], g1 = g[1];
     const double t = u - (double)j;
     const double d = g1.x - g0.x;
@@ -479,6 +455,51 @@ __device__ __forceinline__ float inv_hermite_f64(const PlanView& v, int s, doubl
     const double lnT = g0.x + t * (g0.y + t * (c2 + t * c3));
     const float head = (float)lnT;
     return expf(head) * (1.0f + (float)(lnT - (double)head));
+}
+
+__device__ __forceinline__ float inv_hermite_f64(const PlanView& v, int s, double u, int j) {
+    return hermite_T(v.invd + (int64_t)s * v.M + j, u, j);
+}
+
+// T of a pair the first inverse table does not hold, from the one below its
+// range, and counts it as out of table; false where that one does not hold it
+// either (colder still, above the first, or a table that is not finite: NaN).
+// The exact solve this replaces takes a whole wave about 10 us for a pair at
+// 1000 wavelengths (four FP64 sums): a cold cell held its tile's waves for the
+// time of all the tile's other work.
+__device__ __forceinline__ bool cold_lookup(const PlanView& v, int s, float hs, float* T,
+                                            dust_counters* cnt) {
+    if (hs < 1.17549435e-38f) return false;  // subnormal
+    const double u = (ln_normal_f32(hs) - v.ylo_c[s]) * v.dyinv_c[s];
+    if (!(u >= 0.0 && u <= (double)(COLD_M - 1))) return false;
+    const int j = (int)u < COLD_M - 2 ? (int)u : COLD_M - 2;
+    *T = hermite_T(v.inv_c + (int64_t)s * COLD_M + j, u, j);
+    if (cnt) count(&cnt->n_out_of_table);
+    return true;
+}
+
+// ---------------------------------------------------------------------------
+// FP32 mixed solve of Eq. 7: the grain's inverse table ln T(y), y = ln H',
+// as a cubic Hermite in FP32 between the two nodes around y (one 16-byte
+// entry holds both).  FP32 rounding of y (|y| up to about 50) and of the
+// table leaves a relative T error of about 2e-6; the Hermite itself is far
+// below that.  Returns 0 with *T set, or nonzero for a pair outside the
+// table (then solved exactly).
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ int table_lookup_f32(const PlanView& v, int s, float hs, float* T,
+                                                dust_counters* cnt) {
+    if (!(hs >= 0.0f) || __builtin_isinf(hs)) {
+        if (cnt) count(&cnt->n_nonfinite);
+        *T = __builtin_nanf("");
+        return 0;
+    }
+    if (hs == 0.0f) { *T = 0.0f; return 0; }
+    const float u = inv_pos_f32(v, s, hs);
+    if (!(u >= 0.0f && u <= (float)(v.M - 1)))  // outside, or the table is not finite
+        return cold_lookup(v, s, hs, T, cnt) ? 0 : 1;
+    const int j = (int)u < v.M - 2 ? (int)u : v.M - 2;
+    *T = inv_hermite_f32(v, s, u, j);
+    return 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -500,7 +521,8 @@ __device__ __forceinline__ int table_lookup_f64(const PlanView& v, int s, float 
     if (hs == 0.0f) { *T = 0.0f; return 0; }
     if (hs < 1.17549435e-38f) return 1;  // subnormal
     const double u = inv_pos_f64(v, s, hs);
-    if (!(u >= 0.0 && u <= (double)(v.M - 1))) return 1;  // outside, or not finite
+    if (!(u >= 0.0 && u <= (double)(v.M - 1)))  // outside, or not finite
+        return cold_lookup(v, s, hs, T, cnt) ? 0 : 1;
     const int j = (int)u < v.M - 2 ? (int)u : v.M - 2;
     *T = inv_hermite_f64(v, s, u, j);
     return 0;
@@ -511,7 +533,8 @@ __device__ __forceinline__ int table_lookup_f64(const PlanView& v, int s, float 
 // per thread: the node loads are made at a clamped index whatever the pair,
 // so that the loads of all the thread's pairs can be in flight together, and
 // the outcome is selected at the end.  *T and the status agree with the
-// branching forms pair for pair (the nonfinite count is left to the caller).
+// branching forms pair for pair, but for two things left to the caller: the
+// nonfinite count, and the second table of a pending pair (cold_lookup).
 // ---------------------------------------------------------------------------
 constexpr int LOOKUP_OK = 0, LOOKUP_PENDING = 1, LOOKUP_NONFINITE = 2;
 
@@ -566,7 +589,8 @@ __device__ __forceinline__ int table_lookup_polish(const PlanView& v, int s, flo
     if (hs < 1.17549435e-38f) return 1;  // subnormal
     const double y = ln_normal_f32(hs);
     const double u = (y - v.ylo[s]) * v.dyinv[s];
-    if (!(u >= 0.0 && u <= (double)(v.M - 1))) return 1;  // outside, or not finite
+    if (!(u >= 0.0 && u <= (double)(v.M - 1)))  // outside, or not finite
+        return cold_lookup(v, s, hs, T, cnt) ? 0 : 1;
     const int j = (int)u < v.M - 2 ? (int)u : v.M - 2;
     const double2* g = v.invd + (int64_t)s * v.M + j;
     const double2 g0 = g[0], g1 = g[1];

@@ -15,6 +15,14 @@ namespace dust {
 constexpr int PAD_L = 32;
 constexpr int PAD_S = 16;
 
+// The mixed solve's second inverse table, below the first: its forward and
+// inverse nodes, and how far below Tmin it reaches.  ln P is close to linear in
+// 1/T there, so few nodes do: the interpolation error stays below 1e-9 in T on
+// grids that resolve the emission (the first table's own), 1e-8 on an
+// eight-wavelength one.  The synthetic workloads' coldest grains lie at 2.0 K.
+constexpr int COLD_N = 128, COLD_M = 128;
+constexpr double COLD_RATIO = 3.0;
+
 // Exact SI constants (2019 SI) and the derived radiation constants.
 constexpr double PLANCK_H = 6.62607015e-34;
 constexpr double LIGHT_C = 299792458.0;
@@ -62,6 +70,11 @@ struct PlanView {
     const float4* invf;    // [S][M-1]
     const float* ylof;     // [S] float(ylo)
     const float* dyinvf;   // [S] float(dyinv)
+    // mixed: the same below the table's range, COLD_M nodes for T from
+    // Tmin / COLD_RATIO to Tmin (a pair there is an O(1) lookup too)
+    const double* ylo_c;   // [S] first node's y
+    const double* dyinv_c; // [S] 1 / node spacing
+    const double2* inv_c;  // [S][COLD_M]
     int f32_lookup;        // mixed: FP32 inverse-table lookup instead of the FP64 one
     int polish;            // mixed: FP64 Newton polish on the forward table after the lookup
     int N, M;
@@ -116,6 +129,8 @@ struct dust_plan {
     double2* d_invd;
     float4* d_invf;
     float *d_ylof, *d_dyinvf;
+    double *d_fwd_c, *d_ylo_c, *d_dyinv_c;  // mixed: the table below Tmin
+    double2* d_inv_c;
     int* d_kidx;  // table-linear search brackets [S][M]
     dust::PlanView view;
 };
@@ -141,6 +156,10 @@ struct RefreshJob {
     float *nu, *kf, *kb, *ku, *em;
     __bf16 *khi, *klo;
     double *kdb, *c2l, *fwd, *ylo, *yhi, *dyinv;
+    double *fwd_c, *ylo_c, *dyinv_c;
+    double2* inv_c;
+    double lnTmin_c, hstep_c;  // ln T of the forward nodes below Tmin
+    int Nc;                    // their number (0: no such table)
     int* kidx;
     double2* invd;
     float2* invf;

@@ -12,12 +12,15 @@
 //        temperatures, which the product computes as it goes.
 //  inv   (mixed mode): the inverse function ln T(y) and its derivative at
 //        uniform steps of y, from Newton in FP64 on the forward table's
-//        piecewise cubic, stored as FP32 pairs of nodes (one 16-byte load
-//        per lookup).
+//        piecewise cubic, stored as FP64 nodes and as FP32 pairs of nodes (one
+//        16-byte load per lookup).  A second, smaller pair of tables below the
+//        range makes the lookups of colder grains.
 //  table-linear mode: the same matrix product gives P'(T_k) itself at evenly
 //        spaced T_k (the production table of Sections 2 and 5); kidx gives,
 //        at uniform steps of ln P', the last table point below, so that a
 //        lookup searches only a few points.
+#include <math.h>
+
 #include "device_common.h"
 
 namespace dust {
@@ -91,21 +94,36 @@ __device__ __forceinline__ void prep_body(const RefreshJob& j, int bx, int by) {
 // split form below instead (LT_SG_SINGLE only instantiates the other stages).
 constexpr int LT_SG_BATCHED = 4, LT_SG_SINGLE = 1;
 
+// 1/T of table point k: the N points of the table's range, then the Nc points
+// below it (mixed); 0 past the last.
+__device__ __forceinline__ double point_inv_T(const RefreshJob& j, int k) {
+    const PlanView& v = j.v;
+    if (k >= v.N + j.Nc) return 0.0;
+    if (k >= v.N) return exp(-(j.lnTmin_c + (k - v.N) * j.hstep_c));
+    return v.mode == DUST_TABLE_LINEAR ? 1.0 / v.texp[k] : exp(-(v.lnTmin + k * v.hstep));
+}
+
+// The product's result for grain s and point k.
+__device__ __forceinline__ void store_point(const RefreshJob& j, int s, int k, double P) {
+    const PlanView& v = j.v;
+    if (k < v.N)
+        j.fwd[(int64_t)s * v.N + k] = v.mode == DUST_TABLE_LINEAR ? P : log(P);
+    else
+        j.fwd_c[(int64_t)s * j.Nc + (k - v.N)] = log(P);
+}
+
 template <int LT_SG>
 __device__ __forceinline__ void ltab_gemm_body(const RefreshJob& j, int bx, int by) {
     typedef double f64x4 __attribute__((ext_vector_type(4)));
     const PlanView& v = j.v;
-    double* fwd = j.fwd;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane & 15, q = lane >> 4;
     const int k0 = (bx * 4 + wave) * 16;
     const int sg0 = by * LT_SG * 16;
     const int k = k0 + row;
-    const bool k_ok = k < v.N;
-    const double invT = !k_ok ? 0.0
-                        : (v.mode == DUST_TABLE_LINEAR ? 1.0 / v.texp[k]
-                                                       : exp(-(v.lnTmin + k * v.hstep)));
+    const bool k_ok = k < v.N + j.Nc;
+    const double invT = point_inv_T(j, k);
     f64x4 acc[LT_SG];
 #pragma unroll
     for (int t = 0; t < LT_SG; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
@@ -143,9 +161,7 @@ __device__ __forceinline__ void ltab_gemm_body(const RefreshJob& j, int bx, int 
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
             const int sr = sg0 + st * 16 + q + 4 * jj;
-            if (sr < v.S && k < v.N)
-                fwd[(int64_t)sr * v.N + k] =
-                    (v.mode == DUST_TABLE_LINEAR) ? acc[st][jj] : log(acc[st][jj]);
+            if (sr < v.S && k_ok) store_point(j, sr, k, acc[st][jj]);
         }
     }
 }
@@ -165,10 +181,8 @@ __device__ __forceinline__ void ltab_gemm_split_body(const RefreshJob& j, int bx
     const int row = lane & 15, q = lane >> 4;
     const int k = bx * 16 + row;
     const int s = by * 16 + row;
-    const bool k_ok = k < v.N;
-    const double invT = !k_ok ? 0.0
-                        : (v.mode == DUST_TABLE_LINEAR ? 1.0 / v.texp[k]
-                                                       : exp(-(v.lnTmin + k * v.hstep)));
+    const bool k_ok = k < v.N + j.Nc;
+    const double invT = point_inv_T(j, k);
     const double* wr = v.kdb + (int64_t)(s < v.S ? s : 0) * v.NL;
     f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
     for (int l0 = 32 * wave; l0 < v.NL; l0 += 128) {
@@ -193,8 +207,7 @@ __device__ __forceinline__ void ltab_gemm_split_body(const RefreshJob& j, int bx
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
             const int sr = by * 16 + q + 4 * jj;
-            if (sr < v.S && k_ok)
-                j.fwd[(int64_t)sr * v.N + k] = (v.mode == DUST_TABLE_LINEAR) ? acc[jj] : log(acc[jj]);
+            if (sr < v.S && k_ok) store_point(j, sr, k, acc[jj]);
         }
     }
 }
@@ -228,52 +241,65 @@ __device__ __forceinline__ void kidx_body(const RefreshJob& job, int bx, int by)
     kidx[(int64_t)s * v.M + j] = lo;
 }
 
-// One thread per (grain, inverse node): ln T at y_j = ylo + j dy, by Newton
-// on the forward table's cubic, and dy * d ln T / dy there.
-__device__ __forceinline__ void inv_body(const RefreshJob& job, int bx, int by) {
-    const PlanView& v = job.v;
-    const double* __restrict__ fwd = job.fwd;
-    double* ylo = job.ylo; double* yhi = job.yhi; double* dyinv = job.dyinv;
-    double2* invd = job.invd;
-    float2* invf = job.invf; float* ylof = job.ylof; float* dyinvf = job.dyinvf;
-    const int j = bx * blockDim.x + threadIdx.x;
-    const int s = by;
-    if (j >= v.M) return;
-    const int N = v.N;
-    const double* f = fwd + (int64_t)s * N;
-    const double y0 = f[0], y1 = f[N - 1];
-    const double dinv = (v.M - 1) / (y1 - y0);
-    if (j == 0) {
-        ylo[s] = y0;
-        yhi[s] = y1;
-        dyinv[s] = dinv;
-        ylof[s] = (float)y0;
-        dyinvf[s] = (float)dinv;
-    }
-    const double yj = (j == v.M - 1) ? y1 : y0 + j / dinv;
-    // largest k in [0, N-2] with y_k <= yj
+// ln T at y (>= f[0]) by Newton on the piecewise cubic through a forward table
+// f[0..N-1] at ln T = lnT0 + k h, and d ln T / dy there.
+__device__ __forceinline__ double2 inverse_node(const double* __restrict__ f, int N, double lnT0,
+                                                double h, double y) {
+    // largest k in [0, N-2] with f_k <= y
     int lo = 0, hi = N - 2;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (f[mid] <= yj) lo = mid; else hi = mid - 1;
+        if (f[mid] <= y) lo = mid; else hi = mid - 1;
     }
     const int j0 = stencil_start(lo, N);
     const double a0 = f[j0], a1 = f[j0 + 1], a2 = f[j0 + 2], a3 = f[j0 + 3];
-    double x = lo - j0 + ((f[lo + 1] > f[lo]) ? (yj - f[lo]) / (f[lo + 1] - f[lo]) : 0.0);
+    double x = lo - j0 + ((f[lo + 1] > f[lo]) ? (y - f[lo]) / (f[lo + 1] - f[lo]) : 0.0);
     double dp = 1.0;
     for (int it = 0; it < 4; ++it) {
         const double p = cubic4(x, a0, a1, a2, a3, &dp);
-        x -= (p - yj) / dp;
+        x -= (p - y) / dp;
     }
     cubic4(x, a0, a1, a2, a3, &dp);
-    // d lnT / dy = hstep / (dy/dx), scaled by the node spacing dy = 1/dinv
-    const double lnTj = v.lnTmin + ((double)j0 + x) * v.hstep;
-    const double mj = v.hstep / dp / dinv;
-    invd[(int64_t)s * v.M + j] = make_double2(lnTj, mj);
+    return make_double2(lnT0 + ((double)j0 + x) * h, h / dp);
+}
+
+// One thread per (grain, inverse node): ln T at y_j = ylo + j dy and
+// dy * d ln T / dy.  The last block column makes the table below the range.
+__device__ __forceinline__ void inv_body(const RefreshJob& job, int bx, int by) {
+    const PlanView& v = job.v;
+    const int s = by;
+    const bool cold = bx == job.gx[3] - 1;
+    const int j = cold ? threadIdx.x : bx * blockDim.x + threadIdx.x;
+    const int M = cold ? COLD_M : v.M, N = cold ? job.Nc : v.N;
+    if (j >= M) return;
+    const double* f = (cold ? job.fwd_c : job.fwd) + (int64_t)s * N;
+    const double y0 = f[0], y1 = f[N - 1];
+    const double dinv = (M - 1) / (y1 - y0);
+    if (j == 0) {
+        if (cold) {
+            job.ylo_c[s] = y0;
+            job.dyinv_c[s] = dinv;
+        } else {
+            job.ylo[s] = y0;
+            job.yhi[s] = y1;
+            job.dyinv[s] = dinv;
+            job.ylof[s] = (float)y0;
+            job.dyinvf[s] = (float)dinv;
+        }
+    }
+    const double yj = (j == M - 1) ? y1 : y0 + j / dinv;
+    double2 node = inverse_node(f, N, cold ? job.lnTmin_c : v.lnTmin,
+                                cold ? job.hstep_c : v.hstep, yj);
+    node.y /= dinv;  // the derivative, scaled by the node spacing dy = 1 / dinv
+    if (cold) {
+        job.inv_c[(int64_t)s * M + j] = node;
+        return;
+    }
+    job.invd[(int64_t)s * M + j] = node;
     // the FP32 entries of the two intervals this node bounds
-    const float2 nf = make_float2((float)lnTj, (float)mj);
-    float2* row = invf + (int64_t)s * (v.M - 1) * 2;
-    if (j < v.M - 1) row[2 * j] = nf;
+    const float2 nf = make_float2((float)node.x, (float)node.y);
+    float2* row = job.invf + (int64_t)s * (M - 1) * 2;
+    if (j < M - 1) row[2 * j] = nf;
     if (j > 0) row[2 * (j - 1) + 1] = nf;
 }
 
@@ -320,7 +346,7 @@ __global__ __launch_bounds__(256) void refresh_batched_kernel(const RefreshJob* 
 template <int STAGE>
 hipError_t launch_stage(const RefreshJob& j, hipStream_t st) {
     // the single-plan product: one (16-point block, grain tile) per workgroup
-    const int gx = (STAGE == 2) ? (j.v.N + 15) / 16 : j.gx[STAGE];
+    const int gx = (STAGE == 2) ? (j.v.N + j.Nc + 15) / 16 : j.gx[STAGE];
     const int gy = (STAGE == 2) ? (j.v.S + 15) / 16 : j.gy[STAGE];
     hipLaunchKernelGGL(refresh_kernel<STAGE>, dim3(gx, gy), dim3(256), 0, st, j);
     return hipGetLastError();
@@ -350,11 +376,19 @@ void make_refresh_job(const dust_plan* p, RefreshJob* j) {
     j->invf = reinterpret_cast<float2*>(p->d_invf);
     j->ylof = p->d_ylof; j->dyinvf = p->d_dyinvf;
     const bool tab = table_mode(v.mode);
+    if (mixed_mode(v.mode)) {
+        j->Nc = COLD_N;
+        j->fwd_c = p->d_fwd_c; j->ylo_c = p->d_ylo_c; j->dyinv_c = p->d_dyinv_c;
+        j->inv_c = p->d_inv_c;
+        j->lnTmin_c = v.lnTmin - log(COLD_RATIO);
+        j->hstep_c = log(COLD_RATIO) / (COLD_N - 1);
+    }
     j->gx[0] = (v.NLp + 255) / 256;  j->gy[0] = v.Sp;
     j->gx[1] = 1;                    j->gy[1] = 0;
-    j->gx[2] = (v.N + 63) / 64;
+    j->gx[2] = (v.N + j->Nc + 63) / 64;
     j->gy[2] = tab ? (v.S + LT_SG_BATCHED * 16 - 1) / (LT_SG_BATCHED * 16) : 0;  // batched launches
-    j->gx[3] = (v.M + 255) / 256;    j->gy[3] = tab ? v.S : 0;
+    // (mixed: one more column for the table below the range)
+    j->gx[3] = (v.M + 255) / 256 + (j->Nc > 0); j->gy[3] = tab ? v.S : 0;
 }
 
 hipError_t launch_prepare(const dust_plan* p, hipStream_t st) {

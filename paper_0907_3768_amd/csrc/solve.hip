@@ -95,7 +95,7 @@ __global__ __launch_bounds__(256) void solve_table_kernel(PlanView v, int64_t C,
 // (coalesced H and T) and looks all of them up before it stores any, so that
 // their dependent loads (H, then the grain's inverse-table nodes) overlap: a
 // single lookup per thread leaves the kernel waiting on memory latency.  Pairs
-// outside the table go to an LDS list and are then solved exactly by the
+// outside both tables go to an LDS list and are then solved exactly by the
 // block's waves in turn (one pair per wave at a time, lanes over wavelength).
 constexpr int MIXED_PER = 4;
 constexpr int MIXED_BLOCK = 256 * MIXED_PER;  // pairs per workgroup
@@ -146,6 +146,9 @@ __global__ __launch_bounds__(256) void solve_mixed_kernel(PlanView v, int64_t C,
 #pragma unroll
     for (int k = 0; k < MIXED_PER; ++k) {
         if (base + k * 256 >= n) continue;
+        if (MODE != MODE_MIXED_POLISH && st[k] == LOOKUP_PENDING &&
+            cold_lookup(v, s[k], hs[k], &t[k], cnt))
+            st[k] = LOOKUP_OK;
         if (st[k] == LOOKUP_PENDING) {
             sList[atomicAdd(&sCount, 1)] = threadIdx.x + k * 256;
         } else {

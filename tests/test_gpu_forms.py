@@ -4,8 +4,10 @@ Every sum of a cell is taken in the same order whatever the tile, so the rows
 of a small call must equal those rows of a large one exactly (tolerance 0).
 The large call's form is checked against the oracle by the parity tests.
 """
+import numpy as np
 import pytest
 
+import oracle
 import synth
 
 pytestmark = pytest.mark.gpu
@@ -43,3 +45,31 @@ def test_emission_forms_agree(n_lambda, n_species, n_sizes):
         plan.emit(T[:rows], m[:rows], part[:rows, :n_lambda])
         assert torch.equal(part[:rows, :n_lambda].nan_to_num(-3.0), L[:rows].nan_to_num(-3.0)), rows
         assert bool((part[rows] == -1.0).all()) and bool((part[:, n_lambda:] == -1.0).all())
+
+
+@pytest.mark.parametrize("lookup", ["default", "f32", "polish"])
+@pytest.mark.parametrize("n_lambda,hi_um,tmin", [(120, 1000.0, 2.7), (250, 100.0, 10.0),
+                                                 (8, 1000.0, 2.7)])
+def test_temperatures_below_the_table(n_lambda, hi_um, tmin, lookup):
+    """Pairs from just below the table's lowest T down to a sixth of it:
+    over the whole second table (down to a third) and below that one.
+    Bound on T, given the heating: the second table's interpolation (1e-8 on
+    the coarsest grid) and ln H' to 4e-8 (a fifth of it or less in T), plus the
+    FP32 exponential, its correction and the rounding, 2 ulp = 2.4e-7."""
+    g = synth.make_grid(n_lambda, 2, 5, hi_um=hi_um)
+    T = np.geomspace(0.99 * tmin, tmin / 6.0, 700)
+    c1, c2 = 2 * 6.62607015e-34 * 299792458.0 ** 2, 6.62607015e-34 * 299792458.0 / 1.380649e-23
+    B = c1 / g.lam ** 5 / np.expm1(np.minimum(c2 / (g.lam * T[:, None]), 700.0))
+    scale = 2.0 ** 60  # keeps H in FP32's normal range (the emission weights unchanged)
+    g.c_abs, g.weight = g.c_abs * scale, g.weight / scale
+    H = np.maximum(B @ (g.c_abs * g.dlam).T, 0.0).astype(np.float32)
+    keep = (H > 1e-37).all(axis=1)
+    H = H[keep]
+    assert len(H) > 400
+    ref = oracle.temperature(H.astype(np.float64), g.lam, g.dlam, g.c_abs, g.size)
+    plan = dust.Plan(g, "mixed", ltab_tmin=tmin, f32_lookup=lookup == "f32",
+                     newton_polish=lookup == "polish")
+    cnt = dust.new_counters()
+    out = plan.solve(torch.as_tensor(H, device="cuda"), counters=cnt).cpu().numpy()
+    assert np.abs(out / ref - 1.0).max() <= 3e-7
+    assert cnt.tolist()[:3] == [0, 0, H.size]
