@@ -109,7 +109,8 @@ typedef struct {
     double tol;        /* plain: stop when |P(T)/H - 1| <= tol, default 1e-5 */
     int32_t ltab_n;    /* table points per grain: mixed default 1024 (>= 16),
                           table-linear default 2000 (>= 16) */
-    int32_t fused_kernels; /* dust_run_fused: 0 = library choice, 1 = one kernel
+    int32_t fused_kernels; /* dust_run_fused: 0 = library choice by the call's
+                              size (the same results), 1 = one kernel
                               (absorb, solve and emit per cell tile), 2 = two
                               kernels (absorb + solve per tile, T written once;
                               then emit).  H never reaches device memory. */
@@ -207,8 +208,9 @@ dust_status dust_emit_sed(dust_plan* plan, int64_t n_cells,
                           const float* T, int64_t ldt, const float* m_dust,
                           float* L, int64_t ldl, void* stream);
 
-/* Eqs. 6, 7, 9-10 in one launch per cell tile: H stays on chip and never
- * reaches device memory.  Same results as absorb -> solve -> emit. */
+/* Eqs. 6, 7, 9-10 in one call: H stays on chip and never reaches device
+ * memory (one launch over cell tiles, or, for few cells, one for the
+ * temperatures and one for the emission).  Same results as absorb -> solve -> emit. */
 dust_status dust_run_fused(dust_plan* plan, int64_t n_cells,
                            const float* J, int64_t ldj, const float* m_dust,
                            float* T, int64_t ldt, float* L, int64_t ldl,

@@ -458,7 +458,8 @@ dust_status dust_run_fused_ext(dust_plan* p, int64_t C, const float* J, int64_t 
     const hipStream_t sm = (hipStream_t)stream;
     hipError_t e = (p->opt.fused_kernels == 2)
                        ? launch_absorb_solve(v, C, J, ldj, T, ldt, cnt, sm)
-                       : launch_fused(v, C, J, ldj, m, T, ldt, L, ldl, cnt, sm);
+                       : launch_fused(v, C, J, ldj, m, T, ldt, L, ldl, cnt,
+                                      p->opt.fused_kernels == 1, sm);
     if (e == hipSuccess && p->opt.fused_kernels == 2)
         e = launch_emit(v, C, T, ldt, m, L, ldl, sm);
     return e == hipSuccess ? DUST_OK : hip_error(e, "fused launch");

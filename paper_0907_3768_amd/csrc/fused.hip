@@ -3,6 +3,7 @@
 // solved in place (LDS then holds 1/T), and feeds the emission loop: H never
 // reaches device memory and T is written once.
 #include "fused_body.h"
+#include "wave_heat.h"
 
 namespace dust {
 namespace {
@@ -43,6 +44,95 @@ __global__ __launch_bounds__(256) void absorb_solve_kernel(PlanView v, int64_t C
     __syncthreads();
     fused_solve<MODE, FUSED_TC>(v, c0, C, T, ldt, cnt, lds,
                                 reinterpret_cast<int*>(sStage + STAGE_BYTES));
+}
+
+// Absorb + solve for small calls: one wave per 16 cells x 16 grains, the
+// heating straight from device memory (heat_wave) and the lookups straight
+// from the accumulators, four pairs of one grain per lane; no LDS and no
+// barrier.  Pairs the table does not take are solved exactly by the wave, one
+// after the other.  The emission kernel follows.
+template <int MODE, bool ALIGNED>
+__global__ __launch_bounds__(64) void heat_solve_kernel(PlanView v, int64_t C,
+                                                        const float* __restrict__ J, int64_t ldj,
+                                                        float* __restrict__ T, int64_t ldt,
+                                                        dust_counters* cnt) {
+    const HeatTile ht = heat_tile(blockIdx.x, v.Sp / 16);
+    if (ht.c0 >= C) return;
+    const f32x4 acc = heat_wave<true, ALIGNED>(v, ht.c0, C, ht.tile, J, ldj);
+    const int lane = threadIdx.x & 63;
+    const int s_raw = 16 * ht.tile + (lane & 15);
+    const int s = s_raw < v.S ? s_raw : v.S - 1;  // a lane past the last grain looks it up unused
+    const int64_t cl = ht.c0 + 4 * (lane >> 4);
+    float h[4], t[4];
+    int st[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        h[r] = acc[r];
+        if (v.q && s_raw < v.S && cl + r < C) h[r] += v.q[(cl + r) * v.ldq + s] * v.hscale[s];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const bool pair = s_raw < v.S && cl + r < C;
+        if constexpr (MODE == DUST_MIXED) {
+            st[r] = table_lookup_f64_nb(v, s, h[r], &t[r]);
+            if (!pair)
+                st[r] = LOOKUP_OK;
+            else if (st[r] == LOOKUP_PENDING && cold_lookup(v, s, h[r], &t[r], cnt))
+                st[r] = LOOKUP_OK;
+        } else {  // (the fused kernel's lookup: the branch-free FP32 one rounds differently)
+            st[r] = LOOKUP_OK;
+            if (pair) {
+                if constexpr (mixed_mode(MODE)) {
+                    if (mixed_lookup<MODE>(v, s, h[r], &t[r], cnt) != 0) st[r] = LOOKUP_PENDING;
+                } else {
+                    t[r] = table_linear_T(v, s, h[r], cnt);
+                }
+            }
+        }
+        if (pair && st[r] != LOOKUP_PENDING) T[(cl + r) * ldt + s] = t[r];
+    }
+    if constexpr (mixed_mode(MODE)) {
+        if (MODE == DUST_MIXED && cnt) {
+            int bad = 0;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) bad += st[r] == LOOKUP_NONFINITE;
+            wave_count_add(&cnt->n_nonfinite, bad);
+        }
+#pragma unroll 1
+        for (int r = 0; r < 4; ++r) {
+            const float hr = r == 0 ? h[0] : (r == 1 ? h[1] : (r == 2 ? h[2] : h[3]));
+            const int sr = r == 0 ? st[0] : (r == 1 ? st[1] : (r == 2 ? st[2] : st[3]));
+            uint64_t mask = __ballot(sr == LOOKUP_PENDING);
+            while (mask) {
+                const int src = __builtin_ctzll(mask);
+                mask &= mask - 1;
+                const float hp = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(hr), src));
+                const int sp = 16 * ht.tile + (src & 15);
+                const float tp = wave_solve_pending(v, sp, (double)hp, cnt);
+                if (lane == 0) T[(ht.c0 + 4 * (src >> 4) + r) * ldt + sp] = tp;
+            }
+        }
+    }
+}
+
+template <bool ALIGNED>
+hipError_t launch_heat_solve(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* T,
+                             int64_t ldt, dust_counters* cnt, hipStream_t st) {
+    const dim3 grid(heat_blocks(C, v.Sp / 16));
+    const int km = kernel_mode(v);
+    if (km == DUST_MIXED)
+        hipLaunchKernelGGL((heat_solve_kernel<DUST_MIXED, ALIGNED>), grid, dim3(64), 0, st, v, C,
+                           J, ldj, T, ldt, cnt);
+    else if (km == MODE_MIXED_F32)
+        hipLaunchKernelGGL((heat_solve_kernel<MODE_MIXED_F32, ALIGNED>), grid, dim3(64), 0, st, v,
+                           C, J, ldj, T, ldt, cnt);
+    else if (km == MODE_MIXED_POLISH)
+        hipLaunchKernelGGL((heat_solve_kernel<MODE_MIXED_POLISH, ALIGNED>), grid, dim3(64), 0, st,
+                           v, C, J, ldj, T, ldt, cnt);
+    else
+        hipLaunchKernelGGL((heat_solve_kernel<DUST_TABLE_LINEAR, ALIGNED>), grid, dim3(64), 0, st,
+                           v, C, J, ldj, T, ldt, cnt);
+    return hipGetLastError();
 }
 
 template <int NTW>
@@ -105,12 +195,47 @@ hipError_t launch_fused_as(const PlanView& v, int64_t C, const float* J, int64_t
     return launch_ntw<4, TAIL>(v, C, J, ldj, m, T, ldt, L, ldl, cnt, st);  // 4: several passes above
 }
 
+// Whether a call runs as heat_solve_kernel and the emission kernel instead of
+// one fused kernel.  A fused workgroup takes 16 cells through every phase, so
+// up to two workgroups per CU the call takes as long as one tile's chain
+// whatever the cell count (968 wavelengths x 81 grains: 106 us for 32 cells,
+// 118 for 4099), while the two kernels spread the same work over grain tiles
+// and wavelength blocks: 17 us and 70.  At 8192 cells (512 tiles) 125 against
+// 148 us, at 16384 228 against 219; 250 x 80 and 1000 x 240 cross at the same
+// tile count, a short chain a little earlier (8192 x 200 x 40: 25.6 us fused,
+// 26.6 split; 4096: 22.9, 18.1).  Below 6000 grain-wavelengths a tile's chain
+// is shorter than the second launch is worth (120 x 20: 11.8 us fused, 14.3
+// split; 120 x 40: 15.4 both).
+constexpr int64_t SPLIT_TILES = 384, SPLIT_WORK = 6000;
+constexpr int64_t SPLIT_TILES_LONG = 512, SPLIT_WORK_LONG = 16000;
+
+bool split_pays(const PlanView& v, int64_t C) {
+    const int64_t work = (int64_t)v.S * v.NL;
+    return work >= SPLIT_WORK_LONG ? C <= 16 * SPLIT_TILES_LONG
+                                   : C <= 16 * SPLIT_TILES && work >= SPLIT_WORK;
+}
+
+// Whether two arrays of a and b floats share memory.  The heating's waves read
+// rows of J that another wave's T may replace then; the fused kernel reads a
+// tile's rows before it writes them.
+bool share_memory(const float* x, int64_t a, const float* y, int64_t b) {
+    const uintptr_t px = (uintptr_t)x, py = (uintptr_t)y;
+    return px < py + 4 * (uintptr_t)b && py < px + 4 * (uintptr_t)a;
+}
+
 }  // namespace
 
 hipError_t launch_fused(const PlanView& v, int64_t C, const float* J, int64_t ldj, const float* m,
                         float* T, int64_t ldt, float* L, int64_t ldl, dust_counters* cnt,
-                        hipStream_t st) {
+                        bool one_kernel, hipStream_t st) {
     if (C == 0) return hipSuccess;
+    if (!one_kernel && table_mode(v.mode) && split_pays(v, C) &&
+        !share_memory(J, (C - 1) * ldj + v.NL, T, (C - 1) * ldt + v.S)) {
+        const hipError_t e = rows_aligned16(J, ldj)
+                                 ? launch_heat_solve<true>(v, C, J, ldj, T, ldt, cnt, st)
+                                 : launch_heat_solve<false>(v, C, J, ldj, T, ldt, cnt, st);
+        return e != hipSuccess ? e : launch_emit(v, C, T, ldt, m, L, ldl, st);
+    }
     if (((v.S + EMIT_GROUP - 1) / EMIT_GROUP) & 1)
         return launch_fused_as<true>(v, C, J, ldj, m, T, ldt, L, ldl, cnt, st);
     return launch_fused_as<false>(v, C, J, ldj, m, T, ldt, L, ldl, cnt, st);

@@ -198,6 +198,6 @@ hipError_t launch_absorb_solve(const PlanView& v, int64_t C, const float* J, int
                                float* T, int64_t ldt, dust_counters* cnt, hipStream_t st);
 hipError_t launch_fused(const PlanView& v, int64_t C, const float* J, int64_t ldj,
                         const float* m, float* T, int64_t ldt, float* L, int64_t ldl,
-                        dust_counters* cnt, hipStream_t st);
+                        dust_counters* cnt, bool one_kernel, hipStream_t st);
 
 }  // namespace dust

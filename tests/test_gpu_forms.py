@@ -73,3 +73,42 @@ def test_temperatures_below_the_table(n_lambda, hi_um, tmin, lookup):
     out = plan.solve(torch.as_tensor(H, device="cuda"), counters=cnt).cpu().numpy()
     assert np.abs(out / ref - 1.0).max() <= 3e-7
     assert cnt.tolist()[:3] == [0, 0, H.size]
+
+
+@pytest.mark.parametrize("mode,lookup", [("mixed", "default"), ("mixed", "f32"),
+                                         ("mixed", "polish"), ("table", "default")])
+@pytest.mark.parametrize("n_cells,n_lambda,n_species,n_sizes,pad", [
+    (1, 380, 1, 16, 0),       # one cell, one grain tile, ragged last k-step
+    (33, 127, 3, 17, 2),      # 3 full k-steps and a ragged one, ragged grains, J unaligned
+    (130, 128, 2, 40, 0),     # whole k-steps, aligned rows
+    (515, 161, 1, 45, 3),     # one group of k-steps and two left over
+    (8192, 1000, 1, 16, 0),   # the most cells of the two-kernel form
+    (6145, 400, 1, 16, 0),    # one more than it takes of short rows (one kernel)
+    (100, 30, 3, 80, 1),      # no full k-step
+])
+def test_two_kernel_form_of_small_fused_calls(n_cells, n_lambda, n_species, n_sizes, pad, mode,
+                                              lookup):
+    """A small fused call gives the one-kernel form's T, SED and counters, on
+    cells of every kind: no field, NaN, negative and infinite intensity, too
+    cold for both tables, hotter than the table, with an extra heating."""
+    options = {"f32_lookup": lookup == "f32", "newton_polish": lookup == "polish"}
+    plan, J, m = _inputs(n_cells, n_lambda, n_species, n_sizes, mode, 7, pad, **options)
+    one = dust.Plan(synth.make_grid(n_lambda, n_species, n_sizes), mode, fused_kernels=1,
+                    **options)
+    S = plan.n_grains
+    for c, f in ((3, 0.0), (4, float("nan")), (7, -1.0), (9, 1e-14), (20, 1e12), (21, 1e-8),
+                 (24, float("inf"))):
+        if c < n_cells:
+            J[c] *= f
+    Q = torch.zeros((n_cells, S + 1), device="cuda")
+    Q[::5] = 1e-20
+    for q in (None, Q):
+        out = []
+        for p in (one, plan):
+            T = torch.full((n_cells + 1, S + 2), -1.0, device="cuda")
+            L = torch.full((n_cells + 1, n_lambda + 3), -1.0, device="cuda")
+            cnt = dust.new_counters()
+            p.fused(J, m, T[:n_cells, :S], L[:n_cells, :n_lambda], counters=cnt, Q=q)
+            out.append((T.nan_to_num(-3.0), L.nan_to_num(-3.0), cnt))
+        for a, b in zip(*out):
+            assert torch.equal(a, b)
