@@ -65,7 +65,8 @@ typedef enum {
 
 typedef enum {
     /* FP32 throughout: FP32 MFMA heating, FP32 Newton on the exact sum of
-       Eq. 7 from the Eq. 11 guess, FP32 emission. */
+       Eq. 7 from the Eq. 11 guess (its first iterations on a table of the
+       sum, see maxit), FP32 emission. */
     DUST_PLAIN_FP32 = 0,
     /* Mixed precision: heating on BF16 MFMA with hi+lo split operands and
        FP32 accumulation; T from per-grain tables built in FP64 (ln P at
@@ -105,15 +106,19 @@ typedef struct {
 /* Options; a zero field selects the default shown. */
 typedef struct {
     int32_t mode;      /* dust_mode; default DUST_PLAIN_FP32 */
-    int32_t maxit;     /* plain: Newton iteration cap, default 50 */
-    double tol;        /* plain: stop when |P(T)/H - 1| <= tol, default 1e-5 */
+    int32_t maxit;     /* plain: Newton iteration cap, default 50.  From 8 on
+                          the first iterations run on the grain's power
+                          tabulated at 128 temperatures (0.9-3000 K); the
+                          last one is always on the exact sum. */
+    double tol;        /* plain: stop when |P(T)/H - 1| <= tol, default 1e-5,
+                          or when the Newton step taken will leave less */
     int32_t ltab_n;    /* table points per grain: mixed default 1024 (>= 16),
                           table-linear default 2000 (>= 16) */
     int32_t fused_kernels; /* dust_run_fused: 0 = library choice by the call's
                               size (the same results), 1 = one kernel
                               (absorb, solve and emit per cell tile), 2 = two
                               kernels (absorb + solve per tile, T written once;
-                              then emit).  H never reaches device memory. */
+                              then emit). */
     double ltab_tmin;  /* lowest tabulated T (K): mixed 2.7, table-linear 3 */
     double ltab_tmax;  /* highest tabulated T (K): mixed 3000, table-linear 1500 */
     int32_t f32_lookup; /* mixed: nonzero replaces the FP64 inverse-table
@@ -133,8 +138,8 @@ typedef struct {
     int64_t n_nonfinite;
     int64_t n_unconverged;
     int64_t n_out_of_table;
-    int64_t n_newton_evals;  /* DUST_PLAIN_FP32: evaluations of Eq. 7's sum
-                                (pairs x Newton iterations) */
+    int64_t n_newton_evals;  /* DUST_PLAIN_FP32: pairs x Newton iterations
+                                (on the table and on the exact sum) */
 } dust_counters;
 
 /* Optional inputs of the temperature step (dust_solve_T_ext,
@@ -208,9 +213,10 @@ dust_status dust_emit_sed(dust_plan* plan, int64_t n_cells,
                           const float* T, int64_t ldt, const float* m_dust,
                           float* L, int64_t ldl, void* stream);
 
-/* Eqs. 6, 7, 9-10 in one call: H stays on chip and never reaches device
- * memory (one launch over cell tiles, or, for few cells, one for the
- * temperatures and one for the emission).  Same results as absorb -> solve -> emit. */
+/* Eqs. 6, 7, 9-10 in one call, as one launch over cell tiles or, where that
+ * is faster (few cells, and DUST_PLAIN_FP32), as one per step; no H array is
+ * needed (the plain form rests it in T or L before they are written).  Same
+ * results as absorb -> solve -> emit. */
 dust_status dust_run_fused(dust_plan* plan, int64_t n_cells,
                            const float* J, int64_t ldj, const float* m_dust,
                            float* T, int64_t ldt, float* L, int64_t ldl,

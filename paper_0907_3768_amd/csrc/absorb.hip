@@ -24,7 +24,8 @@ namespace {
 template <int MODE, int NTW>
 __global__ __launch_bounds__(256) void absorb_kernel(PlanView v, int64_t C,
                                                      const float* __restrict__ J, int64_t ldj,
-                                                     float* __restrict__ H, int64_t ldh) {
+                                                     float* __restrict__ H, int64_t ldh,
+                                                     bool scaled) {
     extern __shared__ float lds[];  // sH [16][Sp], then the J staging buffers
     float* sH = lds;
     char* sStage = reinterpret_cast<char*>(lds + 16 * v.Sp);
@@ -33,7 +34,7 @@ __global__ __launch_bounds__(256) void absorb_kernel(PlanView v, int64_t C,
     __syncthreads();
     for (int i = threadIdx.x; i < 16 * v.Sp; i += 256) {
         const int cc = i / v.Sp, s = i - cc * v.Sp;
-        if (s < v.S && c0 + cc < C) H[(c0 + cc) * ldh + s] = sH[i] * v.hinv[s];
+        if (s < v.S && c0 + cc < C) H[(c0 + cc) * ldh + s] = scaled ? sH[i] : sH[i] * v.hinv[s];
     }
 }
 
@@ -665,10 +666,9 @@ hipError_t launch_gemm(const PlanView& v, int64_t C, const float* J, int64_t ldj
     return hipGetLastError();
 }
 
-template <int NTW>
-hipError_t launch_ntw(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
-                      int64_t ldh, hipStream_t st) {
-    if (table_mode(v.mode) && gemm_fits()) {  // blocked bf16 hi+lo heating
+hipError_t launch_bf16(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
+                       int64_t ldh, hipStream_t st) {
+    if (gemm_fits()) {  // blocked bf16 hi+lo heating
         const int tiles = v.Sp / 16;
         if (tiles <= 2) return launch_gemm<2>(v, C, J, ldj, H, ldh, st);
         if (tiles <= 4) return launch_gemm<4>(v, C, J, ldj, H, ldh, st);
@@ -677,29 +677,42 @@ hipError_t launch_ntw(const PlanView& v, int64_t C, const float* J, int64_t ldj,
         if (tiles <= 12) return launch_gemm<12>(v, C, J, ldj, H, ldh, st);
         return launch_gemm<16>(v, C, J, ldj, H, ldh, st);  // passes of 16 tiles
     }
-    if (table_mode(v.mode)) {  // bf16 hi+lo heating, 64 cells per workgroup
-        constexpr int MB = 4;
-        const dim3 grid((unsigned)((C + 16 * MB - 1) / (16 * MB)));
-        const int tiles = v.Sp / 16;
-        if (tiles <= 4)  // four waves, one grain tile each
-            hipLaunchKernelGGL((absorb_mb_kernel<1, MB, 4>), grid, dim3(256), 0, st, v, C, J, ldj,
-                               H, ldh);
-        else if (tiles <= 8)
-            hipLaunchKernelGGL((absorb_mb_kernel<1, MB, 8>), grid, dim3(512), 0, st, v, C, J, ldj,
-                               H, ldh);
-        else if (tiles <= 16)
-            hipLaunchKernelGGL((absorb_mb_kernel<2, MB, 8>), grid, dim3(512), 0, st, v, C, J, ldj,
-                               H, ldh);
-        else  // four tiles per wave and pass; more passes above 32 tiles
-            hipLaunchKernelGGL((absorb_mb_kernel<4, MB, 8>), grid, dim3(512), 0, st, v, C, J, ldj,
-                               H, ldh);
-        return hipGetLastError();
-    }
+    // bf16 hi+lo heating, 64 cells per workgroup
+    constexpr int MB = 4;
+    const dim3 grid((unsigned)((C + 16 * MB - 1) / (16 * MB)));
+    const int tiles = v.Sp / 16;
+    if (tiles <= 4)  // four waves, one grain tile each
+        hipLaunchKernelGGL((absorb_mb_kernel<1, MB, 4>), grid, dim3(256), 0, st, v, C, J, ldj,
+                           H, ldh);
+    else if (tiles <= 8)
+        hipLaunchKernelGGL((absorb_mb_kernel<1, MB, 8>), grid, dim3(512), 0, st, v, C, J, ldj,
+                           H, ldh);
+    else if (tiles <= 16)
+        hipLaunchKernelGGL((absorb_mb_kernel<2, MB, 8>), grid, dim3(512), 0, st, v, C, J, ldj,
+                           H, ldh);
+    else  // four tiles per wave and pass; more passes above 32 tiles
+        hipLaunchKernelGGL((absorb_mb_kernel<4, MB, 8>), grid, dim3(512), 0, st, v, C, J, ldj,
+                           H, ldh);
+    return hipGetLastError();
+}
+
+template <int NTW>
+hipError_t launch_f32_ntw(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
+                          int64_t ldh, bool scaled, hipStream_t st) {
     const dim3 grid((unsigned)((C + 15) / 16));
     const size_t lds = sizeof(float) * 16 * v.Sp + STAGE_BYTES;
     hipLaunchKernelGGL((absorb_kernel<DUST_PLAIN_FP32, NTW>), grid, dim3(256), lds, st, v, C, J,
-                       ldj, H, ldh);
+                       ldj, H, ldh, scaled);
     return hipGetLastError();
+}
+
+hipError_t launch_f32(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
+                      int64_t ldh, bool scaled, hipStream_t st) {
+    const int ntw = (v.Sp / 16 + 3) / 4;  // grain tiles per wave in one pass (several above 4)
+    if (ntw <= 1) return launch_f32_ntw<1>(v, C, J, ldj, H, ldh, scaled, st);
+    if (ntw <= 2) return launch_f32_ntw<2>(v, C, J, ldj, H, ldh, scaled, st);
+    if (ntw <= 3) return launch_f32_ntw<3>(v, C, J, ldj, H, ldh, scaled, st);
+    return launch_f32_ntw<4>(v, C, J, ldj, H, ldh, scaled, st);
 }
 
 }  // namespace
@@ -707,12 +720,14 @@ hipError_t launch_ntw(const PlanView& v, int64_t C, const float* J, int64_t ldj,
 hipError_t launch_absorb(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
                          int64_t ldh, hipStream_t st) {
     if (C == 0) return hipSuccess;
-    const int ntw = (v.Sp / 16 + 3) / 4;  // grain tiles per wave in one pass
-    if (ntw <= 1) return launch_ntw<1>(v, C, J, ldj, H, ldh, st);
-    if (ntw <= 2) return launch_ntw<2>(v, C, J, ldj, H, ldh, st);
-    if (ntw <= 3) return launch_ntw<3>(v, C, J, ldj, H, ldh, st);
-    if (ntw <= 4) return launch_ntw<4>(v, C, J, ldj, H, ldh, st);
-    return launch_ntw<4>(v, C, J, ldj, H, ldh, st);  // several passes
+    return table_mode(v.mode) ? launch_bf16(v, C, J, ldj, H, ldh, st)
+                              : launch_f32(v, C, J, ldj, H, ldh, false, st);
+}
+
+hipError_t launch_absorb_scaled(const PlanView& v, int64_t C, const float* J, int64_t ldj,
+                                float* H, int64_t ldh, hipStream_t st) {
+    if (C == 0) return hipSuccess;
+    return launch_f32(v, C, J, ldj, H, ldh, true, st);
 }
 
 }  // namespace dust

@@ -196,13 +196,14 @@ dust_status dust_plan_create(const dust_grid_desc* g, const dust_options* opt, d
     p->opt = o;
     p->NL = NL; p->S = S; p->NLp = NLp; p->Sp = Sp;
     p->ge = ge;
-    p->N = o.ltab_n;
-    const bool lin = o.mode == DUST_TABLE_LINEAR;
+    const bool lin = o.mode == DUST_TABLE_LINEAR, plain = o.mode == DUST_PLAIN_FP32;
+    p->N = plain ? PLAIN_N : o.ltab_n;
     // nodes of the inverse table (mixed: a start for Newton only) or of the
     // search brackets (table-linear)
     p->M = lin ? 2048 : (o.ltab_n < 256 ? o.ltab_n : 256);
-    p->lnTmin = log(o.ltab_tmin);
-    p->hstep = (log(o.ltab_tmax) - log(o.ltab_tmin)) / (p->N - 1);
+    const double tlo = plain ? PLAIN_TMIN : o.ltab_tmin, thi = plain ? PLAIN_TMAX : o.ltab_tmax;
+    p->lnTmin = log(tlo);
+    p->hstep = (log(thi) - log(tlo)) / (p->N - 1);
     const double tstep = (o.ltab_tmax - o.ltab_tmin) / (p->N - 1);
     const bool mixed = table_mode(o.mode);
 
@@ -229,8 +230,8 @@ dust_status dust_plan_create(const dust_grid_desc* g, const dust_options* opt, d
     ALLOC(p->d_klo, (size_t)Sp * NLp);
     ALLOC(p->d_kdb, (size_t)S * NL);
     ALLOC(p->d_c2l, NL);
+    ALLOC(p->d_fwd, (size_t)S * p->N);
     if (mixed) {
-        ALLOC(p->d_fwd, (size_t)S * p->N);
         if (lin) {
             ALLOC(p->d_kidx, (size_t)S * p->M);
         } else {

@@ -30,20 +30,79 @@ __device__ __forceinline__ void wave_count_add(int64_t* field, int n) {
         atomicAdd(reinterpret_cast<unsigned long long*>(field), (unsigned long long)n);
 }
 
+// Whether the Newton step from a residual r = ln(P/H) ends the iteration: r is
+// within the tolerance, or the residual the step leaves is: r^2 K / 2 with
+// K = y''/y'^2 of y = ln P(ln T), at most 0.1 on the emission of real grains
+// (0.01 typically) and below 1 for any sum of Planck terms that a grid
+// resolves, so r^2 <= tol / 2.5 leaves at most tol / 5 and tol / 50 as a rule.
+__device__ __forceinline__ bool newton_accepts(float r, float tol) {
+    return fabsf(r) <= tol || 2.5f * r * r <= tol;
+}
+
+// ---------------------------------------------------------------------------
+// Start of the plain Newton: its first iterations, from x (the Eq. 11 guess or
+// a previous solution), on the grain's table of ln P' (the cubic through four
+// of its points) instead of the full sum -- a few loads in place of NL terms.
+// A start that the table already accepts stays.  Stops once the table's
+// residual is below 1e-4 (the step that follows leaves about 1e-9, far below
+// the table's own error), at the table's ends, or after six; *it receives the
+// iterations.  Small iteration caps and a table that is not finite (NaN steps)
+// leave x.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ float newton_start(const PlanView& v, int s, float lnH, float x,
+                                              int* it) {
+    *it = 0;
+    if (v.maxit < PLAIN_TABLE_MAXIT) return x;
+    const double* __restrict__ f = v.fwd + (int64_t)s * PLAIN_N;
+    const float x0 = (float)v.lnTmin, h = (float)v.hstep, hinv = 1.0f / h;
+    float u = (x - x0) * hinv;  // position in the table, in node spacings
+    const bool inside = u >= 0.0f && u <= (float)(PLAIN_N - 1);
+    for (int k = 0; k < 6; ++k) {
+        u = fminf(fmaxf(u, 0.0f), (float)(PLAIN_N - 1));
+        int j = (int)u - 1;
+        j = j < 0 ? 0 : (j > PLAIN_N - 4 ? PLAIN_N - 4 : j);
+        // relative to ln H, so that FP32 holds the differences
+        const float y0 = (float)(f[j] - (double)lnH), y1 = (float)(f[j + 1] - (double)lnH);
+        const float y2 = (float)(f[j + 2] - (double)lnH), y3 = (float)(f[j + 3] - (double)lnH);
+        const float t = u - (float)j, d1 = y1 - y0, d2 = 0.5f * (y2 - 2.0f * y1 + y0);
+        const float d3 = (y3 - 3.0f * (y2 - y1) - y0) * (1.0f / 6.0f);
+        const float r = y0 + t * (d1 + (t - 1.0f) * (d2 + (t - 2.0f) * d3));
+        const float dp = d1 + (2.0f * t - 1.0f) * d2 +
+                         (t * (t - 1.0f) + t * (t - 2.0f) + (t - 1.0f) * (t - 2.0f)) * d3;
+        if (k == 0 && inside && newton_accepts(r, v.tol)) break;
+        const float step = r / dp;
+        if (!(fabsf(step) < 1e6f)) { *it = 0; break; }  // not finite
+        *it = k + 1;
+        u -= step;
+        if (fabsf(r) <= 1e-4f || u < -1.0f || u > (float)PLAIN_N) break;
+    }
+    return *it == 0 ? x : x0 + h * fminf(fmaxf(u, 0.0f), (float)(PLAIN_N - 1));
+}
+
+// ln(P / H): of the ratio once it is near 1, since ln P and ln H apart carry the
+// rounding of values up to 80 (4e-6 in the residual, half a microkelvin per
+// kelvin in T).
+__device__ __forceinline__ float newton_residual(float p, float hs, float lnH) {
+    const float q = p / hs;
+    return (q > 0.5f && q < 2.0f) ? logf(q) : logf(p) - lnH;
+}
+
 // ---------------------------------------------------------------------------
 // Plain FP32 solve of Eq. 7 for one pair (Section 4.3): Newton's method on
 // ln P(T) = ln H in the variable ln T from the Eq. 11 guess, with a bracket
-// safeguard.  Stops when |ln(P/H)| <= tol and then applies the Newton step
-// already computed.  `kb` is the grain's row of K' c1 lam^-5 (stride 1);
+// safeguard, the first iterations on the grain's table (newton_start).  Stops
+// when newton_accepts ln(P/H) and then applies the Newton step already
+// computed.  `kb` is the grain's row of K' c1 lam^-5 (stride 1);
 // `nu` the wavelength table.  A finite tstart > 0 (a previous solution)
 // replaces the guess as the starting point.  Returns T; *evals receives the
 // number of evaluations of the sum.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ float solve_newton_f32(const float* __restrict__ kb,
-                                                  const float* __restrict__ nu,
-                                                  int NL, float hs, float gs,
-                                                  float tol, int maxit, float tstart,
-                                                  int* evals, dust_counters* cnt) {
+__device__ __forceinline__ float solve_newton_f32(const PlanView& v, int s, float hs,
+                                                  float tstart, int* evals, dust_counters* cnt) {
+    const float* __restrict__ kb = v.kb + (int64_t)s * v.NLp;
+    const float* __restrict__ nu = v.nu;
+    const int NL = v.NL, maxit = v.maxit;
+    const float gs = v.gs[s], tol = v.tol;
     *evals = 0;
     if (!(hs >= 0.0f) || __builtin_isinf(hs)) {
         if (cnt) count(&cnt->n_nonfinite);
@@ -52,10 +111,11 @@ __device__ __forceinline__ float solve_newton_f32(const float* __restrict__ kb,
     if (hs == 0.0f) return 0.0f;
 
     const float lnH = logf(hs);
-    float lnT = (tstart > 0.0f && tstart < INFINITY) ? logf(tstart) : guess_lnT(hs, gs);
-    float lo = -INFINITY, hi = INFINITY;
-    bool done = false;
     int it = 0;
+    float lnT = newton_start(
+        v, s, lnH, (tstart > 0.0f && tstart < INFINITY) ? logf(tstart) : guess_lnT(hs, gs), &it);
+    float lo = -INFINITY, hi = INFINITY, T = 0.0f;
+    bool done = false;
     for (; it < maxit; ++it) {
         const float invT = expf(-lnT);
         float p0 = 0.f, p1 = 0.f, d0 = 0.f, d1 = 0.f;
@@ -101,12 +161,12 @@ __device__ __forceinline__ float solve_newton_f32(const float* __restrict__ kb,
             lnT = (hi < INFINITY) ? 0.5f * (lo + hi) : fmaxf(lnT + 1.0f, guess_lnT(hs, gs));
             continue;
         }
-        const float r = logf(P) - lnH;           // ln(P / H)
+        const float r = newton_residual(P, hs, lnH);
         const float slope = -0.69314718f * D / P;  // d ln P / d ln T
         if (r < 0.0f) lo = lnT; else hi = lnT;
         float next = lnT - r / slope;
-        if (fabsf(r) <= tol) {
-            lnT = next;
+        if (newton_accepts(r, tol)) {
+            T = expf(-r / slope) / invT;  // (ln T itself would round to 2e-7)
             done = true;
             break;
         }
@@ -117,7 +177,7 @@ __device__ __forceinline__ float solve_newton_f32(const float* __restrict__ kb,
     }
     *evals = done ? it + 1 : it;
     if (!done && cnt) count(&cnt->n_unconverged);
-    return expf(lnT);
+    return done ? T : expf(lnT);
 }
 
 // ---------------------------------------------------------------------------
@@ -156,54 +216,74 @@ __device__ __forceinline__ float wave_min_f32(float x) {
 }
 
 // First wavelength index l with u_l < lim, where u_l = -nu[l] decreases with
-// l (NL if none); lim is wave-uniform, so the search runs on scalar loads.
+// l (NL if none); lim is wave-uniform.  A 64-way search: each round a wave
+// loads 64 wavelengths and counts those at or above lim, so grids up to 4096
+// wavelengths take two dependent loads (a binary search on scalar loads takes
+// ten, which a wave on its own waits out twice per Newton iteration).  Every
+// lane of the wave must call it.
 __device__ __forceinline__ int first_u_below(const float* __restrict__ nu, int NL, float lim) {
-    int a = 0, b = NL;
-    while (a < b) {
-        const int mid = (a + b) >> 1;
-        if (-nu[mid] < lim) b = mid; else a = mid + 1;
+    const int lane = threadIdx.x & 63;
+    int a = 0, n = NL;  // the answer lies in [a, a + n]
+    while (n > 0) {
+        const int st = (n + 63) >> 6;  // lane i probes the last of its st wavelengths
+        const int i = (lane + 1) * st - 1;
+        const bool above = i < n && -nu[a + i] >= lim;
+        const int full = __popcll(__ballot(above));  // segments wholly at or above lim
+        a += full * st;
+        n = n - full * st < st - 1 ? n - full * st : st - 1;
     }
     return a;
 }
 
 // ---------------------------------------------------------------------------
-// Plain FP32 solve of Eq. 7 for one grain and up to 64 cells, one cell per
-// lane: the iteration of solve_newton_f32 (Newton on ln P = ln H in ln T,
-// bracket safeguard, stop at |ln(P/H)| <= tol after applying the step),
-// with the grain's weights wave-uniform (scalar loads) and the sums of
-// Eq. 7 split by wavelength at every evaluation from the wave's hottest
+// Plain FP32 solve of Eq. 7 for one grain and 64 / R cells, R lanes per cell
+// (lanes R c .. R c + R - 1): the iteration of solve_newton_f32, with the sums
+// of Eq. 7 split by wavelength at every evaluation from the wave's hottest
 // active cell, t = u_l / T:
 //   t >= 150 for every lane: the term is exactly 0 in FP32, skipped;
 //   t >= 24 for every lane: 1/(2^t - 1) = 2^-t to FP32 rounding (one
 //                           exponential, no reciprocal);
 //   otherwise: the exact 1/(2^t - 1).
 // The slope uses ku = kb u: T dP/dT = ln 2 / T sum_l ku_l r (1 + r).
+// R = 1: the grain's weights are wave-uniform (scalar loads), a cell per lane.
+// R = 4: the four lanes of a cell take four consecutive wavelengths each of
+// every 16 (one 16-byte load per table, up to the padded NLp, where the
+// weights are zero) and add their sums: four times the waves and a quarter of
+// the chain, for calls that leave the chip idle; its loads would bind a full
+// one (three 1 KB loads per four terms against scalar ones).
 // Every lane of the wave must call it (`live` false for a lane without a
-// pair).  *evals receives the lane's number of evaluations.
+// pair).  *evals receives the cell's iterations (0 in all but its first lane).
 // ---------------------------------------------------------------------------
-__device__ inline float solve_newton_wave(const float* __restrict__ kb,
-                                          const float* __restrict__ ku,
-                                          const float* __restrict__ nu, int NL, bool live,
-                                          float hs, float gs, float tol, int maxit, float tstart,
-                                          int* evals, dust_counters* cnt) {
-    int nev = 0;
+template <int R>
+__device__ inline float solve_newton_wave(const PlanView& v, int s, bool live, float hs,
+                                          float tstart, int* evals, dust_counters* cnt) {
+    const float* __restrict__ kb = v.kb + (int64_t)s * v.NLp;
+    const float* __restrict__ ku = v.ku + (int64_t)s * v.NLp;
+    const float* __restrict__ nu = v.nu;
+    const int NL = v.NL, maxit = v.maxit;
+    const float gs = v.gs[s], tol = v.tol;
+    const int q = threadIdx.x & (R - 1);
     float result = 0.0f;
     bool active = false;
     float lnH = 0.0f, lnT = 0.0f;
+    int nev = 0;  // iterations
     if (live) {
         if (!(hs >= 0.0f) || __builtin_isinf(hs)) {
-            if (cnt) count(&cnt->n_nonfinite);
+            if (cnt && q == 0) count(&cnt->n_nonfinite);
             result = __builtin_nanf("");
         } else if (hs > 0.0f) {
             active = true;
             lnH = logf(hs);
-            lnT = (tstart > 0.0f && tstart < INFINITY) ? logf(tstart) : guess_lnT(hs, gs);
+            lnT = newton_start(
+                v, s, lnH,
+                (tstart > 0.0f && tstart < INFINITY) ? logf(tstart) : guess_lnT(hs, gs), &nev);
         }
     }
     const bool solving = active;
     float lo = -INFINITY, hi = INFINITY;
     bool done = false;
-    for (int it = 0; it < maxit; ++it) {
+    for (;;) {
+        active = active && nev < maxit;
         if (__ballot(active) == 0) break;
         const float invT = active ? expf(-lnT) : INFINITY;
         // hottest active cell; the split only chooses between forms that are
@@ -212,17 +292,45 @@ __device__ inline float solve_newton_wave(const float* __restrict__ kb,
         const int l1 = first_u_below(nu, NL, 150.0f * tinv);
         const int l2 = first_u_below(nu, NL, 24.0f * tinv);
         float p = 0.0f, d = 0.0f;
+        auto wien = [&](float n, float b, float u) {
+            const float y = __builtin_amdgcn_exp2f(n * invT);
+            p = fmaf(b, y, p);
+            d = fmaf(u, y, d);
+        };
+        auto planck = [&](float n, float b, float u) {
+            const float r = __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(-(n * invT)) - 1.0f);
+            p = fmaf(b, r, p);
+            d = fmaf(u, fmaf(r, r, r), d);
+        };
+        if constexpr (R == 1) {
+            // (constant address space: scalar loads, although T may alias as
+            // far as the compiler can tell)
+            typedef const __attribute__((address_space(4))) float* Table;
+            const Table n = (Table)nu, b = (Table)kb, u = (Table)ku;
 #pragma unroll 4
-        for (int l = l1; l < l2; ++l) {
-            const float y = __builtin_amdgcn_exp2f(nu[l] * invT);
-            p = fmaf(kb[l], y, p);
-            d = fmaf(ku[l], y, d);
-        }
+            for (int l = l1; l < l2; ++l) wien(n[l], b[l], u[l]);
 #pragma unroll 4
-        for (int l = l2; l < NL; ++l) {
-            const float r = __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(-(nu[l] * invT)) - 1.0f);
-            p = fmaf(kb[l], r, p);
-            d = fmaf(ku[l], fmaf(r, r, r), d);
+            for (int l = l2; l < NL; ++l) planck(n[l], b[l], u[l]);
+        } else {
+            static_assert(R == 4, "lanes per cell");
+            auto four = [&](int l, auto term) {
+                const float4 n = *reinterpret_cast<const float4*>(nu + l);
+                const float4 b = *reinterpret_cast<const float4*>(kb + l);
+                const float4 u = *reinterpret_cast<const float4*>(ku + l);
+                term(n.x, b.x, u.x);
+                term(n.y, b.y, u.y);
+                term(n.z, b.z, u.z);
+                term(n.w, b.w, u.w);
+            };
+            const int m1 = l1 & ~15, m2 = l2 & ~15;
+#pragma unroll 2
+            for (int l = m1 + 4 * q; l < m2; l += 16) four(l, wien);
+#pragma unroll 2
+            for (int l = m2 + 4 * q; l < v.NLp; l += 16) four(l, planck);
+            p += __shfl_xor(p, 1, 64);
+            d += __shfl_xor(d, 1, 64);
+            p += __shfl_xor(p, 2, 64);
+            d += __shfl_xor(d, 2, 64);
         }
         if (active) {
             ++nev;
@@ -236,12 +344,12 @@ __device__ inline float solve_newton_wave(const float* __restrict__ kb,
                 lo = lnT;
                 lnT = (hi < INFINITY) ? 0.5f * (lo + hi) : fmaxf(lnT + 1.0f, guess_lnT(hs, gs));
             } else {
-                const float r = logf(p) - lnH;                 // ln(P / H)
+                const float r = newton_residual(p, hs, lnH);
                 const float slope = 0.69314718f * invT * d / p;  // d ln P / d ln T
                 if (r < 0.0f) lo = lnT; else hi = lnT;
                 float next = lnT - r / slope;
-                if (fabsf(r) <= tol) {
-                    lnT = next;
+                if (newton_accepts(r, tol)) {
+                    result = expf(-r / slope) / invT;  // (ln T itself would round to 2e-7)
                     done = true;
                     active = false;
                 } else {
@@ -253,9 +361,9 @@ __device__ inline float solve_newton_wave(const float* __restrict__ kb,
             }
         }
     }
-    *evals = nev;
-    if (solving) {
-        if (!done && cnt) count(&cnt->n_unconverged);
+    *evals = q == 0 ? nev : 0;
+    if (solving && !done) {
+        if (cnt && q == 0) count(&cnt->n_unconverged);
         result = expf(lnT);
     }
     return result;

@@ -56,9 +56,9 @@ __global__ __launch_bounds__(64) void heat_solve_kernel(PlanView v, int64_t C,
                                                         const float* __restrict__ J, int64_t ldj,
                                                         float* __restrict__ T, int64_t ldt,
                                                         dust_counters* cnt) {
-    const HeatTile ht = heat_tile(blockIdx.x, v.Sp / 16);
+    const HeatTile ht = heat_tile<16>(blockIdx.x, v.Sp / 16);
     if (ht.c0 >= C) return;
-    const f32x4 acc = heat_wave<true, ALIGNED>(v, ht.c0, C, ht.tile, J, ldj);
+    const f32x4 acc = heat_wave<true, ALIGNED, 4>(v, ht.c0, C, ht.tile, J, ldj);
     const int lane = threadIdx.x & 63;
     const int s_raw = 16 * ht.tile + (lane & 15);
     const int s = s_raw < v.S ? s_raw : v.S - 1;  // a lane past the last grain looks it up unused
@@ -118,7 +118,7 @@ __global__ __launch_bounds__(64) void heat_solve_kernel(PlanView v, int64_t C,
 template <bool ALIGNED>
 hipError_t launch_heat_solve(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* T,
                              int64_t ldt, dust_counters* cnt, hipStream_t st) {
-    const dim3 grid(heat_blocks(C, v.Sp / 16));
+    const dim3 grid(heat_blocks<16>(C, v.Sp / 16));
     const int km = kernel_mode(v);
     if (km == DUST_MIXED)
         hipLaunchKernelGGL((heat_solve_kernel<DUST_MIXED, ALIGNED>), grid, dim3(64), 0, st, v, C,
@@ -215,12 +215,26 @@ bool split_pays(const PlanView& v, int64_t C) {
                                    : C <= 16 * SPLIT_TILES && work >= SPLIT_WORK;
 }
 
-// Whether two arrays of a and b floats share memory.  The heating's waves read
-// rows of J that another wave's T may replace then; the fused kernel reads a
-// tile's rows before it writes them.
+// Whether two arrays of a and b floats share memory.  A call whose input shares
+// memory with an output stays one kernel, which reads a tile's rows before it
+// writes them.
 bool share_memory(const float* x, int64_t a, const float* y, int64_t b) {
     const uintptr_t px = (uintptr_t)x, py = (uintptr_t)y;
     return px < py + 4 * (uintptr_t)b && py < px + 4 * (uintptr_t)a;
+}
+
+// The plain fused call as the kernels of its three steps, so that the Newton
+// sums run on scalar weights (a fused tile's 16 cells give each lane its own
+// grain's, through vector loads: 30001 x 251 x 77 1205 us in one kernel).  The
+// scaled heating H' rests in the call's own output until the solve reads it:
+// in T, solved in place, or, when T holds the start temperatures, in L.
+hipError_t launch_heat_newton(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* T,
+                              int64_t ldt, float* L, int64_t ldl, dust_counters* cnt,
+                              hipStream_t st) {
+    float* H = v.warm ? L : T;
+    const int64_t ldh = v.warm ? ldl : ldt;
+    const hipError_t e = launch_absorb_scaled(v, C, J, ldj, H, ldh, st);
+    return e != hipSuccess ? e : launch_solve_plain(v, C, H, ldh, T, ldt, true, cnt, st);
 }
 
 }  // namespace
@@ -229,8 +243,16 @@ hipError_t launch_fused(const PlanView& v, int64_t C, const float* J, int64_t ld
                         float* T, int64_t ldt, float* L, int64_t ldl, dust_counters* cnt,
                         bool one_kernel, hipStream_t st) {
     if (C == 0) return hipSuccess;
+    const int64_t nj = (C - 1) * ldj + v.NL, nt = (C - 1) * ldt + v.S, nl = (C - 1) * ldl + v.NL;
+    const int64_t nq = (C - 1) * v.ldq + v.S;
+    if (!one_kernel && !table_mode(v.mode) && (!v.warm || v.S <= v.NL) &&
+        !share_memory(J, nj, T, nt) && !share_memory(J, nj, L, nl) &&
+        !(v.q && (share_memory(v.q, nq, T, nt) || share_memory(v.q, nq, L, nl)))) {
+        const hipError_t e = launch_heat_newton(v, C, J, ldj, T, ldt, L, ldl, cnt, st);
+        return e != hipSuccess ? e : launch_emit(v, C, T, ldt, m, L, ldl, st);
+    }
     if (!one_kernel && table_mode(v.mode) && split_pays(v, C) &&
-        !share_memory(J, (C - 1) * ldj + v.NL, T, (C - 1) * ldt + v.S)) {
+        !share_memory(J, nj, T, nt)) {
         const hipError_t e = rows_aligned16(J, ldj)
                                  ? launch_heat_solve<true>(v, C, J, ldj, T, ldt, cnt, st)
                                  : launch_heat_solve<false>(v, C, J, ldj, T, ldt, cnt, st);

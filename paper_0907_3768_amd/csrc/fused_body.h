@@ -245,8 +245,7 @@ __device__ __forceinline__ void fused_solve(const PlanView& v, int64_t c0, int64
             } else {
                 const float t0 = v.warm ? T[c * ldt + s] : 0.0f;
                 int ev;
-                t = solve_newton_f32(v.kb + (int64_t)s * v.NLp, v.nu, v.NL, h, v.gs[s], v.tol,
-                                     v.maxit, t0, &ev, cnt);
+                t = solve_newton_f32(v, s, h, t0, &ev, cnt);
                 evals += ev;
             }
             T[c * ldt + s] = t;

@@ -23,6 +23,14 @@ constexpr int PAD_S = 16;
 constexpr int COLD_N = 128, COLD_M = 128;
 constexpr double COLD_RATIO = 3.0;
 
+// The plain solve's table: ln P' at PLAIN_N log-spaced T, where Newton's first
+// iterations run.  At 0.064 in ln T its cubic interpolation is good to about
+// 1e-6, so that one iteration on the full sum is left.
+constexpr int PLAIN_N = 128;
+constexpr double PLAIN_TMIN = 0.9, PLAIN_TMAX = 3000.0;
+// Iteration caps below this count iterations on the full sum only.
+constexpr int PLAIN_TABLE_MAXIT = 8;
+
 // Exact SI constants (2019 SI) and the derived radiation constants.
 constexpr double PLANCK_H = 6.62607015e-34;
 constexpr double LIGHT_C = 299792458.0;
@@ -42,7 +50,7 @@ struct PlanView {
     int maxit;
     float tol;
     // wavelength tables [NLp]
-    const float* nu;       // -c2 log2(e) / lam  (0 on padding)
+    const float* nu;       // -c2 log2(e) / lam  (the last value on padding)
     // per-grain tables [Sp]
     const float* hscale;   // 2^es: H' = H * hscale (exact)
     const float* hinv;     // 2^-es
@@ -59,6 +67,7 @@ struct PlanView {
     const double* kdb;     // [S][NL] K' c1 lam^-5 (FP64): exact power weights
     const double* c2l;     // [NL] c2 / lam (FP64)
     const double* fwd;     // [S][N] y_k = ln P'(T_k), T_k = exp(lnTmin + k hstep)
+                           // (plain: N = PLAIN_N, where Newton starts)
     const double* ylo;     // [S] y_0
     const double* yhi;     // [S] y_{N-1}
     const double* dyinv;   // [S] (M - 1) / (yhi - ylo)
@@ -173,6 +182,12 @@ hipError_t launch_prepare_batched(const RefreshJob* d_jobs, const int* const d_s
                                   int n_jobs, const int blocks[4], hipStream_t st);
 hipError_t launch_absorb(const PlanView& v, int64_t C, const float* J, int64_t ldj,
                          float* H, int64_t ldh, hipStream_t st);
+// Plain: the scaled heating H' (the plan's units), and the solve of either.  H
+// may be T.
+hipError_t launch_absorb_scaled(const PlanView& v, int64_t C, const float* J, int64_t ldj,
+                                float* H, int64_t ldh, hipStream_t st);
+hipError_t launch_solve_plain(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
+                              int64_t ldt, bool scaled, dust_counters* cnt, hipStream_t st);
 hipError_t launch_solve(const PlanView& v, int64_t C, const float* H, int64_t ldh,
                         float* T, int64_t ldt, dust_counters* cnt, hipStream_t st);
 // Kernel forms: the public modes, plus the mixed mode with the FP32

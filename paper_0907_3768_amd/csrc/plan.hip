@@ -15,6 +15,8 @@
 //        piecewise cubic, stored as FP64 nodes and as FP32 pairs of nodes (one
 //        16-byte load per lookup).  A second, smaller pair of tables below the
 //        range makes the lookups of colder grains.
+//  plain: the same product at a few log-spaced T (y_k only), where Newton's
+//        first iterations run.
 //  table-linear mode: the same matrix product gives P'(T_k) itself at evenly
 //        spaced T_k (the production table of Sections 2 and 5); kidx gives,
 //        at uniform steps of ln P', the last table point below, so that a
@@ -45,7 +47,8 @@ __device__ __forceinline__ void prep_body(const RefreshJob& j, int bx, int by) {
     // wave's fragment of one grain tile and k-step is a contiguous 1 KB.
     const int64_t ob = kfrag_bf16(v, s, l), of = kfrag_f32(v, s, l);
     if (s == 0) {
-        nu[l] = (l < v.NL) ? (float)(-RAD_C2 * LOG2E / lam[l]) : -1.0f;
+        // (padding repeats the last: its terms have zero weight and stay finite)
+        nu[l] = (float)(-RAD_C2 * LOG2E / lam[l < v.NL ? l : v.NL - 1]);
         if (l < v.NL) c2l[l] = RAD_C2 / lam[l];
     }
     if (s < v.S && l < v.NL) {
@@ -395,8 +398,9 @@ hipError_t launch_prepare(const dust_plan* p, hipStream_t st) {
     RefreshJob j;
     make_refresh_job(p, &j);
     hipError_t e = launch_stage<0>(j, st);
+    if (e != hipSuccess) return e;
+    e = launch_stage<2>(j, st);
     if (e != hipSuccess || !table_mode(j.v.mode)) return e;
-    if ((e = launch_stage<2>(j, st)) != hipSuccess) return e;
     return launch_stage<3>(j, st);
 }
 

@@ -1,13 +1,13 @@
 // Temperature solve, Eq. 7 (Section 4.3).
 //
-// Plain FP32: a workgroup takes a tile of 64 cells x up to 16 grains.  The
-// tile's heating (plus the extra term) is staged in LDS with coalesced
-// loads; each wave then solves one grain at a time for the 64 cells (one
-// cell per lane), as the paper's third kernel gives a block one species, so
-// the grain's Planck weights and the wavelength table are wave-uniform and
-// come through the scalar cache.  T goes back through the same LDS slots and
-// leaves with coalesced stores; the Newton evaluations of the block are
-// counted with one atomic.
+// Plain FP32: a workgroup takes a tile of 64 (or 16) cells x 4 grains.  The
+// tile's heating (plus the extra term) is staged in LDS; each wave then solves
+// one grain for the tile's cells (a cell per lane, or per four lanes), as the
+// paper's third kernel gives a block one species, so the grain's Planck
+// weights and the wavelength table are wave-uniform and come through the
+// scalar cache.  Newton's first iterations run on the grain's table of ln P',
+// which leaves one evaluation of the full sum as a rule.  T goes back through
+// the same LDS slots; the iterations of the block are counted with one atomic.
 // Mixed: four (cell, grain) pairs per thread, 256 apart in row-major order
 // (coalesced H and T), each an O(1) lookup in the grain's inverse table
 // ln T(ln H) (a cubic Hermite in FP64 between FP64 nodes, or in FP32 with the
@@ -20,50 +20,55 @@
 namespace dust {
 namespace {
 
-constexpr int PLAIN_CELLS = 64;    // cells per tile: one per lane
-constexpr int PLAIN_GRAINS = 16;   // grains per tile at most
+constexpr int PLAIN_GRAINS = 4;  // grains per workgroup: one per wave
 
-// LDS row stride of a tile of g grains: odd, so the 64 lanes reading one
-// grain column hit distinct banks.
-__host__ __device__ constexpr int plain_stride(int g) { return g | 1; }
-
+// Plain: a workgroup takes 64 / R cells x 4 grains, a wave one grain for all
+// the cells.  One grain per wave rather than several in turn: more workgroups
+// hide the loads of the weights better and end more evenly (with vector loads,
+// 32768 x 968 x 81: 655 us, 799 with four grains per wave).
+// scaled: H holds the plan's scaled H' (the fused call's own).
+// 32768 x 968 x 81: 1479 us with every iteration on the full sum, 382 with the
+// first ones on the table and the weights as scalar loads; bound by the VALU
+// and transcendental issue of the one evaluation of the full sum that is left
+// (6.7e12 terms/s, a third of them in the cheaper forms).
+template <int R>
 __global__ __launch_bounds__(256) void solve_plain_kernel(PlanView v, int64_t C,
-                                                          const float* __restrict__ H,
-                                                          int64_t ldh, float* __restrict__ T,
-                                                          int64_t ldt, dust_counters* cnt) {
-    extern __shared__ float sX[];  // [64][ST]: heating in, T out
+                                                          const float* H, int64_t ldh, float* T,
+                                                          int64_t ldt, bool scaled,
+                                                          dust_counters* cnt) {
+    constexpr int CELLS = 64 / R;
+    constexpr int ST = PLAIN_GRAINS + 1;  // odd: a grain's column falls on distinct banks
+    __shared__ float sX[CELLS * ST];      // heating in, T out
     __shared__ int sEvals[4];
-    const int64_t c0 = (int64_t)blockIdx.x * PLAIN_CELLS;
+    const int64_t c0 = (int64_t)blockIdx.x * CELLS;
     const int g0 = blockIdx.y * PLAIN_GRAINS;
     const int G = (v.S - g0 < PLAIN_GRAINS) ? v.S - g0 : PLAIN_GRAINS;
-    const int ST = plain_stride(G);
-    const int rows = (C - c0 < PLAIN_CELLS) ? (int)(C - c0) : PLAIN_CELLS;
-    for (int i = threadIdx.x; i < rows * G; i += blockDim.x) {
-        const int cc = i / G, sl = i - cc * G;
+    const int rows = (C - c0 < CELLS) ? (int)(C - c0) : CELLS;
+    // (H may be T: every element is read here before its T is written)
+    for (int i = threadIdx.x; i < rows * PLAIN_GRAINS; i += 256) {
+        const int cc = i / PLAIN_GRAINS, sl = i - cc * PLAIN_GRAINS;
+        if (sl >= G) continue;
         const int64_t c = c0 + cc;
-        float h = H[c * ldh + g0 + sl];
-        if (v.q) h += v.q[c * v.ldq + g0 + sl];
-        sX[cc * ST + sl] = h * v.hscale[g0 + sl];
+        const float h = H[c * ldh + g0 + sl], q = v.q ? v.q[c * v.ldq + g0 + sl] : 0.0f;
+        const float hscale = v.hscale[g0 + sl];
+        sX[cc * ST + sl] = scaled ? h + q * hscale : (h + q) * hscale;
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63;
+    const int cell = (threadIdx.x & 63) / R;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const bool live = lane < rows;
+    const bool live = cell < rows;
     int evals = 0;
-    for (int sl = wave; sl < G; sl += 4) {
-        const int s = g0 + sl;  // wave-uniform: the grain's weights come as scalars
-        const float t0 = (live && v.warm) ? T[(c0 + lane) * ldt + s] : 0.0f;
-        int ev;
-        const float t = solve_newton_wave(v.kb + (int64_t)s * v.NLp, v.ku + (int64_t)s * v.NLp,
-                                          v.nu, v.NL, live, live ? sX[lane * ST + sl] : 0.0f,
-                                          v.gs[s], v.tol, v.maxit, t0, &ev, cnt);
-        if (live) sX[lane * ST + sl] = t;
-        evals += ev;
+    if (wave < G) {
+        const int s = g0 + wave;  // wave-uniform: the grain's weights come as scalars
+        const float t0 = (live && v.warm) ? T[(c0 + cell) * ldt + s] : 0.0f;
+        const float t = solve_newton_wave<R>(v, s, live, live ? sX[cell * ST + wave] : 0.0f, t0,
+                                             &evals, cnt);
+        if (live) sX[cell * ST + wave] = t;  // (the R lanes of a cell hold the same)
     }
     if (cnt) {
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) evals += __shfl_xor(evals, off, 64);
-        if (lane == 0) sEvals[wave] = evals;
+        if ((threadIdx.x & 63) == 0) sEvals[wave] = evals;
     }
     __syncthreads();
     if (cnt && threadIdx.x == 0) {
@@ -71,9 +76,9 @@ __global__ __launch_bounds__(256) void solve_plain_kernel(PlanView v, int64_t C,
         if (n) atomicAdd(reinterpret_cast<unsigned long long*>(&cnt->n_newton_evals),
                          (unsigned long long)n);
     }
-    for (int i = threadIdx.x; i < rows * G; i += blockDim.x) {
-        const int cc = i / G, sl = i - cc * G;
-        T[(c0 + cc) * ldt + g0 + sl] = sX[cc * ST + sl];
+    for (int i = threadIdx.x; i < rows * PLAIN_GRAINS; i += 256) {
+        const int cc = i / PLAIN_GRAINS, sl = i - cc * PLAIN_GRAINS;
+        if (sl < G) T[(c0 + cc) * ldt + g0 + sl] = sX[cc * ST + sl];
     }
 }
 
@@ -193,13 +198,27 @@ hipError_t launch_solve(const PlanView& v, int64_t C, const float* H, int64_t ld
         hipLaunchKernelGGL(solve_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
                            st, v, C, H, ldh, T, ldt, cnt);
     } else {
-        const int gt = (v.S + PLAIN_GRAINS - 1) / PLAIN_GRAINS;
-        const int G = v.S < PLAIN_GRAINS ? v.S : PLAIN_GRAINS;
-        const size_t lds = sizeof(float) * PLAIN_CELLS * plain_stride(G);
-        hipLaunchKernelGGL(solve_plain_kernel,
-                           dim3((unsigned)((C + PLAIN_CELLS - 1) / PLAIN_CELLS), gt), dim3(256),
-                           lds, st, v, C, H, ldh, T, ldt, cnt);
+        return launch_solve_plain(v, C, H, ldh, T, ldt, false, cnt, st);
     }
+    return hipGetLastError();
+}
+
+// Four lanes per cell where the (64 cells, grain) waves leave SIMDs idle: 32 x
+// 968 x 81 29.5 -> 9.9 us, 256 x 250 x 80 12.4 -> 8.4, 1024 x 968 x 81 (1296
+// waves) 33.0 -> 29.2; at 2000 waves (1600 x 250 x 80) 13.9 against 15.6, at
+// 3807 (3000 x 968 x 81) 51.6 against 72.1.
+constexpr int64_t PLAIN_FEW_WAVES = 1536;
+
+hipError_t launch_solve_plain(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
+                              int64_t ldt, bool scaled, dust_counters* cnt, hipStream_t st) {
+    if (C == 0) return hipSuccess;
+    const unsigned gy = (unsigned)((v.S + PLAIN_GRAINS - 1) / PLAIN_GRAINS);
+    if ((C + 63) / 64 * v.S <= PLAIN_FEW_WAVES)
+        hipLaunchKernelGGL(solve_plain_kernel<4>, dim3((unsigned)((C + 15) / 16), gy), dim3(256), 0,
+                           st, v, C, H, ldh, T, ldt, scaled, cnt);
+    else
+        hipLaunchKernelGGL(solve_plain_kernel<1>, dim3((unsigned)((C + 63) / 64), gy), dim3(256), 0,
+                           st, v, C, H, ldh, T, ldt, scaled, cnt);
     return hipGetLastError();
 }
 

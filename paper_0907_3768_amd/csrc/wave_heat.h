@@ -1,14 +1,11 @@
-// Heating of 16 cells x 16 grains by one wave, straight from device memory:
-// the form for calls whose (16 cells, 16 grains) tiles do not fill the chip.
+// Heating of 16 cells x 16 grains by one wave, straight from device memory.
 #pragma once
 
 #include "device_common.h"
 
 namespace dust {
 
-constexpr int HEAT_U = 4;  // k-steps whose loads are in flight together
-
-// The tiles of a call as a 1-D grid of one-wave workgroups.  Workgroups go to
+// The (CELLS cells, 16 grains) tiles of a call as a 1-D grid.  Workgroups go to
 // the eight XCDs in turn, so workgroup b's cell block is taken from b mod 8:
 // every grain tile of a cell block runs on one XCD and its J rows come from
 // that L2 once.
@@ -16,13 +13,15 @@ struct HeatTile {
     int64_t c0;  // first cell
     int tile;    // grain tile
 };
+template <int CELLS>
 __device__ __forceinline__ HeatTile heat_tile(unsigned b, int tiles) {
     const unsigned g = b >> 3;
     const unsigned j = g / (unsigned)tiles;
-    return HeatTile{((int64_t)j * 8 + (b & 7)) * 16, (int)(g - j * (unsigned)tiles)};
+    return HeatTile{((int64_t)j * 8 + (b & 7)) * CELLS, (int)(g - j * (unsigned)tiles)};
 }
-inline unsigned heat_blocks(int64_t C, int tiles) {
-    return (unsigned)(((C + 15) / 16 + 7) / 8 * 8 * tiles);
+template <int CELLS>
+unsigned heat_blocks(int64_t C, int tiles) {
+    return (unsigned)(((C + CELLS - 1) / CELLS + 7) / 8 * 8 * tiles);
 }
 
 // Element r of the result in lane (row = lane mod 16, kq = lane / 16) is the
@@ -30,12 +29,12 @@ inline unsigned heat_blocks(int64_t C, int tiles) {
 //
 // Lane (row, kq) loads wavelengths k0 + 8 kq .. + 7 of cell row `row` (two
 // 16-byte loads where ALIGNED: J and its rows on 16 bytes) and its eight
-// values of the weight fragment, HEAT_U k-steps ahead of their MFMAs: with a
+// values of the weight fragment, U k-steps ahead of their MFMAs: with a
 // wave or less per SIMD nothing else hides the loads.  The products and their
 // order are those of fused_absorb, so H' is the same bit for bit.  Rows past
 // the last cell read cell C - 1 again; an MFMA's output row depends on its own
 // input row only, and those rows are not used.
-template <bool BF, bool ALIGNED>
+template <bool BF, bool ALIGNED, int U>
 __device__ __forceinline__ f32x4 heat_wave(const PlanView& v, int64_t c0, int64_t C, int tile,
                                            const float* __restrict__ J, int64_t ldj) {
     const int lane = threadIdx.x & 63;
@@ -94,26 +93,26 @@ __device__ __forceinline__ f32x4 heat_wave(const PlanView& v, int64_t c0, int64_
                 acc = __builtin_amdgcn_mfma_f32_16x16x4f32(st.x[e], b[e], acc, 0, 0, 0);
         }
     };
-    Step cur[HEAT_U], nxt[HEAT_U];
-    const int groups = nfull / HEAT_U;
+    Step cur[U], nxt[U];
+    const int groups = nfull / U;
     if (groups > 0) {
 #pragma unroll
-        for (int u = 0; u < HEAT_U; ++u) load_full(u, cur[u]);
+        for (int u = 0; u < U; ++u) load_full(u, cur[u]);
     }
     for (int g = 0; g < groups; ++g) {
         // past the last group, that group again (in bounds, not used)
-        const int s = (g + 1 < groups ? g + 1 : g) * HEAT_U;
+        const int s = (g + 1 < groups ? g + 1 : g) * U;
 #pragma unroll
-        for (int u = 0; u < HEAT_U; ++u) load_full(s + u, nxt[u]);
+        for (int u = 0; u < U; ++u) load_full(s + u, nxt[u]);
 #pragma unroll
-        for (int u = 0; u < HEAT_U; ++u) multiply(cur[u]);
+        for (int u = 0; u < U; ++u) multiply(cur[u]);
 #pragma unroll
-        for (int u = 0; u < HEAT_U; ++u) cur[u] = nxt[u];
+        for (int u = 0; u < U; ++u) cur[u] = nxt[u];
     }
-    // what is left: up to HEAT_U - 1 full steps and a ragged one (J zero past NL)
-    const int left = groups * HEAT_U;
+    // what is left: up to U - 1 full steps and a ragged one (J zero past NL)
+    const int left = groups * U;
 #pragma unroll
-    for (int u = 0; u < HEAT_U; ++u) {
+    for (int u = 0; u < U; ++u) {
         if (left + u < nfull) {
             load_full(left + u, cur[u]);
         } else if (left + u < nsteps) {
@@ -124,7 +123,7 @@ __device__ __forceinline__ f32x4 heat_wave(const PlanView& v, int64_t c0, int64_
         }
     }
 #pragma unroll
-    for (int u = 0; u < HEAT_U; ++u)
+    for (int u = 0; u < U; ++u)
         if (left + u < nsteps) multiply(cur[u]);
     return acc;
 }

@@ -112,3 +112,46 @@ def test_two_kernel_form_of_small_fused_calls(n_cells, n_lambda, n_species, n_si
             out.append((T.nan_to_num(-3.0), L.nan_to_num(-3.0), cnt))
         for a, b in zip(*out):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("n_cells,n_lambda,n_species,n_sizes", [
+    (1, 8, 1, 1),            # one pair
+    (17, 33, 1, 5),          # four lanes per cell, a ragged cell block and grain group
+    (64, 127, 3, 17),
+    (130, 1000, 1, 33),
+    (1220, 64, 1, 80),       # 1600 (64 cells, grain) waves: one lane per cell
+    (2050, 65, 1, 53),       # ragged in cells, wavelengths and grains
+    (70, 10, 2, 30),         # more grains than wavelengths
+])
+def test_plain_solve_forms(n_cells, n_lambda, n_species, n_sizes):
+    """The FP32 Newton, cold and warm-started, with an extra heating and in the
+    fused call, against the oracle.  Bound on T: rounding of ln P and ln H (up
+    to 80: 4.8e-6 each) and of the FP32 sum (terms to 5e-7), over a slope of at
+    least 4, plus the heating's FP32 sum: 5e-6 covers them (the grids below 64
+    wavelengths put Newton outside its table too)."""
+    plan, J, m = _inputs(n_cells, n_lambda, n_species, n_sizes, "plain", 21, 1)
+    g = synth.make_grid(n_lambda, n_species, n_sizes)
+    if n_cells > 20:
+        J[5] = 0.0
+        J[6] *= 1e-9    # colder than the start table
+        J[7] *= 1e9     # hotter
+    Q = torch.zeros((n_cells, g.n_grains), device="cuda")
+    Q[::3] = 1e-21
+    rows = np.unique(np.r_[np.arange(min(n_cells, 60)), n_cells - 1])
+    for q in (None, Q):
+        H, T, L = plan.run(J, m, Q=q)
+        ref = oracle.temperature(H[rows].cpu().numpy().astype(np.float64)
+                                 + (0 if q is None else q[rows].cpu().numpy()),
+                                 g.lam, g.dlam, g.c_abs, g.size)
+        ok = ref > 0
+        warm = torch.where(T > 0, T * 1.01, T)
+        outs = [T, plan.solve(H, T=warm.clone(), Q=q, warm_start=True)]
+        for t0 in (None, warm):
+            Tf, Lf = plan.fused(J, m, T=None if t0 is None else t0.clone(), Q=q,
+                                warm_start=t0 is not None)
+            outs.append(Tf)
+            assert torch.allclose(Lf[rows], L[rows], rtol=2e-3, atol=float(L.max()) * 1e-12)
+        for t in outs:
+            t = t[rows].cpu().numpy()
+            assert np.abs(t[ok] / ref[ok] - 1.0).max() <= 5e-6
+            assert (t[~ok] == 0).all()
