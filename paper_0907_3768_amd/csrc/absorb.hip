@@ -1,180 +1,22 @@
 // Heating, Eq. 6 (Section 4.2): H[c,s] = sum_l J[c,l] K[s,l], a dense
 // contraction over wavelength on the MFMA units.
 //
-//   DUST_PLAIN_FP32: a workgroup computes the heating of 16 cells for every
-//                    grain with the LDS-staged MFMA routine of the fused
-//                    kernel (fused_absorb) on v_mfma_f32_16x16x4_f32 (exact
-//                    FP32 products), then writes the 16 x S block of H with
-//                    coalesced stores, undoing the per-grain power of two.
+//   DUST_PLAIN_FP32: v_mfma_f32_16x16x4_f32 (exact FP32 products), one wave
+//                    per block of (16 cells, 16 grains) tiles straight from
+//                    device memory (heat_kernel).
 //   DUST_MIXED, DUST_TABLE_LINEAR:
 //                    v_mfma_f32_16x16x32_bf16 on hi+lo splits,
-//                    J_hi K_hi + J_hi K_lo + J_lo K_hi, FP32 accumulation:
-//                    a blocked product of 256 cells x up to 256 grains per
-//                    workgroup with J and the weight fragments staged in LDS
-//                    (absorb_dl_kernel: loaded straight into LDS, for J rows
-//                    aligned to 16 bytes; absorb_gemm_kernel: through
-//                    registers), or, on a device that cannot give one
-//                    workgroup its 144 KB of LDS, 64 cells per workgroup
-//                    with the fragments read from L2 (absorb_mb_kernel).
-#include "fused_body.h"
+//                    J_hi K_hi + J_hi K_lo + J_lo K_hi, FP32 accumulation.
+//                    Few cells, or J rows on odd floats: heat_kernel as above.
+//                    Many: a blocked product of 256 cells x up to 256 grains
+//                    per workgroup with J and the weight fragments staged in
+//                    LDS (absorb_dl_kernel: loaded straight into LDS, for J
+//                    rows aligned to 16 bytes; absorb_gemm_kernel: through
+//                    registers).
+#include "wave_heat.h"
 
 namespace dust {
 namespace {
-
-template <int MODE, int NTW>
-__global__ __launch_bounds__(256) void absorb_kernel(PlanView v, int64_t C,
-                                                     const float* __restrict__ J, int64_t ldj,
-                                                     float* __restrict__ H, int64_t ldh,
-                                                     bool scaled) {
-    extern __shared__ float lds[];  // sH [16][Sp], then the J staging buffers
-    float* sH = lds;
-    char* sStage = reinterpret_cast<char*>(lds + 16 * v.Sp);
-    const int64_t c0 = (int64_t)blockIdx.x * 16;
-    fused_absorb<MODE, NTW>(v, c0, C, J, ldj, sH, sStage);
-    __syncthreads();
-    for (int i = threadIdx.x; i < 16 * v.Sp; i += 256) {
-        const int cc = i / v.Sp, s = i - cc * v.Sp;
-        if (s < v.S && c0 + cc < C) H[(c0 + cc) * ldh + s] = scaled ? sH[i] : sH[i] * v.hinv[s];
-    }
-}
-
-// ---------------------------------------------------------------------------
-// bf16 hi+lo heating of 16 MB cells per workgroup of NW waves (MB 16-cell
-// MFMA row blocks): each wave loads the weight fragments of its grain tiles
-// (tiles wave, wave + NW, ...) once per k-step and applies them to all MB row
-// blocks, 1 / MB of the fragment traffic of one block per workgroup.  Eight
-// waves for more than four grain tiles: fewer tiles, and registers, per wave.  J goes through LDS in chunks of 16 MB
-// cells x 64 wavelengths as bf16 hi and lo planes (rows KC + 8 long, 4 banks
-// apart), double-buffered, one barrier per chunk; the accumulators go
-// straight to H.  Each product runs over every accumulator before the next
-// (consecutive MFMAs are independent), and the k-steps and the three products
-// of any one accumulator run in the order of the fused kernel's heating, so
-// H is the same bit for bit.
-// ---------------------------------------------------------------------------
-constexpr int A_KC = 64;
-constexpr int A_ROW = A_KC + 8;
-
-// Eight-wave workgroups with up to two grain tiles per wave ask for four
-// resident waves per SIMD (two workgroups per CU; a few spilled registers):
-// 8.9 ms against 13.1 ms at two waves on 4194304 cells x 1000 x 240.
-template <int NTW, int MB, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 8 && NTW <= 2 ? 4 : 1, 8))) void absorb_mb_kernel(PlanView v, int64_t C,
-                                                            const float* __restrict__ J,
-                                                            int64_t ldj, float* __restrict__ H,
-                                                            int64_t ldh) {
-    constexpr int CELLS = 16 * MB;
-    constexpr int NT = 64 * NW;              // threads
-    constexpr int NX = CELLS * A_KC / NT;    // J values per thread and chunk
-    constexpr int PASSES = NX / 4;           // loader rows per thread
-    constexpr int RSTEP = NT / 16;           // rows between a thread's loader rows
-    static_assert(NX % 4 == 0 && PASSES * RSTEP == CELLS, "loader covers the chunk");
-    __shared__ __bf16 sJ[2][2][CELLS][A_ROW];  // [buffer][hi, lo][cell][wavelength]
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int row = lane & 15, kq = lane >> 4;
-    const int tiles = v.Sp / 16;
-    const int nsteps = v.NLp / 32;
-    const int nchunks = (nsteps + 1) / 2;  // two k-steps per chunk
-    const int64_t c0 = (int64_t)blockIdx.x * CELLS;
-    // loader: thread t takes rows (t >> 4) + RSTEP p and column pairs 2 (t mod 16) + 32 i
-    const int lrow = tid >> 4, lcol = (tid & 15) * 2;
-    auto load_j = [&](int k0, float (&x)[NX]) {
-#pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
-            const int64_t c = c0 + lrow + RSTEP * p;
-            const bool ok = c < C;
-            const float* jl = J + (ok ? c : 0) * ldj;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int k = k0 + lcol + 32 * i;
-                x[4 * p + 2 * i] = (ok && k < v.NL) ? jl[k] : 0.0f;
-                x[4 * p + 2 * i + 1] = (ok && k + 1 < v.NL) ? jl[k + 1] : 0.0f;
-            }
-        }
-    };
-    auto store_j = [&](int buf, const float (&x)[NX]) {
-        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-#pragma unroll
-        for (int p = 0; p < PASSES; ++p) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const float x0 = x[4 * p + 2 * i], x1 = x[4 * p + 2 * i + 1];
-                const __bf16 h0 = (__bf16)x0, h1 = (__bf16)x1;
-                const bf16x2 hi = {h0, h1};
-                const bf16x2 lo = {(__bf16)(x0 - (float)h0), (__bf16)(x1 - (float)h1)};
-                *reinterpret_cast<bf16x2*>(&sJ[buf][0][lrow + RSTEP * p][lcol + 32 * i]) = hi;
-                *reinterpret_cast<bf16x2*>(&sJ[buf][1][lrow + RSTEP * p][lcol + 32 * i]) = lo;
-            }
-        }
-    };
-    for (int tg = 0; tg < tiles; tg += NW * NTW) {
-        f32x4 acc[NTW][MB];
-#pragma unroll
-        for (int t = 0; t < NTW; ++t)
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) acc[t][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        float x[NX];
-        load_j(0, x);
-        store_j(0, x);
-        __syncthreads();
-        for (int ch = 0; ch < nchunks; ++ch) {
-            const int buf = ch & 1;
-            if (ch + 1 < nchunks) load_j((ch + 1) * A_KC, x);  // next chunk in flight
-#pragma unroll 1
-            for (int ks = 0; ks < 2; ++ks) {
-                const int step = ch * 2 + ks;
-                if (step >= nsteps) break;  // uniform
-                bf16x8 khi[NTW], klo[NTW];
-#pragma unroll
-                for (int t = 0; t < NTW; ++t) {
-                    const int tile = tg + wave + NW * t;
-                    if (tile < tiles) {
-                        const int64_t o = (((int64_t)tile * nsteps + step) * 64 + lane) * 8;
-                        khi[t] = *reinterpret_cast<const bf16x8*>(v.khi + o);
-                        klo[t] = *reinterpret_cast<const bf16x8*>(v.klo + o);
-                    }
-                }
-                bf16x8 ahi[MB], alo[MB];
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb) {
-                    ahi[mb] = *reinterpret_cast<const bf16x8*>(&sJ[buf][0][16 * mb + row][ks * 32 + kq * 8]);
-                    alo[mb] = *reinterpret_cast<const bf16x8*>(&sJ[buf][1][16 * mb + row][ks * 32 + kq * 8]);
-                }
-#pragma unroll
-                for (int pr = 0; pr < 3; ++pr)
-#pragma unroll
-                    for (int t = 0; t < NTW; ++t) {
-                        if (tg + wave + NW * t < tiles) {
-#pragma unroll
-                            for (int mb = 0; mb < MB; ++mb)
-                                acc[t][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                    pr == 2 ? alo[mb] : ahi[mb], pr == 1 ? klo[t] : khi[t],
-                                    acc[t][mb], 0, 0, 0);
-                        }
-                    }
-            }
-            if (ch + 1 < nchunks) store_j(buf ^ 1, x);
-            __syncthreads();
-        }
-        // accumulator element r of lane (row, kq): cell 16 mb + 4 kq + r, grain 16 tile + row
-#pragma unroll
-        for (int t = 0; t < NTW; ++t) {
-            const int tile = tg + wave + NW * t;
-            const int s = tile * 16 + row;
-            if (tile < tiles && s < v.S) {
-                const float hinv = v.hinv[s];
-#pragma unroll
-                for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int64_t c = c0 + 16 * mb + 4 * kq + r;
-                        if (c < C) H[c * ldh + s] = acc[t][mb][r] * hinv;
-                    }
-            }
-        }
-    }
-}
 
 // ---------------------------------------------------------------------------
 // bf16 hi+lo heating as a blocked matrix product for the large shapes: a
@@ -193,7 +35,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW == 8
 // 16.  (Eight waves of 64 cells x 8 tiles, 12 MFMAs per fragment read but two
 // waves per SIMD, measured 12-18 % slower: the four waves per SIMD cover the
 // LDS and barrier latencies.)  A fragment read from L2 once per workgroup
-// serves 256 cells (64 in absorb_mb_kernel).  The next k-step's J
+// serves 256 cells.  The next k-step's J
 // values and fragments are loaded into registers during the MFMAs of the
 // current one and written to the other buffer after them; one barrier per
 // k-step; each tile's fragments are read from LDS one tile ahead of its
@@ -621,6 +463,86 @@ __global__ __launch_bounds__(64 * GW) __attribute__((amdgpu_waves_per_eu(GW / 4,
     }
 }
 
+// Heating by one wave per 16 MB cells x 16 NB grains (heat_block), straight
+// from device memory to H; scaled: H' instead of H.
+template <bool BF, bool ALIGNED, int MB, int NB, int U>
+__global__ __launch_bounds__(64) void heat_kernel(PlanView v, int64_t C,
+                                                  const float* __restrict__ J, int64_t ldj,
+                                                  float* __restrict__ H, int64_t ldh,
+                                                  bool scaled) {
+    const int tiles = (v.Sp / 16 + NB - 1) / NB;
+    const HeatTile ht = heat_tile<16 * MB>(blockIdx.x, tiles);
+    if (ht.c0 >= C) return;
+    f32x4 acc[MB][NB];
+    heat_block<BF, ALIGNED, MB, NB, U>(v, ht.c0, C, ht.tile * NB, J, ldj, acc);
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        const int s = 16 * (ht.tile * NB + n) + (lane & 15);
+        if (s >= v.S) continue;
+        const float hinv = scaled ? 1.0f : v.hinv[s];
+#pragma unroll
+        for (int m = 0; m < MB; ++m)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int64_t c = ht.c0 + 16 * m + 4 * (lane >> 4) + r;
+                if (c < C) H[c * ldh + s] = acc[m][n][r] * hinv;
+            }
+    }
+}
+
+template <bool BF, int MB, int NB, int U>
+hipError_t launch_heat(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
+                       int64_t ldh, bool scaled, hipStream_t st) {
+    const dim3 grid(heat_blocks<16 * MB>(C, (v.Sp / 16 + NB - 1) / NB));
+    if (rows_aligned16(J, ldj))
+        hipLaunchKernelGGL((heat_kernel<BF, true, MB, NB, U>), grid, dim3(64), 0, st, v, C, J, ldj,
+                           H, ldh, scaled);
+    else
+        hipLaunchKernelGGL((heat_kernel<BF, false, MB, NB, U>), grid, dim3(64), 0, st, v, C, J, ldj,
+                           H, ldh, scaled);
+    return hipGetLastError();
+}
+// Tiles per wave of the one-wave heating where waves are plenty: two cell
+// blocks, and the grain tiles that pad least; on a tie, bf16 takes the widest
+// (its operands bind: J is split per grain group), FP32 the narrowest (MFMAs
+// bind, and two k-steps in flight hide the loads better).
+template <bool BF>
+int heat_width(int tiles) {
+    if (tiles <= 2) return tiles;
+    const int bf[] = {5, 4, 3}, f32[] = {2, 4, 5, 3};
+    int best = 0, pad = 1 << 30;
+    for (int nb : bf)
+        if (BF && (tiles + nb - 1) / nb * nb < pad) pad = (tiles + nb - 1) / nb * nb, best = nb;
+    for (int nb : f32)
+        if (!BF && (tiles + nb - 1) / nb * nb < pad) pad = (tiles + nb - 1) / nb * nb, best = nb;
+    return best;
+}
+
+// The one-wave heating at the call's size.  Few tiles: one per wave, its loads
+// four k-steps ahead (32 cells x 968 x 81: FP32 19.7 us with 16 cells per
+// workgroup, now 9.5; bf16 33.8 with 256 cells, 8.1).  Some more: two k-steps
+// ahead and, in bf16, two grain tiles (4099 x 968 x 81: 25.9 -> 14.9 us; 38.9
+// -> 11.8, unaligned 90.8 -> 11.8).  Many: blocks of 2 x heat_width (FP32:
+// 32768 x 968 x 81 96 -> 63 us, 102 TFLOP/s with the padding, of 153; 262144 x
+// 250 x 80 176 -> 163).
+template <bool BF>
+hipError_t launch_heat_sized(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
+                             int64_t ldh, bool scaled, hipStream_t st) {
+    const int tiles = v.Sp / 16;
+    const int64_t waves = (C + 15) / 16 * tiles;
+    if (waves <= 1024) return launch_heat<BF, 1, 1, 4>(v, C, J, ldj, H, ldh, scaled, st);
+    if (BF && waves <= 4096) return launch_heat<BF, 1, 2, 2>(v, C, J, ldj, H, ldh, scaled, st);
+    if (!BF && waves <= 6144) return launch_heat<BF, 1, 1, 2>(v, C, J, ldj, H, ldh, scaled, st);
+    switch (heat_width<BF>(tiles)) {
+        case 1: return launch_heat<BF, 2, 1, 2>(v, C, J, ldj, H, ldh, scaled, st);
+        case 2: return launch_heat<BF, 2, 2, 2>(v, C, J, ldj, H, ldh, scaled, st);
+        case 3: return launch_heat<BF, 2, 3, 1>(v, C, J, ldj, H, ldh, scaled, st);
+        case 4: return launch_heat<BF, 2, 4, 1>(v, C, J, ldj, H, ldh, scaled, st);
+        default: return launch_heat<BF, 2, 5, 1>(v, C, J, ldj, H, ldh, scaled, st);
+    }
+}
+
 // LDS the current device gives one workgroup (asked once per device; 0 if
 // unknown).
 int lds_per_block() {
@@ -668,51 +590,27 @@ hipError_t launch_gemm(const PlanView& v, int64_t C, const float* J, int64_t ldj
 
 hipError_t launch_bf16(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
                        int64_t ldh, hipStream_t st) {
-    if (gemm_fits()) {  // blocked bf16 hi+lo heating
-        const int tiles = v.Sp / 16;
-        if (tiles <= 2) return launch_gemm<2>(v, C, J, ldj, H, ldh, st);
-        if (tiles <= 4) return launch_gemm<4>(v, C, J, ldj, H, ldh, st);
-        if (tiles <= 6) return launch_gemm<6>(v, C, J, ldj, H, ldh, st);
-        if (tiles <= 8) return launch_gemm<8>(v, C, J, ldj, H, ldh, st);
-        if (tiles <= 12) return launch_gemm<12>(v, C, J, ldj, H, ldh, st);
-        return launch_gemm<16>(v, C, J, ldj, H, ldh, st);  // passes of 16 tiles
-    }
-    // bf16 hi+lo heating, 64 cells per workgroup
-    constexpr int MB = 4;
-    const dim3 grid((unsigned)((C + 16 * MB - 1) / (16 * MB)));
     const int tiles = v.Sp / 16;
-    if (tiles <= 4)  // four waves, one grain tile each
-        hipLaunchKernelGGL((absorb_mb_kernel<1, MB, 4>), grid, dim3(256), 0, st, v, C, J, ldj,
-                           H, ldh);
-    else if (tiles <= 8)
-        hipLaunchKernelGGL((absorb_mb_kernel<1, MB, 8>), grid, dim3(512), 0, st, v, C, J, ldj,
-                           H, ldh);
-    else if (tiles <= 16)
-        hipLaunchKernelGGL((absorb_mb_kernel<2, MB, 8>), grid, dim3(512), 0, st, v, C, J, ldj,
-                           H, ldh);
-    else  // four tiles per wave and pass; more passes above 32 tiles
-        hipLaunchKernelGGL((absorb_mb_kernel<4, MB, 8>), grid, dim3(512), 0, st, v, C, J, ldj,
-                           H, ldh);
-    return hipGetLastError();
+    if (tiles <= 2) return launch_gemm<2>(v, C, J, ldj, H, ldh, st);
+    if (tiles <= 4) return launch_gemm<4>(v, C, J, ldj, H, ldh, st);
+    if (tiles <= 6) return launch_gemm<6>(v, C, J, ldj, H, ldh, st);
+    if (tiles <= 8) return launch_gemm<8>(v, C, J, ldj, H, ldh, st);
+    if (tiles <= 12) return launch_gemm<12>(v, C, J, ldj, H, ldh, st);
+    return launch_gemm<16>(v, C, J, ldj, H, ldh, st);  // passes of 16 tiles
 }
 
-template <int NTW>
-hipError_t launch_f32_ntw(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
-                          int64_t ldh, bool scaled, hipStream_t st) {
-    const dim3 grid((unsigned)((C + 15) / 16));
-    const size_t lds = sizeof(float) * 16 * v.Sp + STAGE_BYTES;
-    hipLaunchKernelGGL((absorb_kernel<DUST_PLAIN_FP32, NTW>), grid, dim3(256), lds, st, v, C, J,
-                       ldj, H, ldh, scaled);
-    return hipGetLastError();
-}
-
-hipError_t launch_f32(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
-                      int64_t ldh, bool scaled, hipStream_t st) {
-    const int ntw = (v.Sp / 16 + 3) / 4;  // grain tiles per wave in one pass (several above 4)
-    if (ntw <= 1) return launch_f32_ntw<1>(v, C, J, ldj, H, ldh, scaled, st);
-    if (ntw <= 2) return launch_f32_ntw<2>(v, C, J, ldj, H, ldh, scaled, st);
-    if (ntw <= 3) return launch_f32_ntw<3>(v, C, J, ldj, H, ldh, scaled, st);
-    return launch_f32_ntw<4>(v, C, J, ldj, H, ldh, scaled, st);
+// Whether the bf16 heating runs one wave per tile block instead of 256 cells
+// per workgroup: where the 256-cell blocks leave CUs without one (16384 x 500 x
+// 128, 64 blocks: 30.2 -> 21.5 us, 20000 x 600 x 240, 79: 53.5 -> 39; 32768 x
+// 968 x 81, 128: 41.8 against 45.6), and where J's rows start on odd floats,
+// which the staged kernel loads one by one, unless many grains make it worth
+// that (100003 x 301 x 45 67.6 -> 34.5 us, 1000000 x 251 x 80 607 -> 444, 262144
+// x 501 x 128 323 -> 297; 262144 x 1001 x 240 677 against 801), or on a device
+// that cannot give one workgroup the blocked kernel's 144 KB of LDS.
+bool wave_heating_pays(const PlanView& v, int64_t C, const float* J, int64_t ldj) {
+    const int64_t blocks = (C + 255) / 256;
+    const bool odd = ((uintptr_t)J & 7u) != 0 || (ldj & 1) != 0;
+    return !gemm_fits() || blocks < 112 || (odd && (v.Sp / 16 <= 8 || blocks < 256));
 }
 
 }  // namespace
@@ -720,14 +618,16 @@ hipError_t launch_f32(const PlanView& v, int64_t C, const float* J, int64_t ldj,
 hipError_t launch_absorb(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
                          int64_t ldh, hipStream_t st) {
     if (C == 0) return hipSuccess;
-    return table_mode(v.mode) ? launch_bf16(v, C, J, ldj, H, ldh, st)
-                              : launch_f32(v, C, J, ldj, H, ldh, false, st);
+    if (!table_mode(v.mode)) return launch_heat_sized<false>(v, C, J, ldj, H, ldh, false, st);
+    return wave_heating_pays(v, C, J, ldj)
+               ? launch_heat_sized<true>(v, C, J, ldj, H, ldh, false, st)
+               : launch_bf16(v, C, J, ldj, H, ldh, st);
 }
 
 hipError_t launch_absorb_scaled(const PlanView& v, int64_t C, const float* J, int64_t ldj,
                                 float* H, int64_t ldh, hipStream_t st) {
     if (C == 0) return hipSuccess;
-    return launch_f32(v, C, J, ldj, H, ldh, true, st);
+    return launch_heat_sized<false>(v, C, J, ldj, H, ldh, true, st);
 }
 
 }  // namespace dust

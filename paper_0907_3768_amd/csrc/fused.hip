@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void absorb_solve_kernel(PlanView v, int64_t C
 }
 
 // Absorb + solve for small calls: one wave per 16 cells x 16 grains, the
-// heating straight from device memory (heat_wave) and the lookups straight
+// heating straight from device memory (heat_block) and the lookups straight
 // from the accumulators, four pairs of one grain per lane; no LDS and no
 // barrier.  Pairs the table does not take are solved exactly by the wave, one
 // after the other.  The emission kernel follows.
@@ -58,7 +58,9 @@ __global__ __launch_bounds__(64) void heat_solve_kernel(PlanView v, int64_t C,
                                                         dust_counters* cnt) {
     const HeatTile ht = heat_tile<16>(blockIdx.x, v.Sp / 16);
     if (ht.c0 >= C) return;
-    const f32x4 acc = heat_wave<true, ALIGNED, 4>(v, ht.c0, C, ht.tile, J, ldj);
+    f32x4 hacc[1][1];
+    heat_block<true, ALIGNED, 1, 1, 4>(v, ht.c0, C, ht.tile, J, ldj, hacc);
+    const f32x4 acc = hacc[0][0];
     const int lane = threadIdx.x & 63;
     const int s_raw = 16 * ht.tile + (lane & 15);
     const int s = s_raw < v.S ? s_raw : v.S - 1;  // a lane past the last grain looks it up unused

@@ -155,3 +155,31 @@ def test_plain_solve_forms(n_cells, n_lambda, n_species, n_sizes):
             t = t[rows].cpu().numpy()
             assert np.abs(t[ok] / ref[ok] - 1.0).max() <= 5e-6
             assert (t[~ok] == 0).all()
+
+
+@pytest.mark.parametrize("mode", ["plain", "mixed"])
+@pytest.mark.parametrize("n_lambda,n_sizes,pad", [
+    (31, 9, 0),      # one grain tile, no full k-step
+    (32, 30, 1),     # two tiles, one k-step
+    (161, 48, 0),    # three
+    (130, 55, 2),    # four, rows on even floats
+    (65, 77, 3),     # five
+    (97, 113, 0),    # eight
+    (64, 150, 1),    # ten
+])
+def test_heating_forms_agree(n_lambda, n_sizes, pad, mode):
+    """H of the first rows of a large call equals that of the small calls, whose
+    waves take fewer tiles and whose J starts elsewhere (each alignment)."""
+    tiles = (n_sizes + 15) // 16
+    n = 16 * (6144 // tiles) + 530
+    plan, J, _ = _inputs(n, n_lambda, 1, n_sizes, mode, 5, pad)
+    H = plan.absorb(J)
+    g = synth.make_grid(n_lambda, 1, n_sizes)
+    ref = oracle.heating(J[:40].cpu().numpy().astype(np.float64), g.c_abs, g.dlam)
+    assert np.abs(H[:40].cpu().numpy() / ref - 1.0).max() <= 1e-4
+    for first, rows in ((0, 1), (1, 33), (2, 16 * (1024 // tiles)), (3, 16 * (1024 // tiles) + 1),
+                        (0, 16 * (4096 // tiles) + 1), (1, n - 500)):
+        out = torch.full((rows + 1, n_sizes + 2), -1.0, device="cuda")
+        plan.absorb(J[first:first + rows], out[:rows, :n_sizes])
+        assert torch.equal(out[:rows, :n_sizes], H[first:first + rows]), (first, rows)
+        assert bool((out[rows] == -1.0).all()) and bool((out[:, n_sizes:] == -1.0).all())
