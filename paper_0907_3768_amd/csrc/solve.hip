@@ -8,14 +8,13 @@
 // scalar cache.  Newton's first iterations run on the grain's table of ln P',
 // which leaves one evaluation of the full sum as a rule.  T goes back through
 // the same LDS slots; the iterations of the block are counted with one atomic.
-// Mixed: four (cell, grain) pairs per thread, 256 apart in row-major order
-// (coalesced H and T), each an O(1) lookup in the grain's inverse table
-// ln T(ln H) (a cubic Hermite in FP64 between FP64 nodes, or in FP32 with the
-// FP32 lookup), all four in flight together.
-// Table-linear: the same layout, a bracketed search in the grain's table of
-// powers at evenly spaced T and linear interpolation (Sections 2 and 5).
+// Mixed and table-linear: a workgroup takes 64 or 256 cells x 16 grains, a
+// wave one grain at a time with a cell per lane: an O(1) lookup in the grain's
+// inverse table ln T(ln H) (a cubic Hermite in FP64 between FP64 nodes, or in
+// FP32 with the FP32 lookup), or a bracketed search in its table of powers at
+// evenly spaced T and linear interpolation (Sections 2 and 5).
 // Every form adds the optional extra heating Q to H first.
-#include "device_common.h"
+#include "wave_heat.h"
 
 namespace dust {
 namespace {
@@ -82,98 +81,134 @@ __global__ __launch_bounds__(256) void solve_plain_kernel(PlanView v, int64_t C,
     }
 }
 
-// Table-linear: one thread per (cell, grain) in row-major order.
+// The table forms: a workgroup takes CELLS cells x 16 grains, its heating (plus
+// the extra term) staged in LDS, and each wave four of the grains in turn, a
+// cell per lane and CELLS / 64 lookups of one grain in flight.  A wave's
+// gathers then fall into one grain's table (4 KB of inverse nodes), which L1
+// keeps for the tile's cells, and the grain's constants are scalars; pairs in
+// row-major order gathered 128-byte lines from every grain's table for each
+// pair, and a 64-bit division per pair found its grain.
+// Pairs outside both tables are solved exactly by the wave, one after the
+// other.  Bound by the gathers and, at 64 cells, by the chain of dependent
+// loads: 1048576 x 500 x 128 900 -> 553 us (H and T at copy rate: 225), the
+// table-linear form 100003 x 301 x 45 87 -> 37 us.
+constexpr int TABLE_GRAINS = 16;
+
+template <int MODE, int CELLS>
 __global__ __launch_bounds__(256) void solve_table_kernel(PlanView v, int64_t C,
-                                                          const float* __restrict__ H,
-                                                          int64_t ldh, float* __restrict__ T,
-                                                          int64_t ldt, dust_counters* cnt) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= C * v.S) return;
-    const int64_t c = i / v.S;
-    const int s = (int)(i - c * v.S);
-    float h = H[c * ldh + s];
-    if (v.q) h += v.q[c * v.ldq + s];
-    T[c * ldt + s] = table_linear_T(v, s, h * v.hscale[s], cnt);
-}
-
-// Mixed: each thread takes MIXED_PER pairs 256 apart in row-major order
-// (coalesced H and T) and looks all of them up before it stores any, so that
-// their dependent loads (H, then the grain's inverse-table nodes) overlap: a
-// single lookup per thread leaves the kernel waiting on memory latency.  Pairs
-// outside both tables go to an LDS list and are then solved exactly by the
-// block's waves in turn (one pair per wave at a time, lanes over wavelength).
-constexpr int MIXED_PER = 4;
-constexpr int MIXED_BLOCK = 256 * MIXED_PER;  // pairs per workgroup
-
-template <int MODE>
-__device__ __forceinline__ int lookup_status(const PlanView& v, int s, float hs, float* T,
-                                             bool active, dust_counters* cnt) {
-    if constexpr (MODE == MODE_MIXED_POLISH) {
-        if (!active) return LOOKUP_OK;
-        return table_lookup_polish(v, s, hs, T, cnt) != 0 ? LOOKUP_PENDING : LOOKUP_OK;
-    } else if constexpr (MODE == MODE_MIXED_F32) {
-        return table_lookup_f32_nb(v, s, hs, T);
-    } else {
-        return table_lookup_f64_nb(v, s, hs, T);
-    }
-}
-
-template <int MODE>
-__global__ __launch_bounds__(256) void solve_mixed_kernel(PlanView v, int64_t C,
-                                                          const float* __restrict__ H,
-                                                          int64_t ldh, float* __restrict__ T,
-                                                          int64_t ldt, dust_counters* cnt) {
-    __shared__ int sCount;
-    __shared__ int sList[MIXED_BLOCK];
-    if (threadIdx.x == 0) sCount = 0;
-    __syncthreads();
-    const int64_t n = C * v.S;
-    const int64_t base = (int64_t)blockIdx.x * MIXED_BLOCK + threadIdx.x;
-    int64_t c[MIXED_PER];
-    int s[MIXED_PER];
-    float hs[MIXED_PER];
+                                                          const float* __restrict__ H, int64_t ldh,
+                                                          float* __restrict__ T, int64_t ldt,
+                                                          dust_counters* cnt) {
+    constexpr int ST = TABLE_GRAINS + 1;  // odd: a grain's column falls on distinct banks
+    constexpr int Q = CELLS / 64;
+    __shared__ float sX[CELLS * ST];      // heating in, T out
+    const HeatTile ht = heat_tile<CELLS>(blockIdx.x, v.Sp / 16);
+    if (ht.c0 >= C) return;
+    const int64_t c0 = ht.c0;
+    const int g0 = TABLE_GRAINS * ht.tile;
+    const int G = v.S - g0 < TABLE_GRAINS ? v.S - g0 : TABLE_GRAINS;
+    const int rows = C - c0 < CELLS ? (int)(C - c0) : CELLS;
+    {
+        const int sl = threadIdx.x % TABLE_GRAINS;
+        const float hscale = sl < G ? v.hscale[g0 + sl] : 1.0f;
 #pragma unroll
-    for (int k = 0; k < MIXED_PER; ++k) {
-        // past the end, read the last pair again (nothing is stored for it)
-        const int64_t i = (base + k * 256 < n) ? base + k * 256 : n - 1;
-        c[k] = i / v.S;
-        s[k] = (int)(i - c[k] * v.S);
-        float h = H[c[k] * ldh + s[k]];
-        if (v.q) h += v.q[c[k] * v.ldq + s[k]];
-        hs[k] = h * v.hscale[s[k]];
-    }
-    float t[MIXED_PER];
-    int st[MIXED_PER];
-#pragma unroll
-    for (int k = 0; k < MIXED_PER; ++k)
-        st[k] = lookup_status<MODE>(v, s[k], hs[k], &t[k], base + k * 256 < n, cnt);
-    int nonfinite = 0;
-#pragma unroll
-    for (int k = 0; k < MIXED_PER; ++k) {
-        if (base + k * 256 >= n) continue;
-        if (MODE != MODE_MIXED_POLISH && st[k] == LOOKUP_PENDING &&
-            cold_lookup(v, s[k], hs[k], &t[k], cnt))
-            st[k] = LOOKUP_OK;
-        if (st[k] == LOOKUP_PENDING) {
-            sList[atomicAdd(&sCount, 1)] = threadIdx.x + k * 256;
-        } else {
-            nonfinite += st[k] == LOOKUP_NONFINITE;
-            T[c[k] * ldt + s[k]] = t[k];
+        for (int cc = threadIdx.x / TABLE_GRAINS; cc < CELLS; cc += 256 / TABLE_GRAINS) {
+            float h = 0.0f;  // (pairs past the tile's end: T = 0, not stored)
+            if (cc < rows && sl < G) {
+                h = H[(c0 + cc) * ldh + g0 + sl];
+                if (v.q) h += v.q[(c0 + cc) * v.ldq + g0 + sl];
+            }
+            sX[cc * ST + sl] = h * hscale;
         }
     }
-    if (cnt) wave_count_add(&cnt->n_nonfinite, nonfinite);
     __syncthreads();
-    const int np = sCount;
-    for (int e = threadIdx.x >> 6; e < np; e += blockDim.x >> 6) {
-        const int64_t ip = (int64_t)blockIdx.x * MIXED_BLOCK + sList[e];
-        const int64_t cp = ip / v.S;
-        const int sp = (int)(ip - cp * v.S);
-        float hf = H[cp * ldh + sp];
-        if (v.q) hf += v.q[cp * v.ldq + sp];
-        const double hp = (double)(hf * v.hscale[sp]);
-        const float tp = wave_solve_pending(v, sp, hp, cnt);
-        if ((threadIdx.x & 63) == 0) T[cp * ldt + sp] = tp;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int nonfinite = 0;
+    for (int sl = wave; sl < G; sl += 4) {
+        const int s = g0 + sl;  // wave-uniform
+        float h[Q], t[Q];
+        int st[Q];
+#pragma unroll
+        for (int k = 0; k < Q; ++k) h[k] = sX[(64 * k + lane) * ST + sl];
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+            if constexpr (MODE == DUST_MIXED) {
+                st[k] = table_lookup_f64_nb(v, s, h[k], &t[k]);
+            } else if constexpr (MODE == MODE_MIXED_F32) {
+                st[k] = table_lookup_f32_nb(v, s, h[k], &t[k]);
+            } else {
+                st[k] = LOOKUP_OK;
+                if (64 * k + lane < rows) {
+                    if constexpr (MODE == MODE_MIXED_POLISH) {
+                        if (table_lookup_polish(v, s, h[k], &t[k], cnt) != 0) st[k] = LOOKUP_PENDING;
+                    } else {
+                        t[k] = table_linear_T(v, s, h[k], cnt);
+                    }
+                }
+            }
+        }
+        if constexpr (mixed_mode(MODE)) {
+            bool pending = false;
+#pragma unroll
+            for (int k = 0; k < Q; ++k) {
+                if (64 * k + lane >= rows) st[k] = LOOKUP_OK;
+                if (MODE != MODE_MIXED_POLISH && st[k] == LOOKUP_PENDING &&
+                    cold_lookup(v, s, h[k], &t[k], cnt))
+                    st[k] = LOOKUP_OK;
+                nonfinite += st[k] == LOOKUP_NONFINITE;
+                pending = pending || st[k] == LOOKUP_PENDING;
+            }
+            if (__ballot(pending) != 0) {
+#pragma unroll
+                for (int k = 0; k < Q; ++k) {
+                    uint64_t mask = __ballot(st[k] == LOOKUP_PENDING);
+                    while (mask) {
+                        const int src = __builtin_ctzll(mask);
+                        mask &= mask - 1;
+                        const float hp = __int_as_float(
+                            __builtin_amdgcn_readlane(__float_as_int(h[k]), src));
+                        const float tp = wave_solve_pending(v, s, (double)hp, cnt);
+                        if (lane == src) t[k] = tp;
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < Q; ++k) sX[(64 * k + lane) * ST + sl] = t[k];
     }
+    if (mixed_mode(MODE) && cnt) wave_count_add(&cnt->n_nonfinite, nonfinite);
+    __syncthreads();
+    const int sl = threadIdx.x % TABLE_GRAINS;
+#pragma unroll
+    for (int cc = threadIdx.x / TABLE_GRAINS; cc < CELLS; cc += 256 / TABLE_GRAINS)
+        if (cc < rows && sl < G) T[(c0 + cc) * ldt + g0 + sl] = sX[cc * ST + sl];
+}
+
+template <int MODE, int CELLS>
+hipError_t launch_table(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
+                        int64_t ldt, dust_counters* cnt, hipStream_t st) {
+    hipLaunchKernelGGL((solve_table_kernel<MODE, CELLS>), dim3(heat_blocks<CELLS>(C, v.Sp / 16)),
+                       dim3(256), 0, st, v, C, H, ldh, T, ldt, cnt);
+    return hipGetLastError();
+}
+
+// The branch-free lookups take 256 cells per workgroup, four of a grain in
+// flight, once that leaves four workgroups per CU (100003 x 301 x 45: 21 us
+// either way; 262144 x 250 x 80 71 us against 86 with 64 cells, 32768 x 250 x
+// 80 13.1 with 64 cells, 15.4 with 256).  The polish and the table-linear
+// search branch per pair, so more cells only lengthen a wave's chain (262144
+// x 250 x 80 with 64 cells 136 and 154 us, with 256 140 and 160; 16384 cells
+// 12 and 14, 24 and 25).
+constexpr int64_t TABLE_BLOCKS = 1024;
+
+template <int MODE>
+hipError_t launch_table_mode(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
+                             int64_t ldt, dust_counters* cnt, hipStream_t st) {
+    if ((MODE == DUST_MIXED || MODE == MODE_MIXED_F32) &&
+        (C + 255) / 256 * (v.Sp / 16) >= TABLE_BLOCKS)
+        return launch_table<MODE, 256>(v, C, H, ldh, T, ldt, cnt, st);
+    return launch_table<MODE, 64>(v, C, H, ldh, T, ldt, cnt, st);
 }
 
 }  // namespace
@@ -181,26 +216,14 @@ __global__ __launch_bounds__(256) void solve_mixed_kernel(PlanView v, int64_t C,
 hipError_t launch_solve(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
                         int64_t ldt, dust_counters* cnt, hipStream_t st) {
     if (C == 0) return hipSuccess;
-    if (v.mode == DUST_MIXED) {
-        const int64_t n = C * v.S;
-        const unsigned blocks = (unsigned)((n + MIXED_BLOCK - 1) / MIXED_BLOCK);
-        if (v.f32_lookup)
-            hipLaunchKernelGGL(solve_mixed_kernel<MODE_MIXED_F32>,
-                               dim3(blocks), dim3(256), 0, st, v, C, H, ldh, T, ldt, cnt);
-        else if (v.polish)
-            hipLaunchKernelGGL(solve_mixed_kernel<MODE_MIXED_POLISH>, dim3(blocks), dim3(256), 0,
-                               st, v, C, H, ldh, T, ldt, cnt);
-        else
-            hipLaunchKernelGGL(solve_mixed_kernel<DUST_MIXED>, dim3(blocks), dim3(256), 0, st, v,
-                               C, H, ldh, T, ldt, cnt);
-    } else if (v.mode == DUST_TABLE_LINEAR) {
-        const int64_t n = C * v.S;
-        hipLaunchKernelGGL(solve_table_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                           st, v, C, H, ldh, T, ldt, cnt);
-    } else {
-        return launch_solve_plain(v, C, H, ldh, T, ldt, false, cnt, st);
+    if (!table_mode(v.mode)) return launch_solve_plain(v, C, H, ldh, T, ldt, false, cnt, st);
+    switch (kernel_mode(v)) {
+        case DUST_MIXED: return launch_table_mode<DUST_MIXED>(v, C, H, ldh, T, ldt, cnt, st);
+        case MODE_MIXED_F32: return launch_table_mode<MODE_MIXED_F32>(v, C, H, ldh, T, ldt, cnt, st);
+        case MODE_MIXED_POLISH:
+            return launch_table_mode<MODE_MIXED_POLISH>(v, C, H, ldh, T, ldt, cnt, st);
+        default: return launch_table_mode<DUST_TABLE_LINEAR>(v, C, H, ldh, T, ldt, cnt, st);
     }
-    return hipGetLastError();
 }
 
 // Four lanes per cell where the (64 cells, grain) waves leave SIMDs idle: 32 x

@@ -183,3 +183,30 @@ def test_heating_forms_agree(n_lambda, n_sizes, pad, mode):
         plan.absorb(J[first:first + rows], out[:rows, :n_sizes])
         assert torch.equal(out[:rows, :n_sizes], H[first:first + rows]), (first, rows)
         assert bool((out[rows] == -1.0).all()) and bool((out[:, n_sizes:] == -1.0).all())
+
+
+@pytest.mark.parametrize("mode,lookup", [("mixed", "default"), ("mixed", "f32"),
+                                         ("mixed", "polish"), ("table", "default")])
+def test_table_solve_forms_agree(mode, lookup):
+    """T of the first rows of a large call (256 cells per workgroup) equals that
+    of small ones, on cells of every kind and with an extra heating, and only
+    the grains' columns are written."""
+    n, S = 16 * 1024 * 16 // 3 + 77, 45  # 1026 blocks of (256 cells, 16 grains)
+    plan, J, _ = _inputs(n, 40, 1, S, mode, 9, f32_lookup=lookup == "f32",
+                         newton_polish=lookup == "polish")
+    H = plan.absorb(J)
+    for c, h in ((3, 0.0), (4, float("nan")), (7, -1e-20), (9, 1e-37), (70, 1e3), (71, 3e-30),
+                 (200, float("inf"))):
+        H[c] = h
+    Q = torch.zeros((n, S + 3), device="cuda")
+    Q[::5] = 1e-20
+    for q in (None, Q):
+        big, small = dust.new_counters(), dust.new_counters()
+        T = plan.solve(H, Q=q, counters=big)
+        out = torch.full((n + 1, S + 2), -7.0, device="cuda")
+        for c in range(0, n, 40000):
+            e = min(n, c + 40000)
+            plan.solve(H[c:e], out[c:e, :S], counters=small, Q=None if q is None else q[c:e])
+        assert torch.equal(out[:n, :S].nan_to_num(-3.0), T.nan_to_num(-3.0))
+        assert bool((out[n] == -7.0).all()) and bool((out[:, S:] == -7.0).all())
+        assert torch.equal(big, small) and int(big[0]) == 3 * S
