@@ -50,7 +50,7 @@ struct View {
     const double* E;      // [S][M] level enthalpies
     const double* rcool;  // [S][M] (E_j - E_{j-1}) / P(T_j): 1 / the cooling rate, 0 at j = 0
     const double* invd;   // [S][M] 1 / (E_j - E_{j-1}), 0 at j = 0
-    const int* cnt;       // [S][M][M] cnt[s][i][k] = #{l : eps_l >= E_k - E_i} (NL for k <= i)
+    const uint16_t* cnt;  // [S][M][M] cnt[s][i][k] = #{l : eps_l >= E_k - E_i} (NL for k <= i)
     const float* etab;    // [Kp][NLp] w_s C[s,l] B(lam_l, T_sj) 2^-ge, zero padded
     float escale;         // 2^ge
 };
@@ -68,7 +68,7 @@ struct Prep {
     View v;
     const double *lam, *dlam, *cabs, *w, *T;
     double *eps, *kr, *rcool, *invd;
-    int* cnt;
+    uint16_t* cnt;
     float* etab;
     int ge;
 };
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256) void prep_count_kernel(Prep p) {
         }
         n = lo;
     }
-    p.cnt[t] = n;
+    p.cnt[t] = (uint16_t)n;  // at most NL <= 4095
 }
 
 // Emission table: one thread per (wavelength, (grain, level)).
@@ -223,7 +223,7 @@ __global__ __launch_bounds__(64) void solve_kernel(View v, int64_t C, const floa
     // 2. levels in order; lane holds upper levels j = lane + 64 q
     const double* Es = v.E + (int64_t)s * M;
     const double* rcool = v.rcool + (int64_t)s * M;
-    const int* cn = v.cnt + (int64_t)s * M * M;
+    const uint16_t* cn = v.cnt + (int64_t)s * M * M;
     double acc[Q], X[Q], Ejm1[Q], dinv[Q];
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(64) void solve_kernel(View v, int64_t C, const floa
             if ((i >> 6) == q && lane == (i & 63)) X[q] = xi;
         if (i == M - 1) break;
         const double Ei = Es[i];
-        const int* row = cn + (int64_t)i * M;
+        const uint16_t* row = cn + (int64_t)i * M;
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             if (64 * q + 63 <= i) continue;  // uniform: every level of this chunk is at or below i
@@ -288,179 +288,379 @@ __global__ __launch_bounds__(64) void solve_kernel(View v, int64_t C, const floa
 
 // ---------------------------------------------------------------------------
 // The same distribution for grains of at most 64 levels (one level per lane),
-// several cells of one grain per workgroup (a wave per cell).  The grain's
-// tables go through LDS once per workgroup: the photon counts as byte offsets
-// into a wave's prefix sums ([M][M] ints) and (E_i, 1 / cooling rate_i)
-// ([M] pairs).  Per level step a wave then issues only LDS reads and VALU
-// work: the lower level's value X_i = acc_i / cool_i is read from lane i of
-// the product acc * (1 / cool), its enthalpy is one broadcast LDS read, the
-// rescale test is a scalar branch on X_i's exponent word, and X is not kept
-// per level but read off the sums at the end (X_j = acc_j / cool_j, every
-// sum having taken the same rescales; X_0 = 2^(-500 rescales)).  The
-// arithmetic of every sum is the one of solve_kernel.
+// two cells of one grain per wave and up to eight waves per workgroup.  The
+// grain's photon counts go through LDS once per workgroup (16 bits each), its
+// enthalpies and cooling rates sit in the lanes.  Per level step a wave reads
+// one count and each cell's prefix sums from LDS; the lower level's value X_i =
+// acc_i / cool_i is read from lane i of the product acc * (1 / cool), the
+// rescale test is a scalar branch on the exponent words, and X is not kept per
+// level but read off the sums at the end (X_j = acc_j / cool_j, every sum
+// having taken the same rescales; X_0 = 2^(-500 rescales)).  The arithmetic of
+// every sum is the one of solve_kernel.
+//
+// The two cells share a step's count and difference of enthalpies; and since
+// from level 32 on only lanes 32 and up still collect, the second cell's upper
+// half moves into the first's lower lanes there and one step serves both (a
+// third fewer instructions than one cell per wave).  LDS holds 32 cells per
+// CU, so few waves are there to hide the reads: the sums of step i + 3 and the
+// count of step i + 5 are read at step i.  65536 cells x 16 grains x 64 levels
+// x 250 wavelengths: 2.68 ms with one cell per wave, 2.29 now; 20000 x 16 x 64 x 500 1.55 -> 1.17.
 // ---------------------------------------------------------------------------
 constexpr int STAGED_MAX_LEVELS = 64;
 constexpr int STAGED_MAX_WAVES = 8;
+constexpr int STAGED_MAX_LDS = 160 * 1024;  // a CU's
+constexpr int64_t STAGED_BLOCKS = 2048;     // workgroups at most (a few rounds of the chip)
 
-// LDS of the grain's tables: the offsets [M + 1][M] (a zero row after the
-// last, read by the steps past the end), then (E, 1 / cooling rate) [M].
-__host__ __device__ inline int staged_offsets_bytes(int M) {
-    return (4 * (M + 1) * M + 15) / 16 * 16;
-}
+// LDS of the grain's photon counts: [M + STAGED_PAD][M], zero rows after the
+// last (read by the steps past the end).
+constexpr int STAGED_PAD = 9;
 __host__ __device__ inline int staged_table_bytes(int M) {
-    return staged_offsets_bytes(M) + 16 * M;
+    return (2 * (M + STAGED_PAD) * M + 15) / 16 * 16;
+}
+__host__ __device__ inline int staged_wave_bytes(int NL) {
+    return 2 * (NL + 1) * (int)sizeof(double2);  // two cells' prefix sums
 }
 
+// x moved by a DPP control; lanes without a source (or in rows outside
+// ROWS) get 0.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_f64(double x) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, ROWS == 0xf);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, ROWS == 0xf);
+    return __hiloint2double(hi, lo);
+}
+// lane l gets lane l - 1's x (lane 0: 0)
+__device__ __forceinline__ double from_lane_below(double x) { return dpp_f64<0x138, 0xf>(x); }
+// Inclusive prefix sum over the wave's lanes (rows of 16, then across rows).
+__device__ __forceinline__ double wave_scan_f64(double x) {
+    x += dpp_f64<0x111, 0xf>(x);  // row_shr:1
+    x += dpp_f64<0x112, 0xf>(x);  // row_shr:2
+    x += dpp_f64<0x114, 0xf>(x);  // row_shr:4
+    x += dpp_f64<0x118, 0xf>(x);  // row_shr:8
+    x += dpp_f64<0x142, 0xa>(x);  // row_bcast:15 into rows 1 and 3
+    x += dpp_f64<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+    return x;
+}
+// {lanes 0-31 of a, lanes 0-31 of b} and {lanes 32-63 of a, lanes 32-63 of b}.
+__device__ __forceinline__ double lower_halves(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]);
+}
+__device__ __forceinline__ double upper_halves(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[1], lo[1]);
+}
+
+// A lane's share of the photon rates: the wavelengths [lane G, (lane + 1) G).
+// GR: G, with the grain's weights and energies kept in registers over the
+// workgroup's cells and the cells' intensities loaded a group ahead; 0: any
+// number of wavelengths, everything loaded where it is used.
+template <int GR>
+struct StagedRates {
+    static constexpr int N = GR ? GR : 1;
+    const View& v;
+    const double* kr;
+    int G, lb;
+    bool wide;  // J rows on 16 bytes
+    double k[N], e[N];
+    float xa[N], xb[N];
+
+    __device__ StagedRates(const View& view, int s, bool aligned) : v(view) {
+        kr = v.kr + (int64_t)s * v.NL;
+        G = GR ? GR : (v.NL + 63) >> 6;
+        lb = (threadIdx.x & 63) * G;
+        wide = aligned;
+        if constexpr (GR > 0) {
+#pragma unroll
+            for (int q = 0; q < GR; ++q) {
+                const bool in = lb + q < v.NL;
+                k[q] = in ? kr[lb + q] : 0.0;
+                e[q] = in ? v.eps[lb + q] : 0.0;
+            }
+        }
+    }
+    __device__ void load_row(const float* __restrict__ j, float (&x)[N]) {
+        if constexpr (GR > 0) {
+            if (wide && lb + GR <= v.NL) {
+#pragma unroll
+                for (int q = 0; q < GR; q += 4) {
+                    const float4 f = *reinterpret_cast<const float4*>(j + lb + q);
+                    x[q] = f.x; x[q + 1] = f.y; x[q + 2] = f.z; x[q + 3] = f.w;
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < GR; ++q) x[q] = lb + q < v.NL ? j[lb + q] : 0.0f;
+            }
+        }
+    }
+    __device__ void load(const float* __restrict__ ja, const float* __restrict__ jb) {
+        load_row(ja, xa);
+        load_row(jb, xb);
+    }
+    // The prefix sums of both cells, shortest wavelength first: one wave scan of
+    // the lanes' totals gives each lane its start, then the lane runs through
+    // its wavelengths again writing the sums.
+    __device__ void sums(const float* __restrict__ ja, const float* __restrict__ jb, double2* sa,
+                         double2* sb, bool* bad_a, bool* bad_b) {
+        bool ba = false, bb = false;
+        auto rates = [&](int q, double& ra, double& ea, double& rb, double& eb) {
+            const float fa = GR ? xa[q] : ja[lb + q], fb = GR ? xb[q] : jb[lb + q];
+            const double kq = GR ? k[q] : kr[lb + q], eq = GR ? e[q] : v.eps[lb + q];
+            ba = ba || !(fa >= 0.0f) || __builtin_isinf(fa);
+            bb = bb || !(fb >= 0.0f) || __builtin_isinf(fb);
+            ra = (double)fa * kq;
+            ea = ra * eq;
+            rb = (double)fb * kq;
+            eb = rb * eq;
+        };
+        double a0 = 0.0, a1 = 0.0, b0 = 0.0, b1 = 0.0;
+        auto pass = [&](bool write) {
+            auto one = [&](int q) {
+                double ra, ea, rb, eb;
+                rates(q, ra, ea, rb, eb);
+                a0 += ra;
+                a1 += ea;
+                b0 += rb;
+                b1 += eb;
+                if (write) {
+                    sa[lb + q + 1] = make_double2(a0, a1);
+                    sb[lb + q + 1] = make_double2(b0, b1);
+                }
+            };
+            if constexpr (GR > 0) {
+#pragma unroll
+                for (int q = 0; q < GR; ++q)
+                    if (!write || lb + q < v.NL) one(q);  // (past NL the rates are zero)
+            } else {
+                for (int q = 0; q < G && lb + q < v.NL; ++q) one(q);
+            }
+        };
+        pass(false);
+        a0 = from_lane_below(wave_scan_f64(a0));
+        a1 = from_lane_below(wave_scan_f64(a1));
+        b0 = from_lane_below(wave_scan_f64(b0));
+        b1 = from_lane_below(wave_scan_f64(b1));
+        if (lb == 0) sa[0] = sb[0] = make_double2(0.0, 0.0);
+        pass(true);
+        *bad_a = __ballot(ba) != 0;
+        *bad_b = __ballot(bb) != 0;
+    }
+};
+
+// LDS written by some lanes of a wave and read by others of it: the wave's LDS
+// operations complete in order, so only the compiler has to keep theirs.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Workgroup b takes grain b mod S and of its cell groups (two cells per wave)
+// number b / S and every n_blocks-th after it.
+template <int GR>
 __global__ __launch_bounds__(64 * STAGED_MAX_WAVES) void solve_staged_kernel(
-    View v, int64_t C, const float* __restrict__ J, int64_t ldj, float* __restrict__ P,
-    int64_t ldp, dust_counters* cnt) {
+    View v, int64_t C, const float* __restrict__ J, int64_t ldj, bool aligned,
+    float* __restrict__ P, int64_t ldp, int n_blocks, dust_counters* cnt) {
     extern __shared__ __align__(16) char smem[];
     const int NL = v.NL, M = v.M, S = v.S;
     const int W = (int)(blockDim.x >> 6);
-    int* sOff = reinterpret_cast<int*>(smem);  // [M + 1][M] 16 * count
-    double2* sLev = reinterpret_cast<double2*>(smem + staged_offsets_bytes(M));  // [M]
+    uint16_t* sCnt = reinterpret_cast<uint16_t*>(smem);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
-    char* sFb = smem + staged_table_bytes(M) + (size_t)wave * (NL + 1) * sizeof(double2);
-    double2* sF = reinterpret_cast<double2*>(sFb);
+    char* sA = smem + staged_table_bytes(M) + (size_t)wave * staged_wave_bytes(NL);
+    char* sB = sA + (NL + 1) * sizeof(double2);
     const int s = (int)(blockIdx.x % (unsigned)S);
-    const int64_t c_raw = (int64_t)(blockIdx.x / (unsigned)S) * W + wave;
-    const bool live = c_raw < C;
-    const int64_t c = live ? c_raw : C - 1;  // a wave past the end repeats the last cell, unwritten
-    // 0. the grain's tables
+    // 0. the grain's counts
     {
-        const int* cn = v.cnt + (int64_t)s * M * M;
-        for (int e = threadIdx.x; e < M * M; e += blockDim.x) sOff[e] = cn[e] * (int)sizeof(double2);
-        for (int e = threadIdx.x; e < M; e += blockDim.x) sOff[M * M + e] = 0;
-        for (int e = threadIdx.x; e < M; e += blockDim.x)
-            sLev[e] = make_double2(v.E[(int64_t)s * M + e], v.rcool[(int64_t)s * M + e]);
-    }
-    // 1. photon rates and their prefix sums, shortest wavelength first: lane
-    //    l takes the wavelengths [l G, (l + 1) G), G = ceil(NL / 64); one
-    //    wave scan of the lanes' totals gives each lane its start, then the
-    //    lane runs through its wavelengths again writing the sums.
-    const float* jr = J + c * ldj;
-    const double* kr = v.kr + (int64_t)s * NL;
-    const int G = (NL + 63) >> 6;
-    const int lb = lane * G;
-    bool bad = false;
-    double t0 = 0.0, t1 = 0.0;
-    for (int q = 0; q < G; ++q) {
-        const int l = lb + q;
-        if (l < NL) {
-            const float jv = jr[l];
-            if (!(jv >= 0.0f) || __builtin_isinf(jv)) bad = true;
-            const double r = (double)jv * kr[l];
-            t0 += r;
-            t1 += r * v.eps[l];
+        const uint16_t* cn = v.cnt + (int64_t)s * M * M;
+        if ((M & 3) == 0) {  // 16-byte rows of the plan's table
+            for (int e = threadIdx.x; e < M * M / 8; e += blockDim.x)
+                reinterpret_cast<uint4*>(sCnt)[e] = reinterpret_cast<const uint4*>(cn)[e];
+        } else {
+            for (int e = threadIdx.x; e < M * M; e += blockDim.x) sCnt[e] = cn[e];
         }
+        for (int e = threadIdx.x; e < STAGED_PAD * M; e += blockDim.x) sCnt[M * M + e] = 0;
     }
-    // exclusive scan of the totals: the lane below's total, then an inclusive scan
-    double e0 = __shfl_up(t0, 1, 64), e1 = __shfl_up(t1, 1, 64);
-    if (lane == 0) e0 = e1 = 0.0;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const double a = __shfl_up(e0, d, 64), b = __shfl_up(e1, d, 64);
-        if (lane >= d) {
-            e0 += a;
-            e1 += b;
-        }
-    }
-    if (lane == 0) sF[0] = make_double2(0.0, 0.0);
-    for (int q = 0; q < G; ++q) {
-        const int l = lb + q;
-        if (l < NL) {
-            const double r = (double)jr[l] * kr[l];
-            e0 += r;
-            e1 += r * v.eps[l];
-            sF[l + 1] = make_double2(e0, e1);
-        }
-    }
-    const bool any_bad = __ballot(bad) != 0;
+    const int64_t step_cells = 2 * (int64_t)W * n_blocks;
+    int64_t ca = ((int64_t)(blockIdx.x / (unsigned)S) * W + wave) * 2;
+    // a cell past the end repeats the last one, unwritten
+    auto row = [&](int64_t c) { return J + (c < C ? c : C - 1) * ldj; };
+    StagedRates<GR> rates(v, s, aligned);
+    rates.load(row(ca), row(ca + 1));
     __syncthreads();
+    const int j = lane;
+    const bool jok = j < M;
+    const double Ej = jok ? v.E[(int64_t)s * M + j] : 0.0;
+    const double rc = jok ? v.rcool[(int64_t)s * M + j] : 0.0;  // 0 at j = 0
+    const double dinv = jok ? v.invd[(int64_t)s * M + j] : 0.0;
+    const double Ejm1 = from_lane_below(Ej);
+    for (; ca < C; ca += step_cells) {
+    // 1. the cells' prefix sums
+    bool bad_a, bad_b;
+    wave_lds_fence();
+    rates.sums(row(ca), row(ca + 1), reinterpret_cast<double2*>(sA),
+               reinterpret_cast<double2*>(sB), &bad_a, &bad_b);
+    rates.load(row(ca + step_cells), row(ca + step_cells + 1));  // the next group's, in flight
+    wave_lds_fence();
     // 2. levels in order; lane j holds level j.  The LDS reads are issued
     //    ahead of their use, so the chain from one level to the next is only
-    //    acc -> X_i -> acc: at step i the offsets of step i + 2 and the prefix
-    //    sums of step i + 1 are read, and B[j][i] is formed from the sums read
-    //    at step i - 1.  Lanes with j <= i read valid addresses and drop the
-    //    values.
-    const int j = lane;
-    const bool jok = j >= 1 && j < M;
-    const double Ejm1 = jok ? sLev[j - 1].x : 0.0;
-    const double Ej = j < M ? sLev[j].x : 0.0;
-    const double dinv = jok ? v.invd[(int64_t)s * M + j] : 0.0;
-    const double rc = j < M ? sLev[j].y : 0.0;  // 0 at j = 0
-    // offset of step r <= M for this lane: the count of eps >= E_j - E_r
-    // (column j of row r; column M - 1 for lanes past the last level; row M
-    // is zeros).  The other bound of B[j][r], eps >= E_{j-1} - E_r, is the
-    // next lane down's: its sums come from that lane by a one-lane shift of
-    // the wave (DPP), one LDS gather per step instead of two.
-    const int* col = sOff + (j < M ? j : M - 1);
-    auto offset = [&](int r) { return col[r * M]; };
-    auto sums = [&](int o) { return *reinterpret_cast<const double2*>(sFb + o); };
-    auto from_lane_below = [](const double2& a) {
-        auto sh = [](double x) {  // lane l gets lane l - 1's x (lane 0: 0)
-            const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x138, 0xf, 0xf, false);
-            const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x138, 0xf, 0xf, false);
-            return __hiloint2double(hi, lo);
-        };
-        return make_double2(sh(a.x), sh(a.y));
+    //    X_i -> X_{i+1}: at step i the counts of step i + 5 and the prefix
+    //    sums of step i + 3 are read.  Lanes with j <= i read valid addresses
+    //    and drop the values; the steps run on to a multiple of four, where no
+    //    level is left to collect.  The count of step r for a lane is that of
+    //    eps >= E_j - E_r (column j of row r; column M - 1 for lanes past the
+    //    last level).  The other bound of B[j][r], eps >= E_{j-1} - E_r, is the
+    //    next lane down's: its sums come from that lane by a one-lane shift.
+    auto sums = [](const char* p, int n) {
+        return *reinterpret_cast<const double2*>(p + n * (int)sizeof(double2));
     };
-    int o2 = offset(0);
-    double2 f2 = sums(o2);  // step 0
-    o2 = offset(1);         // step 1
-    double acc = 0.0;
-    int rescales = 0;
-    double xi = 1.0;  // X_0
-    double Ei = sLev[0].x;
-    // one step: B[j][i] from the sums a2 read at the step before (and the
-    // lane below's), the sums of step i + 1 into b2, the offset of step
-    // i + 2 and E_{i+1}, then X_i (from readlane in both branches of the
-    // rescale, so it stays in scalar registers)
-    auto step = [&](int i, const double2& a2, double2& b2) {
-        const double2 a1 = from_lane_below(a2);
-        const double B = a2.x + ((a1.y - a2.y) - (Ejm1 - Ei) * (a1.x - a2.x)) * dinv;
-        // the offset first: LDS reads complete in order, and the next step
-        // needs it before the sums
-        const int n2 = offset(i + 2);
-        b2 = sums(o2);
-        o2 = n2;
-        Ei = sLev[i + 1 < M ? i + 1 : i].x;
-        if (i > 0) {
-            xi = readlane_f64(acc * rc, i);
-            if (__double2hiint(xi) > 0x5F2FFFFF) {  // X_i >= 2^500 (uniform): rescale, exactly
-                // (the empty asm keeps this a scalar branch: without it the
-                // compiler computes the rescale at every step and selects)
-                asm volatile("");
-                acc = ldexp(acc, -500);
-                ++rescales;
-                xi = readlane_f64(acc * rc, i);
+    // B[j][i] from the sums at the level's own count and the lane below's
+    auto rate = [](const double2& a2, double de, double di) {
+        const double b0 = from_lane_below(a2.x), b1 = from_lane_below(a2.y);
+        return a2.x + ((b1 - a2.y) - de * (b0 - a2.x)) * di;
+    };
+    constexpr int BIG = 0x5F2FFFFF;  // exponent word of 2^500, less one
+    double acc_a = 0.0, acc_b = 0.0;  // sum_i B[j][i] X_i
+    int resc_a = 0, resc_b = 0;
+    {
+        const int jl = jok ? j : -1;  // lanes past the last level collect nothing
+        const uint16_t* col = sCnt + (jok ? j : M - 1);
+        double xa = 1.0, xb = 1.0;    // X_0
+        double2 fa[4], fb[4];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int n = col[r * M];
+            fa[r] = sums(sA, n);
+            fb[r] = sums(sB, n);
+        }
+        int n0 = col[3 * M], n1 = col[4 * M];
+        // step i: B[j][i] of both cells, the reads ahead, then X_i
+        auto step = [&](int i, double2& ga, double2& gb, double2& na, double2& nb, int& n) {
+            na = sums(sA, n);
+            nb = sums(sB, n);
+            n = col[(i + 5) * M];
+            const double de = Ejm1 - readlane_f64(Ej, i);
+            const double Ba = rate(ga, de, dinv), Bb = rate(gb, de, dinv);
+            if (i > 0) {
+                xa = readlane_f64(acc_a * rc, i);
+                xb = readlane_f64(acc_b * rc, i);
+                // X_i >= 2^500 (uniform): rescale, exactly (the empty asm keeps
+                // this a scalar branch: without it the compiler computes the
+                // rescale at every step and selects)
+                const int ha = __double2hiint(xa), hb = __double2hiint(xb);
+                if ((ha > hb ? ha : hb) > BIG) {
+                    asm volatile("");
+                    if (ha > BIG) acc_a = ldexp(acc_a, -500), ++resc_a;
+                    if (hb > BIG) acc_b = ldexp(acc_b, -500), ++resc_b;
+                    xa = readlane_f64(acc_a * rc, i);
+                    xb = readlane_f64(acc_b * rc, i);
+                }
             }
+            if (jl > i) {
+                asm volatile("");  // (an exec-masked branch, not selects after the FMAs)
+                acc_a = fma(Ba, xa, acc_a);
+                acc_b = fma(Bb, xb, acc_b);
+            }
+        };
+        const int end = M - 1 < 32 ? M - 1 : 32;
+        for (int i = 0; i < end; i += 4) {
+            step(i, fa[0], fb[0], fa[3], fb[3], n0);
+            step(i + 1, fa[1], fb[1], fa[0], fb[0], n1);
+            step(i + 2, fa[2], fb[2], fa[1], fb[1], n0);
+            step(i + 3, fa[3], fb[3], fa[2], fb[2], n1);
         }
-        if (j > i) {
-            asm volatile("");  // (an exec-masked branch, not a select after the FMA)
-            acc = fma(B, xi, acc);
-        }
-    };
-    // two steps per pass, the sums alternating between two register sets
-    // (a copy from one to the other would wait for the reads at once)
-    double2 g2;
-    int i = 0;
-    for (; i + 1 < M - 1; i += 2) {
-        step(i, f2, g2);
-        step(i + 1, g2, f2);
     }
-    if (i < M - 1) step(i, f2, g2);
+    if (M > 33) {
+        // levels 32 and up of the second cell in lanes 0-31, of the first in 32-63
+        const bool first = lane >= 32;
+        const int jp = 32 + (lane & 31), jl = jp < M ? jp : -1;
+        const double Ep = upper_halves(Ejm1, Ejm1), dp = upper_halves(dinv, dinv);
+        const double rp = upper_halves(rc, rc);
+        const uint16_t* col = sCnt + (jp < M ? jp : M - 1);
+        const char* sp = first ? sA : sB;
+        double acc = upper_halves(acc_b, acc_a);
+        double2 f[4];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) f[r] = sums(sp, col[(32 + r) * M]);
+        int n0 = col[35 * M], n1 = col[36 * M];
+        auto step = [&](int i, double2& g, double2& nx, int& n) {
+            nx = sums(sp, n);
+            n = col[(i + 5) * M];
+            const double B = rate(g, Ep - readlane_f64(Ej, i), dp);
+            double x = acc * rp;
+            double xa = readlane_f64(x, i), xb = readlane_f64(x, i - 32);
+            const int ha = __double2hiint(xa), hb = __double2hiint(xb);
+            if ((ha > hb ? ha : hb) > BIG) {
+                asm volatile("");
+                if (ha > BIG) {
+                    acc_a = ldexp(acc_a, -500);
+                    if (first) acc = ldexp(acc, -500);
+                    ++resc_a;
+                }
+                if (hb > BIG) {
+                    acc_b = ldexp(acc_b, -500);
+                    if (!first) acc = ldexp(acc, -500);
+                    ++resc_b;
+                }
+                x = acc * rp;
+                xa = readlane_f64(x, i);
+                xb = readlane_f64(x, i - 32);
+            }
+            if (jl > i) {  // (lanes that drop their rate may hold the other cell's NaN)
+                asm volatile("");
+                acc = fma(B, first ? xa : xb, acc);
+            }
+        };
+        for (int i = 32; i < M - 1; i += 4) {
+            step(i, f[0], f[3], n0);
+            step(i + 1, f[1], f[0], n1);
+            step(i + 2, f[2], f[1], n0);
+            step(i + 3, f[3], f[2], n1);
+        }
+        acc_a = first ? acc : acc_a;
+        acc_b = lower_halves(acc_b, acc);
+    }
     // 3. normalise
-    const double X = j == 0 ? ldexp(1.0, -500 * rescales) : (j < M ? acc * rc : 0.0);
-    const double tot = wave_sum_f64(X);
-    const double inv = 1.0 / tot;
-    if (live && j < M) {
-        const double pv = X * inv;
-        P[c * ldp + (int64_t)s * M + j] = any_bad ? __builtin_nanf("") : (float)pv;
-        if (cnt && !any_bad && j == M - 1 && pv > TOP_PROBABILITY) count(&cnt->n_out_of_table);
+    auto finish = [&](double acc, int rescales, bool bad, int64_t c, bool live) {
+        const double X = j == 0 ? ldexp(1.0, -500 * rescales) : acc * rc;
+        const double inv = 1.0 / readlane_f64(wave_scan_f64(X), 63);
+        if (live && j < M) {
+            const double pv = X * inv;
+            P[c * ldp + (int64_t)s * M + j] = bad ? __builtin_nanf("") : (float)pv;
+            if (cnt && !bad && j == M - 1 && pv > TOP_PROBABILITY) count(&cnt->n_out_of_table);
+        }
+        if (live && cnt && bad && lane == 0) count(&cnt->n_nonfinite);
+    };
+    finish(acc_a, resc_a, bad_a, ca, true);
+    finish(acc_b, resc_b, bad_b, ca + 1, ca + 1 < C);
     }
-    if (live && cnt && any_bad && lane == 0) count(&cnt->n_nonfinite);
+}
+
+// Waves per workgroup: as many as leave the most waves on a CU, but fewer while
+// a call has less than a workgroup per CU (32 cells x 16 grains: 16.6 us with eight waves, 12.3).
+inline int staged_waves(int M, int NL, int S, int64_t C) {
+    int best = 0, most = 0;
+    for (int w = STAGED_MAX_WAVES; w >= 1; w >>= 1) {
+        const int n = STAGED_MAX_LDS / (staged_table_bytes(M) + w * staged_wave_bytes(NL)) * w;
+        if (n > most) most = n, best = w;
+    }
+    while (best > 1 && (C + 2 * best - 1) / (2 * best) * S < 256) best >>= 1;
+    return best;
+}
+
+template <int GR>
+hipError_t launch_staged(const View& v, int64_t C, const float* J, int64_t ldj, float* P,
+                         int64_t ldp, dust_counters* cnt, int w, hipStream_t st) {
+    const int64_t groups = (C + 2 * w - 1) / (2 * w);
+    const int64_t per = (STAGED_BLOCKS + v.S - 1) / v.S;
+    const int n = (int)(groups < per ? groups : per);
+    const bool aligned = ((uintptr_t)J & 15u) == 0 && (ldj & 3) == 0;
+    hipLaunchKernelGGL(solve_staged_kernel<GR>, dim3((unsigned)n * v.S), dim3(64 * w),
+                       (size_t)staged_table_bytes(v.M) + w * staged_wave_bytes(v.NL), st, v, C, J,
+                       ldj, aligned, P, ldp, n, cnt);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -582,6 +782,77 @@ __global__ __launch_bounds__(256) void emit_kernel(View v, int64_t C, const floa
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same emission for few cells: one wave per 16 cells x 16 wavelengths, both
+// operands straight from device memory a chunk of 32 k ahead, the products in
+// the order of emit_kernel (same bits).  64 cells x 128 wavelengths per
+// workgroup leave a small call with a handful of workgroups that each take
+// every chunk in turn: 32 cells x 1024 k x 250 wavelengths 63 us, 12 here, 2000
+// cells 62 and 25, 4000 (4000 waves) 64 and 48, 8000 58 and 94; 4000 cells x 64
+// k 8.6 and 11.
+// ---------------------------------------------------------------------------
+constexpr int64_t SMALL_EMIT_WAVES = 4096;
+
+template <int VW>
+__global__ __launch_bounds__(64) void emit_small_kernel(View v, int64_t C,
+                                                        const float* __restrict__ P, int64_t ldp,
+                                                        const float* __restrict__ m,
+                                                        float* __restrict__ L, int64_t ldl,
+                                                        int accumulate) {
+    const int lane = threadIdx.x & 63;
+    const int row = lane & 15, q = lane >> 4;
+    const int nl = (v.NL + 15) / 16;
+    const int64_t c0 = (int64_t)(blockIdx.x / (unsigned)nl) * 16;
+    const int l0 = (int)(blockIdx.x % (unsigned)nl) * 16;
+    const int64_t cr = c0 + row < C ? c0 + row : C - 1;
+    const float* pr = P + cr * ldp;
+    const float* et = v.etab + l0 + row;  // (columns padded to 128)
+    const int nch = v.Kp / E_KC;
+    auto load = [&](int ch, float (&a)[8], float (&e)[8]) {
+        const int k = ch * E_KC + 8 * q;
+        if (VW == 4 && k + 8 <= v.K) {
+#pragma unroll
+            for (int i = 0; i < 8; i += 4) {
+                const float4 f = *reinterpret_cast<const float4*>(pr + k + i);
+                a[i] = f.x;
+                a[i + 1] = f.y;
+                a[i + 2] = f.z;
+                a[i + 3] = f.w;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a[i] = k + i < v.K ? pr[k + i] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) e[i] = et[(int64_t)(k + i) * v.NLp];
+    };
+    constexpr int U = 4;  // chunks in flight
+    float a[U][8], e[U][8];
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(u < nch ? u : nch - 1, a[u], e[u]);
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int ch = 0; ch < nch; ch += U) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (ch + u >= nch) break;  // uniform
+#pragma unroll
+            for (int s = 0; s < 8; ++s)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][s], e[u][s], acc, 0, 0, 0);
+            const int nx = ch + u + U;
+            load(nx < nch ? nx : nch - 1, a[u], e[u]);
+        }
+    }
+    const int l = l0 + row;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int64_t cc = c0 + 4 * q + r;
+        if (cc >= C || l >= v.NL) continue;
+        const float val = acc[r] * ((m ? m[cc] : 1.0f) * v.escale);
+        float* dst = L + cc * ldl + l;
+        *dst = accumulate ? *dst + val : val;
+    }
+}
+
 int round_up(int x, int mlt) { return (x + mlt - 1) / mlt * mlt; }
 
 }  // namespace fluct
@@ -591,7 +862,7 @@ struct dust_fluct_plan {
     int device;
     double *d_lam, *d_dlam, *d_cabs, *d_w, *d_T;
     double *d_E, *d_eps, *d_kr, *d_rcool, *d_invd;
-    int* d_cnt;
+    uint16_t* d_cnt;
     float* d_etab;
     dust::fluct::View view;
 };
@@ -794,19 +1065,13 @@ dust_status dust_fluct_solve_P(dust_fluct_plan* p, int64_t C, const float* J, in
         return set_error(DUST_EINVAL, "leading dimension of P is smaller than n_grains x n_levels");
     const hipStream_t st = (hipStream_t)stream;
     const size_t lds = sizeof(double2) * (size_t)(v.NL + 1);
-    if (v.M <= STAGED_MAX_LEVELS) {
-        // as many cells per workgroup (up to eight) as the LDS allows
-        int w = STAGED_MAX_WAVES;
-        while (w > 1 && (size_t)staged_table_bytes(v.M) + w * lds > (size_t)MAX_LDS) w >>= 1;
-        if ((size_t)staged_table_bytes(v.M) + w * lds <= (size_t)MAX_LDS) {
-            const int64_t groups = (C + w - 1) / w;
-            hipLaunchKernelGGL(solve_staged_kernel, dim3((unsigned)(groups * v.S)), dim3(64 * w),
-                               (size_t)staged_table_bytes(v.M) + w * lds, st, v, C, J, ldj, P,
-                               ldp, cnt);
-            const hipError_t e = hipGetLastError();
-            return e == hipSuccess ? DUST_OK
-                                   : hip_error(e, "fluctuating-grain distribution launch");
-        }
+    hipError_t e;
+    const int w = v.M <= STAGED_MAX_LEVELS ? staged_waves(v.M, v.NL, v.S, C) : 0;
+    if (w > 0) {
+        if (v.NL <= 256) e = launch_staged<4>(v, C, J, ldj, P, ldp, cnt, w, st);
+        else if (v.NL <= 512) e = launch_staged<8>(v, C, J, ldj, P, ldp, cnt, w, st);
+        else e = launch_staged<0>(v, C, J, ldj, P, ldp, cnt, w, st);
+        return e == hipSuccess ? DUST_OK : hip_error(e, "fluctuating-grain distribution launch");
     }
     const dim3 grid((unsigned)(C * v.S));
     if (v.M <= 64)
@@ -815,7 +1080,7 @@ dust_status dust_fluct_solve_P(dust_fluct_plan* p, int64_t C, const float* J, in
         hipLaunchKernelGGL(solve_kernel<2>, grid, dim3(64), lds, st, v, C, J, ldj, P, ldp, cnt);
     else
         hipLaunchKernelGGL(solve_kernel<4>, grid, dim3(64), lds, st, v, C, J, ldj, P, ldp, cnt);
-    const hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     return e == hipSuccess ? DUST_OK : hip_error(e, "fluctuating-grain distribution launch");
 }
 
@@ -837,6 +1102,17 @@ dust_status dust_fluct_emit_sed(dust_fluct_plan* p, int64_t C, const float* P, i
     if (blocks > INT32_MAX) return set_error(DUST_EUNSUPPORTED, "too many cells");
     const hipStream_t st = (hipStream_t)stream;
     const int acc_flag = accumulate ? 1 : 0;
+    const int64_t small = (C + 15) / 16 * ((v.NL + 15) / 16);
+    if (small <= (v.K >= 256 ? SMALL_EMIT_WAVES : SMALL_EMIT_WAVES / 2)) {
+        if ((ldp % 4) == 0 && ((uintptr_t)P & 15u) == 0)
+            hipLaunchKernelGGL(emit_small_kernel<4>, dim3((unsigned)small), dim3(64), 0, st, v, C, P,
+                               ldp, m, L, ldl, acc_flag);
+        else
+            hipLaunchKernelGGL(emit_small_kernel<1>, dim3((unsigned)small), dim3(64), 0, st, v, C, P,
+                               ldp, m, L, ldl, acc_flag);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? DUST_OK : hip_error(e, "fluctuating-grain emission launch");
+    }
     if ((ldp % 4) == 0 && ((uintptr_t)P & 15u) == 0)
         hipLaunchKernelGGL(emit_kernel<4>, dim3((unsigned)blocks), dim3(256), 0, st, v, C, P, ldp,
                            m, L, ldl, acc_flag);

@@ -210,3 +210,43 @@ def test_table_solve_forms_agree(mode, lookup):
         assert torch.equal(out[:n, :S].nan_to_num(-3.0), T.nan_to_num(-3.0))
         assert bool((out[n] == -7.0).all()) and bool((out[:, S:] == -7.0).all())
         assert torch.equal(big, small) and int(big[0]) == 3 * S
+
+
+@pytest.mark.parametrize("n_lambda,n_sizes,n_levels", [
+    (250, 3, 64),     # four wavelengths per lane, the packed upper half at its longest
+    (257, 2, 34),     # eight per lane, one packed level
+    (600, 1, 33),     # any number, no packed level; odd level count
+    (40, 2, 5),
+    (250, 2, 80),     # two levels per lane (one cell per wave)
+])
+def test_fluctuating_forms_agree(n_lambda, n_sizes, n_levels):
+    """The distributions of a cell do not depend on the call it is in (which
+    cell shares its wave, how many cells a workgroup takes, how J is aligned),
+    with a neighbour that is NaN; nor does the averaged emission (one wave per
+    tile, or 64-cell workgroups)."""
+    g = synth.make_species_grid(n_lambda, [2], n_sizes)
+    lev_T, lev_E = synth.fluct_levels(g, n_levels)
+    n = 33000 // n_sizes
+    p = synth.cell_params(n, 13)
+    buf = torch.empty((n, n_lambda + 3), dtype=torch.float32, device="cuda")
+    J = synth.radiation_field(p, g.lam, device="cuda", out=buf)[:, :n_lambda]
+    J[2] = 0.0
+    J[5, 3] = float("nan")
+    m = torch.as_tensor(p.m_dust, dtype=torch.float32, device="cuda")
+    plan = dust.FluctPlan(g, lev_T, lev_E)
+    big = dust.new_counters()
+    P = plan.solve_P(J, counters=big)
+    ref = oracle.fluct_distribution(J[6:16].cpu().numpy().astype(np.float64), g, lev_T, lev_E)
+    out = P[6:16].cpu().numpy().reshape(ref.shape)
+    seen = ref >= 1e-30
+    assert np.abs(out[seen] / ref[seen] - 1.0).max() <= 1e-6
+    assert bool(P[5].isnan().all()) and int(big[0]) == n_sizes
+    L = plan.emit(P, m)
+    for first, rows in ((0, 1), (1, 7), (4, 2), (3, 40), (0, 1000), (1, n - 1)):
+        e = first + rows
+        aligned = J[first:e].contiguous()
+        for Jp in (J[first:e], aligned):
+            Pp = plan.solve_P(Jp)
+            assert torch.equal(Pp.nan_to_num(-1.0), P[first:e].nan_to_num(-1.0)), (first, rows)
+        Lp = plan.emit(P[first:e], m[first:e])
+        assert torch.equal(Lp.nan_to_num(-1.0), L[first:e].nan_to_num(-1.0)), (first, rows)
