@@ -517,8 +517,13 @@ dust_status dust_batch_create(dust_plan* const* plans, int32_t n_grids, const in
         std::vector<RefreshJob> jobs(nj);
         std::vector<int> starts(4 * (size_t)nj);
         int64_t total[4] = {0, 0, 0, 0};
+        int64_t pairs = 0;
         for (int k = 0; k < nj; ++k) {
             make_refresh_job(uniq[k], &jobs[k]);
+            pairs += product_pairs(jobs[k]);
+        }
+        for (int k = 0; k < nj; ++k) {
+            set_product_tiles(&jobs[k], pairs);
             for (int st = 0; st < 4; ++st) {
                 starts[(size_t)st * nj + k] = (int)total[st];
                 total[st] += (int64_t)jobs[k].gx[st] * jobs[k].gy[st];

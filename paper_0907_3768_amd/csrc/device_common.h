@@ -400,15 +400,31 @@ __device__ __forceinline__ double exp_f64(double x) {
 }
 
 // ---------------------------------------------------------------------------
-// e^x - 1 in FP64 for x >= 0: e^x - 1 where that loses at most a few units
-// in the last place relative (x >= 0.01: <= 2.3e-14), the Taylor series to
-// x^7 below (truncation x^8/8! < 3e-21 relative).
+// e^x - 1 in FP64 for x >= 0, as 2^k (e^r - 1) + (2^k - 1) with the reduction
+// of exp_f64 and the Taylor series of e^r - 1 to r^12 (truncation < 5e-16
+// relative): +inf from x = 1023.5 ln 2 on.  Without branches, so that several
+// evaluations of a lane run side by side (the series is a chain of twelve
+// dependent instructions).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double expm1_pos(double x) {
-    if (x >= 0.01) return exp_f64(x) - 1.0;
-    const double p = 1.0 + x * (1.0 / 2 + x * (1.0 / 6 + x * (1.0 / 24 + x * (1.0 / 120 +
-                     x * (1.0 / 720 + x * (1.0 / 5040))))));
-    return x * p;
+    const double k = __builtin_rint(x * 1.4426950408889634);
+    double r = fma(-k, 6.93147180369123816490e-01, x);
+    r = fma(-k, 1.90821492927058770002e-10, r);
+    double p = 1.0 / 479001600.0;
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    const int e = (int)k;
+    const double s = __hiloint2double((int)(((uint32_t)e + 1023u) << 20), 0);  // 2^k, k <= 1023
+    return e <= 1023 ? fma(p * r, s, s - 1.0) : __builtin_inf();
 }
 
 // ---------------------------------------------------------------------------

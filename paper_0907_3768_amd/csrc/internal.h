@@ -174,8 +174,14 @@ struct RefreshJob {
     float2* invf;
     float *ylof, *dyinvf;
     int gx[4], gy[4];
+    int lt_tiles;  // grain tiles per workgroup of the table product (stage 2)
 };
+// The job of one plan, its product's grid as for a launch of its own.
 void make_refresh_job(const dust_plan* p, RefreshJob* j);
+// (16-point block, grain tile) pairs of a job's product, and its grid for a
+// launch that holds `pairs` of them in all.
+int64_t product_pairs(const RefreshJob& j);
+void set_product_tiles(RefreshJob* j, int64_t pairs);
 // The refresh of many plans as four launches (one per stage); d_starts[k]
 // holds, per plan, the first block of its range in stage k (ascending).
 hipError_t launch_prepare_batched(const RefreshJob* d_jobs, const int* const d_starts[4],

@@ -82,20 +82,39 @@ __device__ __forceinline__ void prep_body(const RefreshJob& j, int bx, int by) {
 
 // y[s][k] = ln sum_l W[s][l] F[k][l] (table-linear: the sum itself): an FP64
 // product on the matrix cores (v_mfma_f64_16x16x4_f64) whose F operand is
-// computed in registers and never stored.  Each wave owns 16 table points
-// (a workgroup's four waves take four consecutive blocks of them) and up to
-// LT_SG grain tiles of 16.  Per 32-wavelength step, lane (row = lane mod 16,
-// q = lane / 16) computes F for point row and wavelengths l0 + 8 q .. + 7
-// (eight FP64 exponentials), loads the same wavelengths of each grain tile's
-// row of W (contiguous 64 bytes) and issues eight MFMAs per tile; MFMA t
-// takes the t-th wavelength of both operands (any assignment of wavelengths
-// to k-slots gives the same sum when both operands use it).  Element j of a
-// tile's accumulator in lane (col, q) holds grain row q + 4 j of point col
-// (the FP64 form interleaves rows).
-// Grain tiles per wave when many plans share a launch: four (the product's
-// exponentials are spent once per four tiles).  A single plan takes the
-// split form below instead (LT_SG_SINGLE only instantiates the other stages).
-constexpr int LT_SG_BATCHED = 4, LT_SG_SINGLE = 1;
+// computed in registers and never stored.  A workgroup takes one block of 16
+// points and up to LT_TILES grain tiles of 16; its LT_WAVES waves split the
+// 16-wavelength steps (wave w takes steps w, w + 8, ...) and their partial
+// sums meet in LDS.  Per step, lane (row = lane mod 16, q = lane / 16)
+// computes F for point row and wavelengths l0 + 4 q .. + 3 (four FP64
+// exponentials), loads the same wavelengths of each grain tile's row of W
+// (contiguous 32 bytes) and issues four MFMAs per tile; MFMA t takes the
+// t-th wavelength of both operands (any assignment of wavelengths to k-slots
+// gives the same sum when both operands use it).  Element j of a tile's
+// accumulator in lane (col, q) holds grain row q + 4 j of point col (the
+// FP64 form interleaves rows).
+//
+// What bounds it is a wave's chain of exponentials and dependent MFMAs (FP64
+// ones, which take as long as the vector unit's), so the steps are spread over
+// eight waves even where many plans share the launch; there, and for a plan
+// with many grains, a wave shares its exponentials among several tiles
+// (product_tiles).  A refresh of all three stages, with four waves, 32
+// wavelengths a step and one tile (many plans: one wave with the whole range
+// and four tiles), and now: 250 x 80 19.8 -> 16.2 us, 968 x 81 42 -> 27, 1000 x
+// 240 62 -> 46, table-linear 1000 x 240 117 -> 62; 64 plans' refresh and solve
+// 14.23 -> 13.97 ms.  Weights loaded before the exponentials cost the registers
+// of a wave per SIMD (1000 x 240: 55 us).
+constexpr int LT_WAVES = 8, LT_TILES = 4, LT_STEP = 16;
+
+// Grain tiles per workgroup of the product for `blocks` (16-point block, grain
+// tile) pairs in one launch: one as long as the GPU has a place for each
+// workgroup at once (two per CU).  A refresh of 968 x 81 (432 pairs) takes 30.3
+// us with one, 29.4 with two, 36.7 with four; of 500 x 128 (576) 24.4 with two,
+// 25.3 with four.
+constexpr int64_t LT_PAIRS = 512;
+int product_tiles(int64_t blocks) {
+    return blocks <= LT_PAIRS ? 1 : (blocks <= 2 * LT_PAIRS ? 2 : LT_TILES);
+}
 
 // 1/T of table point k: the N points of the table's range, then the Nc points
 // below it (mixed); 0 past the last.
@@ -115,119 +134,109 @@ __device__ __forceinline__ void store_point(const RefreshJob& j, int s, int k, d
         j.fwd_c[(int64_t)s * j.Nc + (k - v.N)] = log(P);
 }
 
-template <int LT_SG>
-__device__ __forceinline__ void ltab_gemm_body(const RefreshJob& j, int bx, int by) {
+__device__ __forceinline__ void product_body(const RefreshJob& j, int bx, int by) {
     typedef double f64x4 __attribute__((ext_vector_type(4)));
-    const PlanView& v = j.v;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int row = lane & 15, q = lane >> 4;
-    const int k0 = (bx * 4 + wave) * 16;
-    const int sg0 = by * LT_SG * 16;
-    const int k = k0 + row;
-    const bool k_ok = k < v.N + j.Nc;
-    const double invT = point_inv_T(j, k);
-    f64x4 acc[LT_SG];
-#pragma unroll
-    for (int t = 0; t < LT_SG; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int l0 = 0; l0 < v.NL; l0 += 32) {
-        double f[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int l = l0 + 8 * q + t;
-            double x = 0.0;
-            if (k_ok && l < v.NL) {
-                const double em = expm1_pos(v.c2l[l] * invT);
-                x = (em < __builtin_inf()) ? rcp_f64(em) : 0.0;  // 0 once e^x overflows
-            }
-            f[t] = x;
-        }
-#pragma unroll
-        for (int st = 0; st < LT_SG; ++st) {
-            const int s_tile = sg0 + st * 16;
-            if (s_tile >= v.S) break;  // uniform
-            const int s = s_tile + row;
-            const double* wr = v.kdb + (int64_t)(s < v.S ? s : 0) * v.NL;
-            double a[8];
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int l = l0 + 8 * q + t;
-                a[t] = (s < v.S && l < v.NL) ? wr[l] : 0.0;
-            }
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-                acc[st] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], f[t], acc[st], 0, 0, 0);
-        }
-    }
-#pragma unroll
-    for (int st = 0; st < LT_SG; ++st) {
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int sr = sg0 + st * 16 + q + 4 * jj;
-            if (sr < v.S && k_ok) store_point(j, sr, k, acc[st][jj]);
-        }
-    }
-}
-
-// The product for a single plan: a workgroup takes one block of 16 points
-// and one grain tile, its four waves split the wavelength steps (wave w
-// takes steps w, w + 4, ...) and the partial accumulators meet in LDS.  A
-// single grid has too few (point block, grain tile) pairs to fill the GPU
-// with one wave each, and each wave's chain of FP64 exponentials is then the
-// whole wavelength range.
-__device__ __forceinline__ void ltab_gemm_split_body(const RefreshJob& j, int bx, int by) {
-    typedef double f64x4 __attribute__((ext_vector_type(4)));
-    __shared__ f64x4 part[3][64];
+    __shared__ f64x4 part[LT_WAVES / 2][LT_TILES][64];
+    constexpr int NF = LT_STEP / 4;
     const PlanView& v = j.v;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane & 15, q = lane >> 4;
     const int k = bx * 16 + row;
-    const int s = by * 16 + row;
     const bool k_ok = k < v.N + j.Nc;
     const double invT = point_inv_T(j, k);
-    const double* wr = v.kdb + (int64_t)(s < v.S ? s : 0) * v.NL;
-    f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int l0 = 32 * wave; l0 < v.NL; l0 += 128) {
+    const int tiles = (v.S + 15) / 16 - by * j.lt_tiles;
+    const int nt = tiles < j.lt_tiles ? tiles : j.lt_tiles;
+    const int s0 = by * j.lt_tiles * 16;
+    f64x4 acc[LT_TILES];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-            const int l = l0 + 8 * q + t;
-            double f = 0.0, a = 0.0;
-            if (l < v.NL) {
-                if (k_ok) {
-                    const double em = expm1_pos(v.c2l[l] * invT);
-                    f = (em < __builtin_inf()) ? rcp_f64(em) : 0.0;  // 0 once e^x overflows
-                }
-                if (s < v.S) a = wr[l];
+    for (int t = 0; t < LT_TILES; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+    for (int l0 = LT_STEP * wave; l0 < v.NL; l0 += LT_STEP * LT_WAVES) {
+        const int lq = l0 + NF * q;
+        double f[NF];
+#pragma unroll
+        for (int t = 0; t < NF; ++t) {
+            const int l = lq + t < v.NL ? lq + t : v.NL - 1;
+            const double em = expm1_pos(v.c2l[l] * invT);
+            // 0 once e^x overflows, and past the last wavelength or point
+            f[t] = (em < __builtin_inf() && lq + t < v.NL && k_ok) ? rcp_f64(em) : 0.0;
+        }
+#pragma unroll
+        for (int st = 0; st < LT_TILES; ++st) {
+            if (st >= nt) break;  // uniform
+            const int s = s0 + 16 * st + row;
+            const double* wr = v.kdb + (int64_t)(s < v.S ? s : v.S - 1) * v.NL;
+            double a[NF];
+            if (l0 + LT_STEP <= v.NL) {  // uniform
+#pragma unroll
+                for (int t = 0; t < NF; ++t) a[t] = wr[lq + t];
+            } else {
+#pragma unroll
+                for (int t = 0; t < NF; ++t) a[t] = wr[lq + t < v.NL ? lq + t : v.NL - 1];
             }
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, f, acc, 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < NF; ++t)
+                acc[st] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], f[t], acc[st], 0, 0, 0);
         }
     }
-    if (wave > 0) part[wave - 1][lane] = acc;
+    // waves 4-7 hand their sums to waves 0-3, whose four then meet in the wave
+    // that stores the tile
+    constexpr int HALF = LT_WAVES / 2;
+    static_assert(HALF == LT_TILES, "wave st finishes tile st");
+    if (wave >= HALF) {
+#pragma unroll
+        for (int st = 0; st < LT_TILES; ++st)
+            if (st < nt) part[wave - HALF][st][lane] = acc[st];
+    }
     __syncthreads();
-    if (wave == 0) {
-        acc += part[0][lane] + part[1][lane] + part[2][lane];
+    if (wave < HALF) {
+#pragma unroll
+        for (int st = 0; st < LT_TILES; ++st)
+            if (st < nt) {
+                acc[st] += part[wave][st][lane];
+                part[wave][st][lane] = acc[st];
+            }
+    }
+    __syncthreads();
+    if (wave < nt) {
+        const f64x4 sum = (part[0][wave][lane] + part[1][wave][lane]) +
+                          (part[2][wave][lane] + part[3][wave][lane]);
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
-            const int sr = by * 16 + q + 4 * jj;
-            if (sr < v.S && k_ok) store_point(j, sr, k, acc[jj]);
+            const int sr = s0 + 16 * wave + q + 4 * jj;
+            if (sr < v.S && k_ok) store_point(j, sr, k, sum[jj]);
         }
     }
+}
+
+// A grain's forward row for the searches below: in LDS up to FWD_LDS points
+// (a search is ten or more reads, each waiting for the one before), in place
+// above.  The caller's whole block takes part.
+constexpr int FWD_LDS = 2048;
+
+template <bool LOG>
+__device__ __forceinline__ const double* stage_row(const double* f, int N, double* sF) {
+    if (N > FWD_LDS) return f;  // uniform
+    for (int i = threadIdx.x; i < N; i += blockDim.x) sF[i] = LOG ? log(f[i]) : f[i];
+    __syncthreads();
+    return sF;
 }
 
 // Table-linear: one thread per (grain, node); node j sits at
 // ln P' = ylo + j (yhi - ylo) / (M - 1) and kidx[s][j] is the largest k in
 // [0, N-2] with ln P'_k <= that value (0 if none).
-__device__ __forceinline__ void kidx_body(const RefreshJob& job, int bx, int by) {
+__device__ __forceinline__ void kidx_body(const RefreshJob& job, int bx, int by, double* sF) {
     const PlanView& v = job.v;
     const double* __restrict__ fwd = job.fwd;
     int* kidx = job.kidx;
     double* ylo = job.ylo; double* yhi = job.yhi; double* dyinv = job.dyinv;
     const int j = bx * blockDim.x + threadIdx.x;
     const int s = by;
-    if (j >= v.M) return;
     const int N = v.N;
     const double* P = fwd + (int64_t)s * N;
+    const double* y = stage_row<true>(P, N, sF);
+    if (j >= v.M) return;
+    const bool staged = N <= FWD_LDS;
     const double y0 = log(P[0]), y1 = log(P[N - 1]);
     const double dinv = (v.M - 1) / (y1 - y0);
     if (j == 0) {
@@ -239,7 +248,7 @@ __device__ __forceinline__ void kidx_body(const RefreshJob& job, int bx, int by)
     int lo = 0, hi = N - 2;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (log(P[mid]) <= yj) lo = mid; else hi = mid - 1;
+        if ((staged ? y[mid] : log(P[mid])) <= yj) lo = mid; else hi = mid - 1;
     }
     kidx[(int64_t)s * v.M + j] = lo;
 }
@@ -268,14 +277,14 @@ __device__ __forceinline__ double2 inverse_node(const double* __restrict__ f, in
 
 // One thread per (grain, inverse node): ln T at y_j = ylo + j dy and
 // dy * d ln T / dy.  The last block column makes the table below the range.
-__device__ __forceinline__ void inv_body(const RefreshJob& job, int bx, int by) {
+__device__ __forceinline__ void inv_body(const RefreshJob& job, int bx, int by, double* sF) {
     const PlanView& v = job.v;
     const int s = by;
     const bool cold = bx == job.gx[3] - 1;
     const int j = cold ? threadIdx.x : bx * blockDim.x + threadIdx.x;
     const int M = cold ? COLD_M : v.M, N = cold ? job.Nc : v.N;
+    const double* f = stage_row<false>((cold ? job.fwd_c : job.fwd) + (int64_t)s * N, N, sF);
     if (j >= M) return;
-    const double* f = (cold ? job.fwd_c : job.fwd) + (int64_t)s * N;
     const double y0 = f[0], y1 = f[N - 1];
     const double dinv = (M - 1) / (y1 - y0);
     if (j == 0) {
@@ -309,29 +318,33 @@ __device__ __forceinline__ void inv_body(const RefreshJob& job, int bx, int by) 
 // The stages of a refresh (0 prep, 2 table product, 3 inverse table or search
 // brackets; stage 1 is empty since the product computes its Planck factors
 // itself): one block of a stage's grid.
-template <int STAGE, int LT_SG>
+template <int STAGE>
 __device__ __forceinline__ void refresh_stage(const RefreshJob& j, int bx, int by) {
-    if constexpr (STAGE == 0) prep_body(j, bx, by);
-    else if constexpr (STAGE == 2) ltab_gemm_body<LT_SG>(j, bx, by);
-    else if (j.v.mode == DUST_TABLE_LINEAR) kidx_body(j, bx, by);
-    else inv_body(j, bx, by);
+    if constexpr (STAGE == 0) {
+        prep_body(j, bx, by);
+    } else if constexpr (STAGE == 2) {
+        product_body(j, bx, by);
+    } else {
+        __shared__ double sF[FWD_LDS];
+        if (j.v.mode == DUST_TABLE_LINEAR) kidx_body(j, bx, by, sF);
+        else inv_body(j, bx, by, sF);
+    }
 }
 
-// One plan: the job by value, the stage's 2-D grid (the product in its
-// split form).
+// Threads of a stage's workgroup.
+constexpr int stage_threads(int stage) { return stage == 2 ? 64 * LT_WAVES : 256; }
+
+// One plan: the job by value, the stage's 2-D grid.
 template <int STAGE>
-__global__ __launch_bounds__(256) void refresh_kernel(RefreshJob j) {
-    if constexpr (STAGE == 2)
-        ltab_gemm_split_body(j, blockIdx.x, blockIdx.y);
-    else
-        refresh_stage<STAGE, LT_SG_SINGLE>(j, blockIdx.x, blockIdx.y);
+__global__ __launch_bounds__(stage_threads(STAGE)) void refresh_kernel(RefreshJob j) {
+    refresh_stage<STAGE>(j, blockIdx.x, blockIdx.y);
 }
 
 // Many plans in one launch: the flat block index is located among the plans'
 // consecutive ranges (starts[p] = first block of plan p, ascending) and
 // unfolded into that plan's 2-D grid of x extent gx.
 template <int STAGE>
-__global__ __launch_bounds__(256) void refresh_batched_kernel(const RefreshJob* __restrict__ jobs,
+__global__ __launch_bounds__(stage_threads(STAGE)) void refresh_batched_kernel(const RefreshJob* __restrict__ jobs,
                                                               const int* __restrict__ starts,
                                                               int n_jobs) {
     const int b = blockIdx.x;
@@ -343,15 +356,13 @@ __global__ __launch_bounds__(256) void refresh_batched_kernel(const RefreshJob* 
     const RefreshJob& j = jobs[lo];
     const int local = b - starts[lo];
     const int gx = j.gx[STAGE];
-    refresh_stage<STAGE, LT_SG_BATCHED>(j, local % gx, local / gx);
+    refresh_stage<STAGE>(j, local % gx, local / gx);
 }
 
 template <int STAGE>
 hipError_t launch_stage(const RefreshJob& j, hipStream_t st) {
-    // the single-plan product: one (16-point block, grain tile) per workgroup
-    const int gx = (STAGE == 2) ? (j.v.N + j.Nc + 15) / 16 : j.gx[STAGE];
-    const int gy = (STAGE == 2) ? (j.v.S + 15) / 16 : j.gy[STAGE];
-    hipLaunchKernelGGL(refresh_kernel<STAGE>, dim3(gx, gy), dim3(256), 0, st, j);
+    hipLaunchKernelGGL(refresh_kernel<STAGE>, dim3(j.gx[STAGE], j.gy[STAGE]),
+                       dim3(stage_threads(STAGE)), 0, st, j);
     return hipGetLastError();
 }
 
@@ -359,12 +370,19 @@ template <int STAGE>
 hipError_t launch_batched_stage(const RefreshJob* d_jobs, const int* d_starts, int n_jobs,
                                 int blocks, hipStream_t st) {
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(refresh_batched_kernel<STAGE>, dim3(blocks), dim3(256), 0, st, d_jobs,
-                       d_starts, n_jobs);
+    hipLaunchKernelGGL(refresh_batched_kernel<STAGE>, dim3(blocks), dim3(stage_threads(STAGE)), 0,
+                       st, d_jobs, d_starts, n_jobs);
     return hipGetLastError();
 }
 
 }  // namespace
+
+int64_t product_pairs(const RefreshJob& j) { return (int64_t)j.gx[2] * ((j.v.S + 15) / 16); }
+
+void set_product_tiles(RefreshJob* j, int64_t pairs) {
+    j->lt_tiles = product_tiles(pairs);
+    j->gy[2] = ((j->v.S + 15) / 16 + j->lt_tiles - 1) / j->lt_tiles;
+}
 
 void make_refresh_job(const dust_plan* p, RefreshJob* j) {
     const PlanView& v = p->view;
@@ -388,8 +406,8 @@ void make_refresh_job(const dust_plan* p, RefreshJob* j) {
     }
     j->gx[0] = (v.NLp + 255) / 256;  j->gy[0] = v.Sp;
     j->gx[1] = 1;                    j->gy[1] = 0;
-    j->gx[2] = (v.N + j->Nc + 63) / 64;
-    j->gy[2] = tab ? (v.S + LT_SG_BATCHED * 16 - 1) / (LT_SG_BATCHED * 16) : 0;  // batched launches
+    j->gx[2] = (v.N + j->Nc + 15) / 16;
+    set_product_tiles(j, product_pairs(*j));
     // (mixed: one more column for the table below the range)
     j->gx[3] = (v.M + 255) / 256 + (j->Nc > 0); j->gy[3] = tab ? v.S : 0;
 }

@@ -250,3 +250,56 @@ def test_fluctuating_forms_agree(n_lambda, n_sizes, n_levels):
             assert torch.equal(Pp.nan_to_num(-1.0), P[first:e].nan_to_num(-1.0)), (first, rows)
         Lp = plan.emit(P[first:e], m[first:e])
         assert torch.equal(Lp.nan_to_num(-1.0), L[first:e].nan_to_num(-1.0)), (first, rows)
+
+
+@pytest.mark.parametrize("n_lambda,n_species,n_sizes,ltab_n", [
+    (8, 1, 5, 0),        # one partial wavelength step, one grain tile
+    (16, 2, 8, 3000),    # one whole step; forward rows too long for LDS
+    (129, 1, 81, 0),     # one step more than the eight waves take; one tile per workgroup
+    (250, 3, 50, 0),     # two tiles per workgroup
+    (301, 3, 75, 0),     # four tiles per workgroup and a rest of three
+])
+def test_refresh_forms(n_lambda, n_species, n_sizes, ltab_n):
+    """The tables of every form of the refresh: T of heating in their range,
+    given in FP32, against the oracle (mixed, polished on the forward table,
+    whose cubic's error is below 1e-8; ln H' to 4e-8, rounding and FP32
+    exponential 2 ulp) and against the linear interpolation in 64 bits (table:
+    rounding, with 1 ulp for the reciprocal's argument), and the same bits from
+    the refresh of a batch.  (The default lookup on a grid of 8 wavelengths
+    adds its inverse table's own interpolation error, 3.5e-7.)"""
+    g = synth.make_grid(n_lambda, n_species, n_sizes)
+    scale = 2.0 ** 60  # keeps H in FP32's normal range (the emission weights unchanged)
+    g.c_abs, g.weight = g.c_abs * scale, g.weight / scale
+    T = np.geomspace(12.0, 1200.0, 61)
+    c1, c2 = 2 * 6.62607015e-34 * 299792458.0 ** 2, 6.62607015e-34 * 299792458.0 / 1.380649e-23
+
+    def power(t):
+        B = c1 / g.lam ** 5 / np.expm1(np.minimum(c2 / (g.lam * t[:, None]), 700.0))
+        return B @ (g.c_abs * g.dlam).T
+
+    H = power(T).astype(np.float32)
+    Hd = torch.as_tensor(H, device="cuda")
+    n = ltab_n or 2000
+    plan = dust.Plan(g, "table", ltab_n=ltab_n)
+    out = plan.solve(Hd).cpu().numpy()
+    t = 3.0 + np.arange(n) * (1500.0 - 3.0) / (n - 1)
+    P = power(t)
+    ref = np.stack([np.interp(H[:, s].astype(np.float64), P[:, s], t)
+                    for s in range(g.n_grains)], axis=1)
+    assert np.abs(out / ref - 1.0).max() <= 1.2e-7
+    polished = dust.Plan(g, "mixed", ltab_n=ltab_n, newton_polish=True)
+    ref = oracle.temperature(H.astype(np.float64), g.lam, g.dlam, g.c_abs, g.size)
+    assert np.abs(polished.solve(Hd).cpu().numpy() / ref - 1.0).max() <= 3e-7
+    plan = dust.Plan(g, "mixed", ltab_n=ltab_n)
+    before = plan.solve(Hd)
+    other = dust.Plan(synth.make_grid(200, 3, 80), "mixed")
+    plans = [plan, other, plan]
+    args = []
+    for k, p in enumerate(plans):
+        J = torch.rand((20 + k, p.n_lambda), device="cuda")
+        args.append((J, torch.ones(20 + k, device="cuda"),
+                     torch.empty((20 + k, p.n_grains), device="cuda"), torch.empty_like(J)))
+    b = dust.Batch(plans, *[list(a) for a in zip(*args)], refresh_plans=True)
+    b.launch()
+    torch.cuda.synchronize()
+    assert torch.equal(plan.solve(Hd), before)
