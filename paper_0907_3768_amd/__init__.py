@@ -124,10 +124,17 @@ def _check(code):
         raise DustError(code, last_error())
 
 
+def _current_stream():
+    """The current device's current stream as an integer handle.  Without the
+    Stream object that torch.cuda.current_stream() makes (2.9 us a call, as much
+    as a launch; the handle alone 0.1 us)."""
+    import torch
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return _vp(torch.cuda.current_stream().cuda_stream)
+        return _vp(_current_stream())
     if isinstance(stream, int):
         return _vp(stream)
     return _vp(stream.cuda_stream)
@@ -302,6 +309,7 @@ class Plan:
     def run(self, J, m_dust=None, counters=None, stream=None, Q=None, T=None,
             warm_start=False):
         """absorb -> solve -> emit as three launches; returns (H, T, L)."""
+        stream = _current_stream() if stream is None else stream
         H = self.absorb(J, stream=stream)
         T = self.solve(H, T=T, counters=counters, stream=stream, Q=Q, warm_start=warm_start)
         L = self.emit(T, m_dust, stream=stream)
