@@ -303,3 +303,26 @@ def test_refresh_forms(n_lambda, n_species, n_sizes, ltab_n):
     b.launch()
     torch.cuda.synchronize()
     assert torch.equal(plan.solve(Hd), before)
+
+
+@pytest.mark.parametrize("n_lambda,n_sizes", [(60, 9), (97, 17), (300, 40)])
+def test_emission_over_every_form(n_lambda, n_sizes):
+    """Cells of one temperature, 3 K to 1e5 K, so that each block of wavelengths
+    meets every form of the Planck term, against 64 bits.  Bound for
+    x = hc/(k lam T): the exponent's factors and product, 4 roundings times its
+    sensitivity x / (1 - e^-x); e^x and 1 / (e^x - 1), 2 units each, the first
+    over 1 - e^-x; the cut series, 1; the weights and the sum, n_sizes + 4
+    roundings."""
+    g = synth.make_grid(n_lambda, 1, n_sizes)
+    T = np.geomspace(3.0, 1e5, 400).astype(np.float32)
+    Td = torch.as_tensor(np.repeat(T[:, None], n_sizes, axis=1), device="cuda")
+    L = dust.Plan(g, "plain").emit(Td).cpu().numpy()
+    c1, c2 = 2 * 6.62607015e-34 * 299792458.0 ** 2, 6.62607015e-34 * 299792458.0 / 1.380649e-23
+    x = c2 / (g.lam * T[:, None].astype(np.float64))
+    em = (g.weight[:, None] * g.c_abs * c1 / g.lam ** 5).sum(axis=0)
+    with np.errstate(over="ignore"):
+        ref = em / np.expm1(x)
+    tol = 2.0 ** -24 * ((4 * x + 4) / -np.expm1(-x) + 5 + n_sizes + 4)
+    seen = (x < 100.0) & (ref > 1e-25 * em.max())
+    assert seen.sum() > 0.5 * x.size
+    assert (np.abs(L[seen] / ref[seen] - 1.0) <= tol[seen]).all()
