@@ -117,7 +117,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTW <= 2 ? 
 // registers (values the compiler keeps live across items).  Resident waves
 // per SIMD as for the single-grid fused kernel: six for up to 128 grains,
 // five above.
-template <int TC, int NTW>
+// PARTS: gridDim.y workgroups per item share its emission (see fused_tile),
+// the first counting its events (item_parts).
+template <int TC, int NTW, bool PARTS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTW <= 2 ? 6 : 5, 8))) void batch_item_kernel(
     const GridArgs* __restrict__ grids,
                                                          const int2* __restrict__ items,
@@ -129,8 +131,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTW <= 2 ? 
     const int gx = __builtin_amdgcn_readfirstlane(items[it].x);
     const int ty = __builtin_amdgcn_readfirstlane(items[it].y);
     const GridArgs& g = grids[gx];
-    fused_tile<DUST_MIXED, TC, NTW, true, BATCH_KC>(g.v, (int64_t)ty * TC, g.C, g.J, g.ldj, g.m, g.T, g.ldt, g.L,
-                                    g.ldl, cnt, sTile);
+    fused_tile<DUST_MIXED, TC, NTW, true, BATCH_KC>(
+        g.v, (int64_t)ty * TC, g.C, g.J, g.ldj, g.m, g.T, g.ldt, g.L, g.ldl,
+        PARTS && blockIdx.y > 0 ? nullptr : cnt, sTile, PARTS ? (int)blockIdx.y : 0,
+        PARTS ? (int)gridDim.y : 1);
     (void)counter;
 }
 
@@ -150,16 +154,31 @@ KernelFn pick_kernel(int ntw) {
     return batch_kernel<TC, 4>;  // larger grain sets take several passes
 }
 
-template <int TC>
+template <int TC, bool PARTS>
 KernelFn pick_item_kernel(int ntw) {
-    if (ntw <= 1) return batch_item_kernel<TC, 1>;
-    if (ntw <= 2) return batch_item_kernel<TC, 2>;
-    return batch_item_kernel<TC, 4>;
+    if (ntw <= 1) return batch_item_kernel<TC, 1, PARTS>;
+    if (ntw <= 2) return batch_item_kernel<TC, 2, PARTS>;
+    return batch_item_kernel<TC, 4, PARTS>;
 }
 
-KernelFn kernel_for(int tc, int ntw, bool persistent) {
+KernelFn kernel_for(int tc, int ntw, bool persistent, int parts) {
     if (persistent) return tc == 32 ? pick_kernel<32>(ntw) : pick_kernel<16>(ntw);
-    return tc == 32 ? pick_item_kernel<32>(ntw) : pick_item_kernel<16>(ntw);
+    if (parts > 1) return tc == 32 ? pick_item_kernel<32, true>(ntw) : pick_item_kernel<16, true>(ntw);
+    return tc == 32 ? pick_item_kernel<32, false>(ntw) : pick_item_kernel<16, false>(ntw);
+}
+
+// Workgroups per item of the per-item kernel.  Few items leave most of the GPU
+// idle and the launch takes as long as the longest tile's chain, most of it
+// emission; the workgroups that share an item repeat its heating and solve and
+// split its emission by rounds of four blocks.  As many as are resident at
+// once (six per CU): 44 tiles of up to 600 wavelengths x 240 grains 114 -> 56 us
+// (five parts), 235 tiles 201 -> 102 (110 with slots for four per CU), 451 tiles
+// 125 -> 78 (89; with 3072 slots 86).
+constexpr int64_t PART_SLOTS = 1536;
+int item_parts(int64_t n_items, int rounds) {
+    if (n_items < 1) return 1;
+    const int64_t p = std::min<int64_t>(PART_SLOTS / n_items, rounds);
+    return (int)std::max<int64_t>(p, 1);
 }
 
 // Autotuner cache: the best candidate per (max-S bucket, mean-NL bucket,
@@ -203,13 +222,15 @@ int forced_candidate(Candidate* c) {
 // Host side shared by dust_batch_create and dust_batch_run: checks every
 // grid's arguments and fills the per-grid launch arguments, cell counts and
 // costs; *sp_max receives the largest padded grain count, *tiles16 the number
-// of 16-cell tiles.
+// of 16-cell tiles, *rounds the most rounds of four emission blocks that a
+// grid has (1 where a grid's inputs share memory with its outputs, so that
+// one workgroup reads and writes a tile).
 dust_status bind_grids(dust_plan* const* plans, int32_t n_grids, const int64_t* n_cells,
                        const float* const* J, const int64_t* ldj, const float* const* m_dust,
                        float* const* T, const int64_t* ldt, float* const* L,
                        const int64_t* ldl, dust_counters* counters, std::vector<GridArgs>* args,
                        std::vector<int64_t>* C, std::vector<double>* cost, int* sp_max,
-                       int64_t* tiles16, int* device) {
+                       int64_t* tiles16, int* rounds, int* device) {
     if (n_grids < 1) return set_error(DUST_EINVAL, "n_grids must be >= 1");
     if (!plans || !n_cells || !J || !ldj || !m_dust || !T || !ldt || !L || !ldl)
         return set_error(DUST_EINVAL, "a per-grid array is NULL");
@@ -220,6 +241,8 @@ dust_status bind_grids(dust_plan* const* plans, int32_t n_grids, const int64_t* 
     cost->assign(n_grids, 0.0);
     *sp_max = 16;
     *tiles16 = 0;
+    *rounds = 1;
+    bool shared = false;
     for (int g = 0; g < n_grids; ++g) {
         const dust_plan* p = plans[g];
         if (!p) return set_error(DUST_EINVAL, "plans[" + std::to_string(g) + "] is NULL");
@@ -237,6 +260,13 @@ dust_status bind_grids(dust_plan* const* plans, int32_t n_grids, const int64_t* 
             if (((uintptr_t)J[g] | (uintptr_t)T[g] | (uintptr_t)L[g] |
                  (uintptr_t)m_dust[g]) & 3u)
                 return set_error(DUST_EINVAL, "buffers must be 4-byte aligned");
+            const int64_t nt = (c - 1) * ldt[g] + p->S, nl = (c - 1) * ldl[g] + p->NL;
+            const int64_t nj = (c - 1) * ldj[g] + p->NL;
+            shared = shared || share_memory(J[g], nj, T[g], nt) ||
+                     share_memory(J[g], nj, L[g], nl) ||
+                     (m_dust[g] && (share_memory(m_dust[g], c, T[g], nt) ||
+                                    share_memory(m_dust[g], c, L[g], nl)));
+            *rounds = std::max(*rounds, ((p->NL + 31) / 32 + 3) / 4);
         }
         (*args)[g] = GridArgs{p->view, c, J[g], ldj[g], m_dust[g], T[g], ldt[g], L[g], ldl[g]};
         (*C)[g] = c;
@@ -244,6 +274,7 @@ dust_status bind_grids(dust_plan* const* plans, int32_t n_grids, const int64_t* 
         *sp_max = std::max(*sp_max, p->Sp);
         *tiles16 += (c + 15) / 16;
     }
+    if (shared) *rounds = 1;
     if (*tiles16 > (int64_t)1 << 30) return set_error(DUST_EUNSUPPORTED, "too many tiles");
     hipError_t e;
     if ((e = hipGetDevice(device)) != hipSuccess) return hip_error(e, "hipGetDevice");
@@ -260,6 +291,7 @@ struct dust_batch {
     int device;
     int n_grids;
     int sp_max;
+    int rounds;
     dust::Candidate cand;
     int64_t n_items_16, n_items_32;
     dust::GridArgs* d_grids;
@@ -292,8 +324,9 @@ hipError_t enqueue(const dust_batch* b, const Candidate& c, hipStream_t st) {
     const int blocks = persistent ? std::max(1, std::min(n_items, b->n_cu * c.per_cu))
                                   : std::max(1, n_items);
     const size_t lds = fused_lds_bytes(c.tc, b->sp_max, Stage<BATCH_KC>::BYTES);
-    hipLaunchKernelGGL(kernel_for(c.tc, c.ntw, persistent), dim3(blocks), dim3(256), lds, st,
-                       (const GridArgs*)b->d_grids, items, n_items, b->d_counter, b->counters);
+    const int parts = persistent ? 1 : item_parts(n_items, b->rounds);
+    hipLaunchKernelGGL(kernel_for(c.tc, c.ntw, persistent, parts), dim3(blocks, parts), dim3(256),
+                       lds, st, (const GridArgs*)b->d_grids, items, n_items, b->d_counter, b->counters);
     return hipGetLastError();
 }
 
@@ -356,8 +389,8 @@ hipError_t scratch_ptr(int dev, void** out) {
 // Copies the work list (host staging) to `d` on `sm` and launches the
 // per-item kernel of the default form over it.
 hipError_t launch_work_list(const std::vector<GridArgs>& args, const std::vector<int2>& items,
-                            int sp_max, const Candidate& c, void* d, dust_counters* counters,
-                            hipStream_t sm) {
+                            int sp_max, int rounds, const Candidate& c, void* d,
+                            dust_counters* counters, hipStream_t sm) {
     const size_t args_bytes = work_list_args_bytes((int)args.size());
     const size_t bytes = args_bytes + sizeof(int2) * items.size();
     std::vector<char> host(bytes);
@@ -367,8 +400,9 @@ hipError_t launch_work_list(const std::vector<GridArgs>& args, const std::vector
     hipError_t e = hipMemcpyAsync(d, host.data(), bytes, hipMemcpyHostToDevice, sm);
     if (e != hipSuccess) return e;
     const size_t lds = fused_lds_bytes(c.tc, sp_max, Stage<BATCH_KC>::BYTES);
-    hipLaunchKernelGGL(kernel_for(c.tc, c.ntw, false), dim3((unsigned)items.size()), dim3(256),
-                       lds, sm, (const GridArgs*)d,
+    const int parts = item_parts((int64_t)items.size(), rounds);
+    hipLaunchKernelGGL(kernel_for(c.tc, c.ntw, false, parts),
+                       dim3((unsigned)items.size(), (unsigned)parts), dim3(256), lds, sm, (const GridArgs*)d,
                        reinterpret_cast<const int2*>((char*)d + args_bytes), (int)items.size(),
                        nullptr, counters);
     return hipGetLastError();
@@ -402,10 +436,10 @@ dust_status dust_batch_create(dust_plan* const* plans, int32_t n_grids, const in
     std::vector<GridArgs> args;
     std::vector<int64_t> C;
     std::vector<double> cost;
-    int sp_max = 16, dev = 0;
+    int sp_max = 16, rounds = 1, dev = 0;
     int64_t total16 = 0;
     dust_status st = bind_grids(plans, n_grids, n_cells, J, ldj, m_dust, T, ldt, L, ldl, counters,
-                                &args, &C, &cost, &sp_max, &total16, &dev);
+                                &args, &C, &cost, &sp_max, &total16, &rounds, &dev);
     if (st != DUST_OK) return st;
     const int max_lds = max_lds_bytes(dev);
     Candidate forced{};
@@ -426,6 +460,7 @@ dust_status dust_batch_create(dust_plan* const* plans, int32_t n_grids, const in
     b->device = dev;
     b->n_grids = n_grids;
     b->sp_max = sp_max;
+    b->rounds = rounds;
     b->n_cu = prop.multiProcessorCount;
     b->counters = counters;
     std::vector<int2> it16 = build_items(C, cost, 16), it32 = build_items(C, cost, 32);
@@ -606,10 +641,10 @@ dust_status dust_batch_run(dust_plan* const* plans, int32_t n_grids, const int64
     std::vector<GridArgs> args;
     std::vector<int64_t> C;
     std::vector<double> cost;
-    int sp_max = 16, dev = 0;
+    int sp_max = 16, rounds = 1, dev = 0;
     int64_t total16 = 0;
     dust_status st = bind_grids(plans, n_grids, n_cells, J, ldj, m_dust, T, ldt, L, ldl, counters,
-                                &args, &C, &cost, &sp_max, &total16, &dev);
+                                &args, &C, &cost, &sp_max, &total16, &rounds, &dev);
     if (st != DUST_OK) return st;
     if (total16 == 0) return DUST_OK;
     const Candidate c = default_candidate(sp_max);
@@ -618,7 +653,7 @@ dust_status dust_batch_run(dust_plan* const* plans, int32_t n_grids, const int64
     void* d = nullptr;
     hipError_t e = hipMallocAsync(&d, work_list_args_bytes(n_grids) + sizeof(int2) * items.size(), sm);
     if (e != hipSuccess) return hip_error(e, "hipMallocAsync (batch work list)");
-    e = launch_work_list(args, items, sp_max, c, d, counters, sm);
+    e = launch_work_list(args, items, sp_max, rounds, c, d, counters, sm);
     const hipError_t ef = hipFreeAsync(d, sm);
     if (e != hipSuccess) return hip_error(e, "batch run");
     return ef == hipSuccess ? DUST_OK : hip_error(ef, "hipFreeAsync (batch work list)");
@@ -646,17 +681,17 @@ dust_status dust_batch_run_noalloc(dust_plan* const* plans, int32_t n_grids,
     std::vector<GridArgs> args;
     std::vector<int64_t> C;
     std::vector<double> cost;
-    int sp_max = 16, dev = 0;
+    int sp_max = 16, rounds = 1, dev = 0;
     int64_t total16 = 0;
     dust_status st = bind_grids(plans, n_grids, n_cells, J, ldj, m_dust, T, ldt, L, ldl, counters,
-                                &args, &C, &cost, &sp_max, &total16, &dev);
+                                &args, &C, &cost, &sp_max, &total16, &rounds, &dev);
     if (st != DUST_OK) return st;
     if (total16 == 0) return DUST_OK;
     void* d = nullptr;
     hipError_t e = scratch_ptr(dev, &d);
     if (e != hipSuccess) return hip_error(e, "hipGetSymbolAddress (work-list array)");
     const Candidate c = default_candidate(sp_max);
-    e = launch_work_list(args, build_items(C, cost, c.tc), sp_max, c, d, counters,
+    e = launch_work_list(args, build_items(C, cost, c.tc), sp_max, rounds, c, d, counters,
                          (hipStream_t)stream);
     return e == hipSuccess ? DUST_OK : hip_error(e, "batch run (no allocation)");
 }

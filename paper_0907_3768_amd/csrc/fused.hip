@@ -217,14 +217,6 @@ bool split_pays(const PlanView& v, int64_t C) {
                                    : C <= 16 * SPLIT_TILES && work >= SPLIT_WORK;
 }
 
-// Whether two arrays of a and b floats share memory.  A call whose input shares
-// memory with an output stays one kernel, which reads a tile's rows before it
-// writes them.
-bool share_memory(const float* x, int64_t a, const float* y, int64_t b) {
-    const uintptr_t px = (uintptr_t)x, py = (uintptr_t)y;
-    return px < py + 4 * (uintptr_t)b && py < px + 4 * (uintptr_t)a;
-}
-
 // The plain fused call as the kernels of its three steps, so that the Newton
 // sums run on scalar weights (a fused tile's 16 cells give each lane its own
 // grain's, through vector loads: 30001 x 251 x 77 1205 us in one kernel).  The

@@ -292,7 +292,8 @@ __device__ __forceinline__ void fused_solve_emit(const PlanView& v, int64_t c0, 
                                                  const float* __restrict__ m,
                                                  float* __restrict__ T, int64_t ldt,
                                                  float* __restrict__ L, int64_t ldl,
-                                                 dust_counters* cnt, float* sH) {
+                                                 dust_counters* cnt, float* sH, int part,
+                                                 int parts) {
     const int n = TC * v.Sp;
     fused_solve<MODE, TC>(v, c0, C, T, ldt, cnt, sH,
                           reinterpret_cast<int*>(reinterpret_cast<char*>(sH) +
@@ -308,7 +309,9 @@ __device__ __forceinline__ void fused_solve_emit(const PlanView& v, int64_t c0, 
     const int NB = (v.NL + LW - 1) / LW;
     if (NB >= 4) {
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-        emit_tile<EMIT_ROWS, TC, TAIL>(v, c0, C, m, L, ldl, sH, sChunk, w, 4, NB);
+        emit_tile<EMIT_ROWS, TC, TAIL>(v, c0, C, m, L, ldl, sH, sChunk, w + 4 * part, 4 * parts,
+                                       NB);
+    } else if (part > 0) {  // (uniform) one part emits all of so few blocks
     } else if (v.NL > 64) {
         emit_cell_part<TC / 2, TC>(v, c0, C, m, L, ldl, sH, sChunk, 2);
     } else {
@@ -338,20 +341,23 @@ __host__ __device__ constexpr int fused_kc(int ntw) { return ntw >= 3 ? 64 : 128
 // One tile of TC cells (TC a multiple of 16) starting at cell c0, J staged in
 // chunks of KC wavelengths; lds holds fused_lds_bytes(TC, Sp,
 // Stage<KC>::BYTES) bytes.  Ends with every thread past its last read of the
-// tile's LDS.
+// tile's LDS.  With parts > 1 as many workgroups take the same tile: each
+// heats and solves it (and stores the same T) and emits the rounds of four
+// blocks part, part + parts, ....
 template <int MODE, int TC, int NTW, bool TAIL, int KC>
 __device__ __forceinline__ void fused_tile(const PlanView& v, int64_t c0, int64_t C,
                                            const float* __restrict__ J, int64_t ldj,
                                            const float* __restrict__ m, float* __restrict__ T,
                                            int64_t ldt, float* __restrict__ L, int64_t ldl,
-                                           dust_counters* cnt, float* lds) {
+                                           dust_counters* cnt, float* lds, int part = 0,
+                                           int parts = 1) {
     float* sH = lds;
     char* sStage = reinterpret_cast<char*>(lds + TC * v.Sp);  // shared, see fused_lds_bytes
 #pragma unroll
     for (int mb = 0; mb < TC / 16; ++mb)
         fused_absorb<MODE, NTW, KC>(v, c0 + 16 * mb, C, J, ldj, sH + 16 * mb * v.Sp, sStage);
     __syncthreads();
-    fused_solve_emit<MODE, TC, TAIL>(v, c0, C, m, T, ldt, L, ldl, cnt, sH);
+    fused_solve_emit<MODE, TC, TAIL>(v, c0, C, m, T, ldt, L, ldl, cnt, sH, part, parts);
     __syncthreads();
 }
 

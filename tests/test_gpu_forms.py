@@ -326,3 +326,43 @@ def test_emission_over_every_form(n_lambda, n_sizes):
     seen = (x < 100.0) & (ref > 1e-25 * em.max())
     assert seen.sum() > 0.5 * x.size
     assert (np.abs(L[seen] / ref[seen] - 1.0) <= tol[seen]).all()
+
+
+@pytest.mark.parametrize("n_cells,n_lambda", [
+    ((1,), 600),               # five workgroups share the only tile
+    ((33, 5, 700), 301),       # three rounds of blocks, fewer in the other grids
+    ((300, 40, 0, 17), 96),    # fewer than four blocks in every grid: no split
+    ((24576,), 250),           # as many tiles as workgroups are resident: no split
+])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_batches_of_few_tiles(n_cells, n_lambda, in_place):
+    """A batch gives the one-kernel fused call's T and SED bit for bit and its
+    counters once, however many workgroups share a tile, also where L is J."""
+    J, m, plans, ref = [], [], [], []
+    cnt1, cnt2, cnt3 = dust.new_counters(), dust.new_counters(), dust.new_counters()
+    for k, n in enumerate(n_cells):
+        nl = max(30, n_lambda - 71 * k)
+        p, j, d = _inputs(max(n, 1), nl, 1 + k % 3, 17 + 16 * k, "mixed", 5 + k, fused_kernels=1)
+        j, d = j[:n], d[:n]
+        for c, f in ((3, 0.0), (4, float("nan")), (9, 1e-14), (16, 1e12)):
+            if c < n:
+                j[c] *= f
+        plans.append(p), J.append(j), m.append(d)
+        ref.append(p.fused(j, d, counters=cnt1))
+    T = [torch.empty_like(r[0]) for r in ref]
+    src = [j.clone() for j in J]
+    L = src if in_place else [torch.empty_like(j) for j in src]
+    b = dust.Batch(plans, src, m, T, L, counters=cnt2)
+    for j, s in zip(J, src):  # the tuner has run on the bound buffers
+        s.copy_(j)
+    cnt2.zero_()
+    b.launch()
+    for again in (False, True):
+        for r, t, l in zip(ref, T, L):
+            assert torch.equal(t.nan_to_num(-3.0), r[0].nan_to_num(-3.0))
+            assert torch.equal(l.nan_to_num(-3.0), r[1].nan_to_num(-3.0))
+        if not again:
+            for j, s in zip(J, src):
+                s.copy_(j)
+            dust.batch_run(plans, src, m, T, L, counters=cnt3)
+    assert cnt1.tolist() == cnt2.tolist() == cnt3.tolist()
