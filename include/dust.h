@@ -106,10 +106,11 @@ typedef struct {
 /* Options; a zero field selects the default shown. */
 typedef struct {
     int32_t mode;      /* dust_mode; default DUST_PLAIN_FP32 */
-    int32_t maxit;     /* plain: Newton iteration cap, default 50.  From 8 on
-                          the first iterations run on the grain's power
-                          tabulated at 128 temperatures (0.9-3000 K); the
-                          last one is always on the exact sum. */
+    int32_t maxit;     /* plain: cap on Newton's iterations on the exact sum,
+                          default 50.  From 8 on up to six more run before
+                          them on the grain's power tabulated at 128
+                          temperatures (0.9-3000 K), unless the start and the
+                          root lie beyond the same end of the table. */
     double tol;        /* plain: stop when |P(T)/H - 1| <= tol, default 1e-5,
                           or when the Newton step taken will leave less */
     int32_t ltab_n;    /* table points per grain: mixed default 1024 (>= 16),

@@ -43,11 +43,14 @@ __device__ __forceinline__ bool newton_accepts(float r, float tol) {
 // Start of the plain Newton: its first iterations, from x (the Eq. 11 guess or
 // a previous solution), on the grain's table of ln P' (the cubic through four
 // of its points) instead of the full sum -- a few loads in place of NL terms.
-// A start that the table already accepts stays.  Stops once the table's
-// residual is below 1e-4 (the step that follows leaves about 1e-9, far below
-// the table's own error), at the table's ends, or after six; *it receives the
-// iterations.  Small iteration caps and a table that is not finite (NaN steps)
-// leave x.
+// Stops once the table's residual is below 1e-4 (the step that follows leaves
+// about 1e-9, far below the table's own error), where a step leaves the table
+// at the end it already stands on, or after six; *it receives the iterations.
+// x itself is returned, with no iteration, where the table cannot better it:
+// the table accepts it, x and the root lie beyond the same end of the table
+// (that end is farther from the root than x may be), six iterations leave a
+// residual above 1/2, the table is not finite (NaN steps), or the iteration
+// cap is small.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float newton_start(const PlanView& v, int s, float lnH, float x,
                                               int* it) {
@@ -55,10 +58,12 @@ __device__ __forceinline__ float newton_start(const PlanView& v, int s, float ln
     if (v.maxit < PLAIN_TABLE_MAXIT) return x;
     const double* __restrict__ f = v.fwd + (int64_t)s * PLAIN_N;
     const float x0 = (float)v.lnTmin, h = (float)v.hstep, hinv = 1.0f / h;
+    constexpr float LAST = PLAIN_N - 1;
     float u = (x - x0) * hinv;  // position in the table, in node spacings
-    const bool inside = u >= 0.0f && u <= (float)(PLAIN_N - 1);
+    const float u0 = u;
+    float r = 0.0f;
     for (int k = 0; k < 6; ++k) {
-        u = fminf(fmaxf(u, 0.0f), (float)(PLAIN_N - 1));
+        u = fminf(fmaxf(u, 0.0f), LAST);
         int j = (int)u - 1;
         j = j < 0 ? 0 : (j > PLAIN_N - 4 ? PLAIN_N - 4 : j);
         // relative to ln H, so that FP32 holds the differences
@@ -66,17 +71,21 @@ __device__ __forceinline__ float newton_start(const PlanView& v, int s, float ln
         const float y2 = (float)(f[j + 2] - (double)lnH), y3 = (float)(f[j + 3] - (double)lnH);
         const float t = u - (float)j, d1 = y1 - y0, d2 = 0.5f * (y2 - 2.0f * y1 + y0);
         const float d3 = (y3 - 3.0f * (y2 - y1) - y0) * (1.0f / 6.0f);
-        const float r = y0 + t * (d1 + (t - 1.0f) * (d2 + (t - 2.0f) * d3));
+        r = y0 + t * (d1 + (t - 1.0f) * (d2 + (t - 2.0f) * d3));
         const float dp = d1 + (2.0f * t - 1.0f) * d2 +
                          (t * (t - 1.0f) + t * (t - 2.0f) + (t - 1.0f) * (t - 2.0f)) * d3;
-        if (k == 0 && inside && newton_accepts(r, v.tol)) break;
+        if (k == 0 && (u0 < 0.0f ? r >= 0.0f
+                                 : (u0 > LAST ? r <= 0.0f : newton_accepts(r, v.tol))))
+            return x;
         const float step = r / dp;
-        if (!(fabsf(step) < 1e6f)) { *it = 0; break; }  // not finite
+        if (!(fabsf(step) < 1e6f)) { *it = 0; return x; }  // not finite
+        const bool leaves = (u <= 0.0f && step > 0.0f) || (u >= LAST && step < 0.0f);
         *it = k + 1;
         u -= step;
-        if (fabsf(r) <= 1e-4f || u < -1.0f || u > (float)PLAIN_N) break;
+        if (fabsf(r) <= 1e-4f || leaves) return x0 + h * fminf(fmaxf(u, 0.0f), LAST);
     }
-    return *it == 0 ? x : x0 + h * fminf(fmaxf(u, 0.0f), (float)(PLAIN_N - 1));
+    if (!(fabsf(r) <= 0.5f)) { *it = 0; return x; }
+    return x0 + h * fminf(fmaxf(u, 0.0f), LAST);
 }
 
 // ln(P / H): of the ratio once it is near 1, since ln P and ln H apart carry the
@@ -95,7 +104,7 @@ __device__ __forceinline__ float newton_residual(float p, float hs, float lnH) {
 // computed.  `kb` is the grain's row of K' c1 lam^-5 (stride 1);
 // `nu` the wavelength table.  A finite tstart > 0 (a previous solution)
 // replaces the guess as the starting point.  Returns T; *evals receives the
-// number of evaluations of the sum.
+// iterations, on the table and on the sum; the cap is on those on the sum.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float solve_newton_f32(const PlanView& v, int s, float hs,
                                                   float tstart, int* evals, dust_counters* cnt) {
@@ -111,9 +120,10 @@ __device__ __forceinline__ float solve_newton_f32(const PlanView& v, int s, floa
     if (hs == 0.0f) return 0.0f;
 
     const float lnH = logf(hs);
-    int it = 0;
+    int it = 0, on_table = 0;
     float lnT = newton_start(
-        v, s, lnH, (tstart > 0.0f && tstart < INFINITY) ? logf(tstart) : guess_lnT(hs, gs), &it);
+        v, s, lnH, (tstart > 0.0f && tstart < INFINITY) ? logf(tstart) : guess_lnT(hs, gs),
+        &on_table);
     float lo = -INFINITY, hi = INFINITY, T = 0.0f;
     bool done = false;
     for (; it < maxit; ++it) {
@@ -175,7 +185,7 @@ __device__ __forceinline__ float solve_newton_f32(const PlanView& v, int s, floa
                                                      : lnT - copysignf(1.0f, r);
         lnT = next;
     }
-    *evals = done ? it + 1 : it;
+    *evals = on_table + (done ? it + 1 : it);
     if (!done && cnt) count(&cnt->n_unconverged);
     return done ? T : expf(lnT);
 }
@@ -266,7 +276,7 @@ __device__ inline float solve_newton_wave(const PlanView& v, int s, bool live, f
     float result = 0.0f;
     bool active = false;
     float lnH = 0.0f, lnT = 0.0f;
-    int nev = 0;  // iterations
+    int nev = 0, on_table = 0;  // iterations on the sum and on the table
     if (live) {
         if (!(hs >= 0.0f) || __builtin_isinf(hs)) {
             if (cnt && q == 0) count(&cnt->n_nonfinite);
@@ -276,7 +286,7 @@ __device__ inline float solve_newton_wave(const PlanView& v, int s, bool live, f
             lnH = logf(hs);
             lnT = newton_start(
                 v, s, lnH,
-                (tstart > 0.0f && tstart < INFINITY) ? logf(tstart) : guess_lnT(hs, gs), &nev);
+                (tstart > 0.0f && tstart < INFINITY) ? logf(tstart) : guess_lnT(hs, gs), &on_table);
         }
     }
     const bool solving = active;
@@ -361,7 +371,7 @@ __device__ inline float solve_newton_wave(const PlanView& v, int s, bool live, f
             }
         }
     }
-    *evals = q == 0 ? nev : 0;
+    *evals = q == 0 ? on_table + nev : 0;
     if (solving && !done) {
         if (cnt && q == 0) count(&cnt->n_unconverged);
         result = expf(lnT);

@@ -28,7 +28,7 @@ constexpr double COLD_RATIO = 3.0;
 // 1e-6, so that one iteration on the full sum is left.
 constexpr int PLAIN_N = 128;
 constexpr double PLAIN_TMIN = 0.9, PLAIN_TMAX = 3000.0;
-// Iteration caps below this count iterations on the full sum only.
+// Iteration caps below this keep Newton off the table.
 constexpr int PLAIN_TABLE_MAXIT = 8;
 
 // Exact SI constants (2019 SI) and the derived radiation constants.

@@ -366,3 +366,46 @@ def test_batches_of_few_tiles(n_cells, n_lambda, in_place):
                 s.copy_(j)
             dust.batch_run(plans, src, m, T, L, counters=cnt3)
     assert cnt1.tolist() == cnt2.tolist() == cnt3.tolist()
+
+
+def _power(g, T):
+    """The right side of Eq. 7 in 64 bits, [len(T), S]."""
+    c1, c2 = 2 * 6.62607015e-34 * 299792458.0 ** 2, 6.62607015e-34 * 299792458.0 / 1.380649e-23
+    B = c1 / g.lam ** 5 / np.expm1(np.minimum(c2 / (g.lam * np.asarray(T)[:, None]), 700.0))
+    return B @ (g.c_abs * g.dlam).T
+
+
+def _bright_grid(n_lambda, n_species, n_sizes, **kw):
+    """A grid whose H stays in FP32's normal range down to a few tenths of a
+    kelvin (the emission weights unchanged)."""
+    g = synth.make_grid(n_lambda, n_species, n_sizes, **kw)
+    scale = 2.0 ** 60
+    g.c_abs, g.weight = g.c_abs * scale, g.weight / scale
+    return g
+
+
+@pytest.mark.parametrize("maxit", [0, 8])
+@pytest.mark.parametrize("factor", [1.001, 0.999])
+def test_plain_warm_starts_beside_the_table(factor, maxit):
+    """A warm start 0.1 % off its root takes a few iterations wherever the root
+    lies: far below the start table (0.9 K), at its ends and far above
+    (3000 K).  Newton in ln T leaves K r^2 / 2 of a residual r <= 0.001 x / 1,
+    x <= 240 (0.2 K at 1000 um): two evaluations of the sum and the accepting
+    one, or three on the table and one.  Bound on T as in test_plain_solve_forms."""
+    g = _bright_grid(250, 1, 7)
+    for T in (0.3, 0.5, 0.85, 0.87, 0.95, 20.0, 2990.0, 3010.0, 3100.0, 5000.0, 1e5):
+        H = np.repeat(_power(g, [T]), 70, axis=0).astype(np.float32)
+        ref = oracle.temperature(H[:1].astype(np.float64), g.lam, g.dlam, g.c_abs, g.size)
+        Hd = torch.as_tensor(H, device="cuda")
+        warm = torch.as_tensor(np.repeat(ref * factor, 70, axis=0).astype(np.float32),
+                               device="cuda")
+        for one_kernel in (0, 1):
+            plan = dust.Plan(g, "plain", maxit=maxit, fused_kernels=one_kernel)
+            cnt = dust.new_counters()
+            if one_kernel:  # the heating as the extra term of cells without a field
+                out, _ = plan.fused(torch.zeros((70, 250), device="cuda"), T=warm.clone(), Q=Hd,
+                                    warm_start=True, counters=cnt)
+            else:
+                out = plan.solve(Hd, T=warm.clone(), warm_start=True, counters=cnt)
+            assert np.abs(out.cpu().numpy() / ref - 1.0).max() <= 5e-6, T
+            assert int(cnt[1]) == 0 and int(cnt[3]) <= (4 if 0.9 < T < 3000 else 3) * H.size, T
