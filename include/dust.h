@@ -111,8 +111,7 @@ typedef struct {
                           them on the grain's power tabulated at 128
                           temperatures (0.9-3000 K), unless the start and the
                           root lie beyond the same end of the table. */
-    double tol;        /* plain: stop when |P(T)/H - 1| <= tol, default 1e-5,
-                          or when the Newton step taken will leave less */
+    double tol;        /* plain: stop when |P(T)/H - 1| <= tol, default 1e-5 */
     int32_t ltab_n;    /* table points per grain: mixed default 1024 (>= 16),
                           table-linear default 2000 (>= 16) */
     int32_t fused_kernels; /* dust_run_fused: 0 = library choice by the call's

@@ -30,15 +30,6 @@ __device__ __forceinline__ void wave_count_add(int64_t* field, int n) {
         atomicAdd(reinterpret_cast<unsigned long long*>(field), (unsigned long long)n);
 }
 
-// Whether the Newton step from a residual r = ln(P/H) ends the iteration: r is
-// within the tolerance, or the residual the step leaves is: r^2 K / 2 with
-// K = y''/y'^2 of y = ln P(ln T), at most 0.1 on the emission of real grains
-// (0.01 typically) and below 1 for any sum of Planck terms that a grid
-// resolves, so r^2 <= tol / 2.5 leaves at most tol / 5 and tol / 50 as a rule.
-__device__ __forceinline__ bool newton_accepts(float r, float tol) {
-    return fabsf(r) <= tol || 2.5f * r * r <= tol;
-}
-
 // ---------------------------------------------------------------------------
 // Start of the plain Newton: its first iterations, from x (the Eq. 11 guess or
 // a previous solution), on the grain's table of ln P' (the cubic through four
@@ -75,7 +66,7 @@ __device__ __forceinline__ float newton_start(const PlanView& v, int s, float ln
         const float dp = d1 + (2.0f * t - 1.0f) * d2 +
                          (t * (t - 1.0f) + t * (t - 2.0f) + (t - 1.0f) * (t - 2.0f)) * d3;
         if (k == 0 && (u0 < 0.0f ? r >= 0.0f
-                                 : (u0 > LAST ? r <= 0.0f : newton_accepts(r, v.tol))))
+                                 : (u0 > LAST ? r <= 0.0f : fabsf(r) <= v.tol)))
             return x;
         const float step = r / dp;
         if (!(fabsf(step) < 1e6f)) { *it = 0; return x; }  // not finite
@@ -100,7 +91,7 @@ __device__ __forceinline__ float newton_residual(float p, float hs, float lnH) {
 // Plain FP32 solve of Eq. 7 for one pair (Section 4.3): Newton's method on
 // ln P(T) = ln H in the variable ln T from the Eq. 11 guess, with a bracket
 // safeguard, the first iterations on the grain's table (newton_start).  Stops
-// when newton_accepts ln(P/H) and then applies the Newton step already
+// when |ln(P/H)| <= tol and then applies the Newton step already
 // computed.  `kb` is the grain's row of K' c1 lam^-5 (stride 1);
 // `nu` the wavelength table.  A finite tstart > 0 (a previous solution)
 // replaces the guess as the starting point.  Returns T; *evals receives the
@@ -175,7 +166,7 @@ __device__ __forceinline__ float solve_newton_f32(const PlanView& v, int s, floa
         const float slope = -0.69314718f * D / P;  // d ln P / d ln T
         if (r < 0.0f) lo = lnT; else hi = lnT;
         float next = lnT - r / slope;
-        if (newton_accepts(r, tol)) {
+        if (fabsf(r) <= tol) {
             T = expf(-r / slope) / invT;  // (ln T itself would round to 2e-7)
             done = true;
             break;
@@ -358,7 +349,7 @@ __device__ inline float solve_newton_wave(const PlanView& v, int s, bool live, f
                 const float slope = 0.69314718f * invT * d / p;  // d ln P / d ln T
                 if (r < 0.0f) lo = lnT; else hi = lnT;
                 float next = lnT - r / slope;
-                if (newton_accepts(r, tol)) {
+                if (fabsf(r) <= tol) {
                     result = expf(-r / slope) / invT;  // (ln T itself would round to 2e-7)
                     done = true;
                     active = false;

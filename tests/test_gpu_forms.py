@@ -409,3 +409,34 @@ def test_plain_warm_starts_beside_the_table(factor, maxit):
                 out = plan.solve(Hd, T=warm.clone(), warm_start=True, counters=cnt)
             assert np.abs(out.cpu().numpy() / ref - 1.0).max() <= 5e-6, T
             assert int(cnt[1]) == 0 and int(cnt[3]) <= (4 if 0.9 < T < 3000 else 3) * H.size, T
+
+
+@pytest.mark.parametrize("n_lambda", [2, 3, 4, 5])
+@pytest.mark.parametrize("tol", [0.0, 1e-3])
+def test_plain_tolerance_on_coarse_grids(n_lambda, tol):
+    """On a few wavelengths ln P is far from a power of T, so only a residual
+    within the tolerance ends the iteration.  Bound on T: what the last step
+    leaves, K tol^2 / 2 of the residual with K <= 30 there (neighbouring
+    wavelengths up to a factor 105 apart: K <= 105 / 4), and rounding: of nu, of 1/T, of their product (6e-8
+    each: T moves by as much), of the exponential, the reciprocal, the sum and
+    the logarithm (4e-7 over a slope of at least 1) and of T and its exponential
+    (1.8e-7): 8e-7.  (Two wavelengths only to 60 K: beyond, the FP32 e^x - 1 at
+    1000 um itself cancels.)"""
+    g = _bright_grid(n_lambda, 1, 6)
+    T = np.geomspace(4.0, 60.0 if n_lambda == 2 else 2000.0, 500)
+    H = _power(g, T).astype(np.float32)
+    H = H[(H > 1e-36).all(axis=1)]
+    ref = oracle.temperature(H.astype(np.float64), g.lam, g.dlam, g.c_abs, g.size)
+    Hd = torch.as_tensor(H, device="cuda")
+    bound = 8e-7 + 15.0 * (tol or 1e-5) ** 2
+    for one_kernel in (0, 1):
+        plan = dust.Plan(g, "plain", tol=tol, fused_kernels=one_kernel)
+        cnt = dust.new_counters()
+        outs = [plan.fused(torch.zeros((len(H), n_lambda), device="cuda"), Q=Hd, counters=cnt)[0],
+                plan.solve(Hd, counters=cnt)]
+        for f in (0.999, 1.001, 1.0003):
+            warm = torch.as_tensor((ref * f).astype(np.float32), device="cuda")
+            outs.append(plan.solve(Hd, T=warm, warm_start=True, counters=cnt))
+        assert int(cnt[1]) == 0
+        for t in outs:
+            assert np.abs(t.cpu().numpy() / ref - 1.0).max() <= bound
