@@ -110,7 +110,8 @@ typedef struct {
                           default 50.  From 8 on up to six more run before
                           them on the grain's power tabulated at 128
                           temperatures (0.9-3000 K), unless the start and the
-                          root lie beyond the same end of the table. */
+                          root lie beyond the same end of the table or the
+                          grid has fewer than five wavelengths. */
     double tol;        /* plain: stop when |P(T)/H - 1| <= tol, default 1e-5 */
     int32_t ltab_n;    /* table points per grain: mixed default 1024 (>= 16),
                           table-linear default 2000 (>= 16) */

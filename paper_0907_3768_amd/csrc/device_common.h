@@ -38,15 +38,17 @@ __device__ __forceinline__ void wave_count_add(int64_t* field, int n) {
 // about 1e-9, far below the table's own error), where a step leaves the table
 // at the end it already stands on, or after six; *it receives the iterations.
 // x itself is returned, with no iteration, where the table cannot better it:
-// the table accepts it, x and the root lie beyond the same end of the table
+// the table's residual is within half the tolerance (its error is a quarter of
+// the default's, and an x that the sum does not accept costs its whole wave a
+// second evaluation), x and the root lie beyond the same end of the table
 // (that end is farther from the root than x may be), six iterations leave a
 // residual above 1/2, the table is not finite (NaN steps), or the iteration
-// cap is small.
+// cap or the number of wavelengths is small.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ float newton_start(const PlanView& v, int s, float lnH, float x,
                                               int* it) {
     *it = 0;
-    if (v.maxit < PLAIN_TABLE_MAXIT) return x;
+    if (v.maxit < PLAIN_TABLE_MAXIT || v.NL < PLAIN_TABLE_NL) return x;
     const double* __restrict__ f = v.fwd + (int64_t)s * PLAIN_N;
     const float x0 = (float)v.lnTmin, h = (float)v.hstep, hinv = 1.0f / h;
     constexpr float LAST = PLAIN_N - 1;
@@ -66,7 +68,7 @@ __device__ __forceinline__ float newton_start(const PlanView& v, int s, float ln
         const float dp = d1 + (2.0f * t - 1.0f) * d2 +
                          (t * (t - 1.0f) + t * (t - 2.0f) + (t - 1.0f) * (t - 2.0f)) * d3;
         if (k == 0 && (u0 < 0.0f ? r >= 0.0f
-                                 : (u0 > LAST ? r <= 0.0f : fabsf(r) <= v.tol)))
+                                 : (u0 > LAST ? r <= 0.0f : fabsf(r) <= 0.5f * v.tol)))
             return x;
         const float step = r / dp;
         if (!(fabsf(step) < 1e6f)) { *it = 0; return x; }  // not finite
