@@ -217,6 +217,22 @@ bool split_pays(const PlanView& v, int64_t C) {
                                    : C <= 16 * SPLIT_TILES && work >= SPLIT_WORK;
 }
 
+// Whether a plain call runs as the kernels of its three steps (launch_heat_newton)
+// instead of one.  The one kernel's Newton sums, on vector loads, cost up to
+// three times those of the solve kernel; the three pay their launches and the
+// trips of H' and T through memory.  One kernel against three: 400000 x 80
+// grains 857 and 927 us at 24 wavelengths, 937 and 950 at 32, 1145 and 1033 at
+// 48; 6000 x 200 80 and 69 us at 24.  Up to 16 grains a tile's solve is one
+// round of its threads: 6000 x 16 18.0 and 23.5 us at 100 wavelengths, 30.8 and
+// 28.4 at 250; 700 x 16 16.3 and 17.1 at 100, 21.2 and 17.4 at 160; 400000 x 16
+// 226 and 223 at 32, 303 and 255 at 64.  Few cells of more than 32 grains have
+// rounds enough at any length: 40 x 80 28.8 and 21.1 us at 24 wavelengths, 700 x
+// 40 18.8 and 17.0.
+bool plain_split_pays(const PlanView& v, int64_t C) {
+    if (v.S <= 16) return v.NL >= (C < 32768 ? 128 : 64);
+    return v.NL >= (v.S > 32 && C <= 4096 ? 8 : 32);
+}
+
 // The plain fused call as the kernels of its three steps, so that the Newton
 // sums run on scalar weights (a fused tile's 16 cells give each lane its own
 // grain's, through vector loads: 30001 x 251 x 77 1205 us in one kernel).  The
@@ -239,7 +255,8 @@ hipError_t launch_fused(const PlanView& v, int64_t C, const float* J, int64_t ld
     if (C == 0) return hipSuccess;
     const int64_t nj = (C - 1) * ldj + v.NL, nt = (C - 1) * ldt + v.S, nl = (C - 1) * ldl + v.NL;
     const int64_t nq = (C - 1) * v.ldq + v.S;
-    if (!one_kernel && !table_mode(v.mode) && (!v.warm || v.S <= v.NL) &&
+    if (!one_kernel && !table_mode(v.mode) && plain_split_pays(v, C) &&
+        (!v.warm || v.S <= v.NL) &&
         !share_memory(J, nj, T, nt) && !share_memory(J, nj, L, nl) &&
         !(v.q && (share_memory(v.q, nq, T, nt) || share_memory(v.q, nq, L, nl)))) {
         const hipError_t e = launch_heat_newton(v, C, J, ldj, T, ldt, L, ldl, cnt, st);

@@ -440,3 +440,30 @@ def test_plain_tolerance_on_coarse_grids(n_lambda, tol):
         assert int(cnt[1]) == 0
         for t in outs:
             assert np.abs(t.cpu().numpy() / ref - 1.0).max() <= bound
+
+
+@pytest.mark.parametrize("n_cells,n_lambda,n_sizes", [
+    (50, 7, 33), (50, 8, 33), (4097, 31, 33), (4097, 32, 33),   # more than 16 grains
+    (300, 127, 16), (300, 128, 16), (32769, 63, 5), (32769, 64, 5),
+])
+def test_plain_fused_forms(n_cells, n_lambda, n_sizes):
+    """The plain fused call beside its lines between one kernel and three, cold
+    and warm-started, against the one-kernel form: the two differ by the order
+    of their sums (T within twice the bound of test_plain_solve_forms) and the
+    events they count are the same."""
+    plan, J, m = _inputs(n_cells, n_lambda, 1, n_sizes, "plain", 31, 1)
+    one = dust.Plan(synth.make_grid(n_lambda, 1, n_sizes), "plain", fused_kernels=1)
+    J[5] = 0.0
+    J[11] *= float("nan")
+    Q = torch.zeros((n_cells, n_sizes), device="cuda")
+    Q[::3] = 1e-21
+    c0, c1 = dust.new_counters(), dust.new_counters()
+    T0, L0 = one.fused(J, m, Q=Q, counters=c0)
+    outs = [plan.fused(J, m, Q=Q, counters=c1),
+            plan.fused(J, m, Q=Q, T=T0 * 1.01, warm_start=True)]
+    for T, L in outs:
+        assert torch.equal(T.isnan(), T0.isnan()) and torch.equal(L.isnan(), L0.isnan())
+        assert torch.allclose(T.nan_to_num(), T0.nan_to_num(), rtol=1e-5, atol=0.0)
+        assert torch.allclose(L.nan_to_num(), L0.nan_to_num(), rtol=2e-3,
+                              atol=float(L0.nan_to_num().max()) * 1e-12)
+    assert c0.tolist()[:3] == c1.tolist()[:3] == [n_sizes, 0, 0]
