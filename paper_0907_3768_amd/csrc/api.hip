@@ -239,7 +239,7 @@ dust_status dust_plan_create(const dust_grid_desc* g, const dust_options* opt, d
             ALLOC(p->d_invf, (size_t)S * (p->M - 1));
             ALLOC(p->d_ylof, S);
             ALLOC(p->d_dyinvf, S);
-            ALLOC(p->d_fwd_c, (size_t)S * COLD_N);
+            ALLOC(p->d_fwd_c, (size_t)S * COLD_P);
             ALLOC(p->d_inv_c, (size_t)S * COLD_M);
             ALLOC(p->d_ylo_c, S);
             ALLOC(p->d_dyinv_c, S);

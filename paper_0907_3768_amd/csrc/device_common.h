@@ -566,6 +566,16 @@ __device__ __forceinline__ double ln_normal_f32(float x) {
     return ((double)e + (double)__builtin_amdgcn_logf(m)) * LN2;
 }
 
+// ln T at u in the interval j whose nodes are g[0] and g[1] (cubic Hermite).
+__device__ __forceinline__ double hermite_lnT(const double2* __restrict__ g, double u, int j) {
+    const double2 g0 = g[0], g1 = g[1];
+    const double t = u - (double)j;
+    const double d = g1.x - g0.x;
+    const double c2 = 3.0 * d - 2.0 * g0.y - g1.y;
+    const double c3 = g0.y + g1.y - 2.0 * d;
+    return g0.x + t * (g0.y + t * (c2 + t * c3));
+}
+
 // Position u = (ln H' - y_0) / dy of ln H' on the grain's FP64 inverse-table
 // grid, and the cubic Hermite of that table at u in node interval j, with T
 // leaving in FP32 as e^head (1 + tail) from the FP32 head of ln T.
@@ -573,34 +583,26 @@ __device__ __forceinline__ double inv_pos_f64(const PlanView& v, int s, float hs
     return (ln_normal_f32(hs) - v.ylo[s]) * v.dyinv[s];
 }
 
-__device__ __forceinline__ float hermite_T(const double2* __restrict__ g, double u, int j) {
-    const double2 g0 = g[0], g1 = g[1];
-    const double t = u - (double)j;
-    const double d = g1.x - g0.x;
-    const double c2 = 3.0 * d - 2.0 * g0.y - g1.y;
-    const double c3 = g0.y + g1.y - 2.0 * d;
-    const double lnT = g0.x + t * (g0.y + t * (c2 + t * c3));
+__device__ __forceinline__ float inv_hermite_f64(const PlanView& v, int s, double u, int j) {
+    const double lnT = hermite_lnT(v.invd + (int64_t)s * v.M + j, u, j);
     const float head = (float)lnT;
     return expf(head) * (1.0f + (float)(lnT - (double)head));
 }
 
-__device__ __forceinline__ float inv_hermite_f64(const PlanView& v, int s, double u, int j) {
-    return hermite_T(v.invd + (int64_t)s * v.M + j, u, j);
-}
-
 // T of a pair the first inverse table does not hold, from the one below its
 // range, and counts it as out of table; false where that one does not hold it
-// either (colder still, above the first, or a table that is not finite: NaN).
-// The exact solve this replaces takes a whole wave about 10 us for a pair at
-// 1000 wavelengths (four FP64 sums): a cold cell held its tile's waves for the
-// time of all the tile's other work.
+// either (colder still, above the first, or a grain without one: NaN).  The
+// logarithm and the exponential are FP64, so that T is rounded once, as the
+// exact solve's.  That solve takes a whole wave about 10 us for a pair at 1000
+// wavelengths (four FP64 sums): a cold cell held its tile's waves for the time
+// of all the tile's other work.
 __device__ __forceinline__ bool cold_lookup(const PlanView& v, int s, float hs, float* T,
                                             dust_counters* cnt) {
     if (hs < 1.17549435e-38f) return false;  // subnormal
-    const double u = (ln_normal_f32(hs) - v.ylo_c[s]) * v.dyinv_c[s];
+    const double u = (ln_f32_value((double)hs, v.lntab) - v.ylo_c[s]) * v.dyinv_c[s];
     if (!(u >= 0.0 && u <= (double)(COLD_M - 1))) return false;
     const int j = (int)u < COLD_M - 2 ? (int)u : COLD_M - 2;
-    *T = hermite_T(v.inv_c + (int64_t)s * COLD_M + j, u, j);
+    *T = (float)exp_f64(hermite_lnT(v.inv_c + (int64_t)s * COLD_M + j, u, j));
     if (cnt) count(&cnt->n_out_of_table);
     return true;
 }

@@ -17,11 +17,14 @@ constexpr int PAD_S = 16;
 
 // The mixed solve's second inverse table, below the first: its forward and
 // inverse nodes, and how far below Tmin it reaches.  ln P is close to linear in
-// 1/T there, so few nodes do: the interpolation error stays below 1e-9 in T on
-// grids that resolve the emission (the first table's own), 1e-8 on an
-// eight-wavelength one.  The synthetic workloads' coldest grains lie at 2.0 K.
-constexpr int COLD_N = 128, COLD_M = 128;
-constexpr double COLD_RATIO = 3.0;
+// 1/T there, so few nodes do: the interpolation error is 3e-10 in T on grids
+// that resolve the emission, 1e-8 on one of eight wavelengths.  COLD_P forward
+// points are tabulated, every other one a node; the points between them measure
+// the finished table, and a grain whose table misses one by more than COLD_TOL
+// (a hundredth of FP32's rounding) has none: its pairs are solved exactly.
+// The synthetic workloads' coldest grains lie at 2.0 K.
+constexpr int COLD_N = 128, COLD_M = 128, COLD_P = 2 * COLD_N - 1;
+constexpr double COLD_RATIO = 3.0, COLD_TOL = 1e-9;
 
 // The plain solve's table: ln P' at PLAIN_N log-spaced T, where Newton's first
 // iterations run.  At 0.064 in ln T its cubic interpolation is good to about
@@ -85,7 +88,7 @@ struct PlanView {
     // mixed: the same below the table's range, COLD_M nodes for T from
     // Tmin / COLD_RATIO to Tmin (a pair there is an O(1) lookup too)
     const double* ylo_c;   // [S] first node's y
-    const double* dyinv_c; // [S] 1 / node spacing
+    const double* dyinv_c; // [S] 1 / node spacing (NaN: no table)
     const double2* inv_c;  // [S][COLD_M]
     int f32_lookup;        // mixed: FP32 inverse-table lookup instead of the FP64 one
     int polish;            // mixed: FP64 Newton polish on the forward table after the lookup
@@ -179,7 +182,7 @@ struct RefreshJob {
     double *fwd_c, *ylo_c, *dyinv_c;
     double2* inv_c;
     double lnTmin_c, hstep_c;  // ln T of the forward nodes below Tmin
-    int Nc;                    // their number (0: no such table)
+    int Nc;                    // their number (0: no such table), every other one a node
     int* kidx;
     double2* invd;
     float2* invf;

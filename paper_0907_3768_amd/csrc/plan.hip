@@ -254,18 +254,21 @@ __device__ __forceinline__ void kidx_body(const RefreshJob& job, int bx, int by,
 }
 
 // ln T at y (>= f[0]) by Newton on the piecewise cubic through a forward table
-// f[0..N-1] at ln T = lnT0 + k h, and d ln T / dy there.
+// of N values f[0], f[ST], ... at ln T = lnT0 + k h, and d ln T / dy there.
+template <int ST>
 __device__ __forceinline__ double2 inverse_node(const double* __restrict__ f, int N, double lnT0,
                                                 double h, double y) {
     // largest k in [0, N-2] with f_k <= y
     int lo = 0, hi = N - 2;
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (f[mid] <= y) lo = mid; else hi = mid - 1;
+        if (f[ST * mid] <= y) lo = mid; else hi = mid - 1;
     }
     const int j0 = stencil_start(lo, N);
-    const double a0 = f[j0], a1 = f[j0 + 1], a2 = f[j0 + 2], a3 = f[j0 + 3];
-    double x = lo - j0 + ((f[lo + 1] > f[lo]) ? (y - f[lo]) / (f[lo + 1] - f[lo]) : 0.0);
+    const double a0 = f[ST * j0], a1 = f[ST * (j0 + 1)], a2 = f[ST * (j0 + 2)],
+                 a3 = f[ST * (j0 + 3)];
+    const double fl = f[ST * lo], fh = f[ST * (lo + 1)];
+    double x = lo - j0 + (fh > fl ? (y - fl) / (fh - fl) : 0.0);
     double dp = 1.0;
     for (int it = 0; it < 4; ++it) {
         const double p = cubic4(x, a0, a1, a2, a3, &dp);
@@ -276,43 +279,62 @@ __device__ __forceinline__ double2 inverse_node(const double* __restrict__ f, in
 }
 
 // One thread per (grain, inverse node): ln T at y_j = ylo + j dy and
-// dy * d ln T / dy.  The last block column makes the table below the range.
+// dy * d ln T / dy.
 __device__ __forceinline__ void inv_body(const RefreshJob& job, int bx, int by, double* sF) {
     const PlanView& v = job.v;
-    const int s = by;
-    const bool cold = bx == job.gx[3] - 1;
-    const int j = cold ? threadIdx.x : bx * blockDim.x + threadIdx.x;
-    const int M = cold ? COLD_M : v.M, N = cold ? job.Nc : v.N;
-    const double* f = stage_row<false>((cold ? job.fwd_c : job.fwd) + (int64_t)s * N, N, sF);
+    const int s = by, M = v.M, N = v.N;
+    const int j = bx * blockDim.x + threadIdx.x;
+    const double* f = stage_row<false>(job.fwd + (int64_t)s * N, N, sF);
     if (j >= M) return;
     const double y0 = f[0], y1 = f[N - 1];
     const double dinv = (M - 1) / (y1 - y0);
     if (j == 0) {
-        if (cold) {
-            job.ylo_c[s] = y0;
-            job.dyinv_c[s] = dinv;
-        } else {
-            job.ylo[s] = y0;
-            job.yhi[s] = y1;
-            job.dyinv[s] = dinv;
-            job.ylof[s] = (float)y0;
-            job.dyinvf[s] = (float)dinv;
-        }
+        job.ylo[s] = y0;
+        job.yhi[s] = y1;
+        job.dyinv[s] = dinv;
+        job.ylof[s] = (float)y0;
+        job.dyinvf[s] = (float)dinv;
     }
     const double yj = (j == M - 1) ? y1 : y0 + j / dinv;
-    double2 node = inverse_node(f, N, cold ? job.lnTmin_c : v.lnTmin,
-                                cold ? job.hstep_c : v.hstep, yj);
+    double2 node = inverse_node<1>(f, N, v.lnTmin, v.hstep, yj);
     node.y /= dinv;  // the derivative, scaled by the node spacing dy = 1 / dinv
-    if (cold) {
-        job.inv_c[(int64_t)s * M + j] = node;
-        return;
-    }
     job.invd[(int64_t)s * M + j] = node;
     // the FP32 entries of the two intervals this node bounds
     const float2 nf = make_float2((float)node.x, (float)node.y);
     float2* row = job.invf + (int64_t)s * (M - 1) * 2;
     if (j < M - 1) row[2 * j] = nf;
     if (j > 0) row[2 * (j - 1) + 1] = nf;
+}
+
+// The same below the table's range, by one workgroup per grain: the nodes from
+// every other forward point, then the table's ln T at the points between.
+__device__ __forceinline__ void cold_inv_body(const RefreshJob& job, int s, double* sF) {
+    static_assert(COLD_P + 2 * COLD_M <= FWD_LDS, "forward points and nodes in LDS");
+    const int j = threadIdx.x;
+    const double* f = stage_row<false>(job.fwd_c + (int64_t)s * COLD_P, COLD_P, sF);
+    double2* nodes = reinterpret_cast<double2*>(sF + COLD_P + 1);
+    const double y0 = f[0], y1 = f[COLD_P - 1];
+    const double dinv = (COLD_M - 1) / (y1 - y0);
+    if (j < COLD_M) {
+        const double yj = (j == COLD_M - 1) ? y1 : y0 + j / dinv;
+        double2 node = inverse_node<2>(f, COLD_N, job.lnTmin_c, 2.0 * job.hstep_c, yj);
+        node.y /= dinv;
+        nodes[j] = node;
+        job.inv_c[(int64_t)s * COLD_M + j] = node;
+    }
+    __syncthreads();
+    bool good = true;  // (a table that is not finite fails)
+    if (j < COLD_N - 1) {
+        const int k = 2 * j + 1;
+        const double u = fmin(fmax((f[k] - y0) * dinv, 0.0), (double)(COLD_M - 1));
+        const int i = (int)u < COLD_M - 2 ? (int)u : COLD_M - 2;
+        good = fabs(hermite_lnT(nodes + i, u, i) - (job.lnTmin_c + k * job.hstep_c)) <= COLD_TOL;
+    }
+    const int bad = __syncthreads_or(!good);
+    if (j == 0) {
+        job.ylo_c[s] = y0;
+        job.dyinv_c[s] = bad ? __builtin_nan("") : dinv;
+    }
 }
 
 // The stages of a refresh (0 prep, 2 table product, 3 inverse table or search
@@ -325,8 +347,9 @@ __device__ __forceinline__ void refresh_stage(const RefreshJob& j, int bx, int b
     } else if constexpr (STAGE == 2) {
         product_body(j, bx, by);
     } else {
-        __shared__ double sF[FWD_LDS];
+        __shared__ __align__(16) double sF[FWD_LDS];
         if (j.v.mode == DUST_TABLE_LINEAR) kidx_body(j, bx, by, sF);
+        else if (bx == j.gx[3] - 1) cold_inv_body(j, by, sF);
         else inv_body(j, bx, by, sF);
     }
 }
@@ -398,11 +421,11 @@ void make_refresh_job(const dust_plan* p, RefreshJob* j) {
     j->ylof = p->d_ylof; j->dyinvf = p->d_dyinvf;
     const bool tab = table_mode(v.mode);
     if (mixed_mode(v.mode)) {
-        j->Nc = COLD_N;
+        j->Nc = COLD_P;
         j->fwd_c = p->d_fwd_c; j->ylo_c = p->d_ylo_c; j->dyinv_c = p->d_dyinv_c;
         j->inv_c = p->d_inv_c;
         j->lnTmin_c = v.lnTmin - log(COLD_RATIO);
-        j->hstep_c = log(COLD_RATIO) / (COLD_N - 1);
+        j->hstep_c = log(COLD_RATIO) / (COLD_P - 1);
     }
     j->gx[0] = (v.NLp + 255) / 256;  j->gy[0] = v.Sp;
     j->gx[1] = 1;                    j->gy[1] = 0;

@@ -467,3 +467,30 @@ def test_plain_fused_forms(n_cells, n_lambda, n_sizes):
         assert torch.allclose(L.nan_to_num(), L0.nan_to_num(), rtol=2e-3,
                               atol=float(L0.nan_to_num().max()) * 1e-12)
     assert c0.tolist()[:3] == c1.tolist()[:3] == [n_sizes, 0, 0]
+
+
+@pytest.mark.parametrize("lookup", ["default", "f32", "polish"])
+@pytest.mark.parametrize("n_lambda,hi_um,tmin", [(2, 1000.0, 2.7), (3, 1000.0, 60.0),
+                                                 (8, 1000.0, 2.7), (8, 1000.0, 100.0),
+                                                 (30, 1000.0, 2.7), (250, 100.0, 10.0),
+                                                 (600, 1000.0, 2.7)])
+def test_temperatures_below_the_table_are_rounded_once(n_lambda, hi_um, tmin, lookup):
+    """Below the table T is the FP64 result rounded to FP32 on every grid, by
+    the second table (or the exact solve where a grain has none) and below it,
+    in every path.  Bound, given the heating: half a unit of FP32 (6.0e-8) and
+    1e-9, doubled, of the second table and of the exact solve's last step."""
+    g = _bright_grid(n_lambda, 1, 5, hi_um=hi_um)
+    T = np.geomspace(0.999 * tmin, tmin / 4.0, 700)
+    H = np.maximum(_power(g, T), 0.0).astype(np.float32)
+    H = H[(H > 1e-36).all(axis=1)]
+    assert len(H) > 400
+    ref = oracle.temperature(H.astype(np.float64), g.lam, g.dlam, g.c_abs, g.size)
+    Hd = torch.as_tensor(H, device="cuda")
+    J = torch.zeros((len(H), n_lambda), device="cuda")
+    for fused_kernels in (0, 1, 2):
+        plan = dust.Plan(g, "mixed", ltab_tmin=tmin, f32_lookup=lookup == "f32",
+                         newton_polish=lookup == "polish", fused_kernels=fused_kernels)
+        cnt = dust.new_counters()
+        for out in (plan.solve(Hd, counters=cnt), plan.fused(J, Q=Hd, counters=cnt)[0]):
+            assert np.abs(out.cpu().numpy() / ref - 1.0).max() <= 6.0e-8 + 2e-9
+        assert cnt.tolist()[:3] == [0, 0, 2 * H.size]
