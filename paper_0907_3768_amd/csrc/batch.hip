@@ -223,8 +223,8 @@ int forced_candidate(Candidate* c) {
 // grid's arguments and fills the per-grid launch arguments, cell counts and
 // costs; *sp_max receives the largest padded grain count, *tiles16 the number
 // of 16-cell tiles, *rounds the most rounds of four emission blocks that a
-// grid has (1 where a grid's inputs share memory with its outputs, so that
-// one workgroup reads and writes a tile).
+// grid has (1 where a grid's inputs share memory with its outputs, or its T with
+// its L, so that one workgroup reads and writes a tile).
 dust_status bind_grids(dust_plan* const* plans, int32_t n_grids, const int64_t* n_cells,
                        const float* const* J, const int64_t* ldj, const float* const* m_dust,
                        float* const* T, const int64_t* ldt, float* const* L,
@@ -263,7 +263,7 @@ dust_status bind_grids(dust_plan* const* plans, int32_t n_grids, const int64_t* 
             const int64_t nt = (c - 1) * ldt[g] + p->S, nl = (c - 1) * ldl[g] + p->NL;
             const int64_t nj = (c - 1) * ldj[g] + p->NL;
             shared = shared || share_memory(J[g], nj, T[g], nt) ||
-                     share_memory(J[g], nj, L[g], nl) ||
+                     share_memory(J[g], nj, L[g], nl) || share_memory(T[g], nt, L[g], nl) ||
                      (m_dust[g] && (share_memory(m_dust[g], c, T[g], nt) ||
                                     share_memory(m_dust[g], c, L[g], nl)));
             *rounds = std::max(*rounds, ((p->NL + 31) / 32 + 3) / 4);

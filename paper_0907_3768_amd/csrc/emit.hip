@@ -52,16 +52,19 @@ __global__ __launch_bounds__(256) void emit_kernel(PlanView v, int64_t C,
     }
 }
 
-template <int TC>
-hipError_t launch_emit_tc(const PlanView& v, int64_t C, const float* T, int64_t ldt,
-                          const float* m, float* L, int64_t ldl, hipStream_t st) {
-    const int64_t tiles = (C + TC - 1) / TC;
-    const int NB = (v.NL + 31) / 32;
-    // Columns: as few as give EMIT_WORKGROUPS workgroups (a column refills the
-    // tile's 1/T), each of whole rounds of the four waves.
+// Blocks per column: as few columns as give EMIT_WORKGROUPS workgroups (a column
+// refills the tile's 1/T), each of whole rounds of the four waves.
+int column_blocks(int64_t tiles, int NB) {
     const int64_t want = (EMIT_WORKGROUPS + tiles - 1) / tiles;
     const int cols = want < NB ? (int)want : NB;
-    const int bpc = ((NB + cols - 1) / cols + 3) / 4 * 4;
+    return ((NB + cols - 1) / cols + 3) / 4 * 4;
+}
+
+template <int TC>
+hipError_t launch_emit_tc(const PlanView& v, int64_t C, const float* T, int64_t ldt,
+                          const float* m, float* L, int64_t ldl, int bpc, hipStream_t st) {
+    const int64_t tiles = (C + TC - 1) / TC;
+    const int NB = (v.NL + 31) / 32;
     const dim3 grid((unsigned)tiles, (unsigned)((NB + bpc - 1) / bpc));
     const size_t lds = emit_lds_bytes(TC, v.Sp);
     if (((v.S + EMIT_GROUP - 1) / EMIT_GROUP) & 1)
@@ -94,11 +97,16 @@ hipError_t launch_emit(const PlanView& v, int64_t C, const float* T, int64_t ldt
     if (C == 0) return hipSuccess;
     const int NB = (v.NL + 31) / 32;
     const int64_t tasks = (C + 15) / 16 * NB;
+    // T and L in one piece of memory (L over T, or rows side by side): a tile's
+    // 256 wavelengths belong to one workgroup, which has read the tile's T
+    // before it writes them
+    if (share_memory(T, (C - 1) * ldt + v.S, L, (C - 1) * ldl + v.NL))
+        return launch_emit_tc<16>(v, C, T, ldt, m, L, ldl, 256 / 32, st);
     if (NB >= 4 && v.S > 32 && tasks <= EMIT_SLOTS * 3 / 2)
-        return launch_emit_tc<4>(v, C, T, ldt, m, L, ldl, st);
+        return launch_emit_tc<4>(v, C, T, ldt, m, L, ldl, column_blocks((C + 3) / 4, NB), st);
     if (NB >= 4 && v.S > 32 && tasks <= EMIT_SLOTS * 12)
-        return launch_emit_tc<8>(v, C, T, ldt, m, L, ldl, st);
-    return launch_emit_tc<16>(v, C, T, ldt, m, L, ldl, st);
+        return launch_emit_tc<8>(v, C, T, ldt, m, L, ldl, column_blocks((C + 7) / 8, NB), st);
+    return launch_emit_tc<16>(v, C, T, ldt, m, L, ldl, column_blocks((C + 15) / 16, NB), st);
 }
 
 }  // namespace dust

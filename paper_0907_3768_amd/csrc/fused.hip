@@ -255,6 +255,9 @@ hipError_t launch_fused(const PlanView& v, int64_t C, const float* J, int64_t ld
     if (C == 0) return hipSuccess;
     const int64_t nj = (C - 1) * ldj + v.NL, nt = (C - 1) * ldt + v.S, nl = (C - 1) * ldl + v.NL;
     const int64_t nq = (C - 1) * v.ldq + v.S;
+    // (the one kernel stores a tile's T before its L, which stays where the two
+    // share memory)
+    one_kernel = one_kernel || share_memory(T, nt, L, nl);
     if (!one_kernel && !table_mode(v.mode) && plain_split_pays(v, C) &&
         (!v.warm || v.S <= v.NL) &&
         !share_memory(J, nj, T, nt) && !share_memory(J, nj, L, nl) &&

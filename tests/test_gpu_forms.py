@@ -494,3 +494,44 @@ def test_temperatures_below_the_table_are_rounded_once(n_lambda, hi_um, tmin, lo
         for out in (plan.solve(Hd, counters=cnt), plan.fused(J, Q=Hd, counters=cnt)[0]):
             assert np.abs(out.cpu().numpy() / ref - 1.0).max() <= 6.0e-8 + 2e-9
         assert cnt.tolist()[:3] == [0, 0, 2 * H.size]
+
+
+@pytest.mark.parametrize("mode", ["plain", "mixed", "table"])
+@pytest.mark.parametrize("n_cells,n_lambda,n_sizes", [
+    (1, 250, 40),       # two columns of blocks, or one
+    (70, 250, 80),      # four-cell tiles
+    (3000, 130, 40),    # eight-cell tiles
+    (900, 100, 20),     # 16-cell tiles
+])
+def test_sed_over_the_temperatures(n_cells, n_lambda, n_sizes, mode):
+    """L may take the memory of T (rows of one length, T in the first columns):
+    an emission of up to 256 wavelengths, a fused call and a batch, against the
+    same calls on memory of their own, bit for bit."""
+    plan, J, m = _inputs(n_cells, n_lambda, 1, n_sizes, mode, 17)
+    T = plan.solve(plan.absorb(J))
+    buf = torch.empty((n_cells, n_lambda), device="cuda")
+    for _ in range(3):
+        buf.fill_(-1.0)
+        buf[:, :n_sizes] = T
+        plan.emit(buf, m, buf)
+        assert torch.equal(buf, plan.emit(T, m))
+    for fused_kernels in (1, 0):
+        p = dust.Plan(synth.make_grid(n_lambda, 1, n_sizes), mode, fused_kernels=fused_kernels)
+        if fused_kernels:
+            _, L = p.fused(J, m)  # (the one-kernel form, which memory in common takes)
+        buf.fill_(-1.0)
+        p.fused(J, m, buf, buf)
+        assert torch.equal(buf, L)
+    if mode == "plain":  # T holds the start temperatures too
+        buf[:, :n_sizes] = T * 1.01
+        plan.fused(J, m, buf, buf, warm_start=True)
+        assert torch.allclose(buf, L, rtol=2e-3, atol=float(L.max()) * 1e-12)
+    if mode == "mixed":
+        for _ in range(2):
+            buf.fill_(-1.0)
+            dust.batch_run([plan], [J], [m], [buf], [buf])
+            assert torch.equal(buf, L)
+        b = dust.Batch([plan], [J], [m], [buf], [buf])
+        buf.fill_(-1.0)
+        b.launch()
+        assert torch.equal(buf, L)
