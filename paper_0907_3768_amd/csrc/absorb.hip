@@ -3,7 +3,8 @@
 //
 //   DUST_PLAIN_FP32: v_mfma_f32_16x16x4_f32 (exact FP32 products), one wave
 //                    per block of (16 cells, 16 grains) tiles straight from
-//                    device memory (heat_kernel).
+//                    device memory (heat_kernel), or a workgroup per 16 cells
+//                    (absorb_tile_kernel: H over J).
 //   DUST_MIXED, DUST_TABLE_LINEAR:
 //                    v_mfma_f32_16x16x32_bf16 on hi+lo splits,
 //                    J_hi K_hi + J_hi K_lo + J_lo K_hi, FP32 accumulation.
@@ -13,6 +14,7 @@
 //                    LDS (absorb_dl_kernel: loaded straight into LDS, for J
 //                    rows aligned to 16 bytes; absorb_gemm_kernel: through
 //                    registers).
+#include "fused_body.h"
 #include "wave_heat.h"
 
 namespace dust {
@@ -463,6 +465,48 @@ __global__ __launch_bounds__(64 * GW) __attribute__((amdgpu_waves_per_eu(GW / 4,
     }
 }
 
+// ---------------------------------------------------------------------------
+// Heating of 16 cells for every grain by one workgroup, as in the fused kernel
+// (fused_absorb: J through LDS in chunks, the products in the same order), H
+// from LDS with stores along its rows.  The workgroup has read its cells' J
+// before it writes their H, so H may take the memory of J.
+// ---------------------------------------------------------------------------
+template <int MODE, int NTW>
+__global__ __launch_bounds__(256) void absorb_tile_kernel(PlanView v, int64_t C, const float* J,
+                                                          int64_t ldj, float* H, int64_t ldh,
+                                                          bool scaled) {
+    extern __shared__ float lds[];  // sH [16][Sp], then the J staging buffers
+    const int64_t c0 = (int64_t)blockIdx.x * FUSED_TC;
+    fused_absorb<MODE, NTW>(v, c0, C, J, ldj, lds, reinterpret_cast<char*>(lds + FUSED_TC * v.Sp));
+    __syncthreads();
+    for (int i = threadIdx.x; i < FUSED_TC * v.Sp; i += 256) {
+        const int cc = i / v.Sp, s = i - cc * v.Sp;
+        if (s < v.S && c0 + cc < C)
+            H[(c0 + cc) * ldh + s] = lds[i] * (scaled ? 1.0f : v.hinv[s]);
+    }
+}
+
+template <int MODE>
+hipError_t launch_tile(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
+                       int64_t ldh, bool scaled, hipStream_t st) {
+    const size_t lds = sizeof(float) * FUSED_TC * v.Sp + STAGE_BYTES;
+    const dim3 grid((unsigned)((C + FUSED_TC - 1) / FUSED_TC));
+    const int ntw = (v.Sp / 16 + 3) / 4;
+    if (ntw <= 1)
+        hipLaunchKernelGGL((absorb_tile_kernel<MODE, 1>), grid, dim3(256), lds, st, v, C, J, ldj, H,
+                           ldh, scaled);
+    else if (ntw <= 2)
+        hipLaunchKernelGGL((absorb_tile_kernel<MODE, 2>), grid, dim3(256), lds, st, v, C, J, ldj, H,
+                           ldh, scaled);
+    else if (ntw <= 3)
+        hipLaunchKernelGGL((absorb_tile_kernel<MODE, 3>), grid, dim3(256), lds, st, v, C, J, ldj, H,
+                           ldh, scaled);
+    else  // (several passes above 16 tiles)
+        hipLaunchKernelGGL((absorb_tile_kernel<MODE, 4>), grid, dim3(256), lds, st, v, C, J, ldj, H,
+                           ldh, scaled);
+    return hipGetLastError();
+}
+
 // Heating by one wave per 16 MB cells x 16 NB grains (heat_block), straight
 // from device memory to H; scaled: H' instead of H.
 template <bool BF, bool ALIGNED, int MB, int NB, int U>
@@ -618,10 +662,19 @@ bool wave_heating_pays(const PlanView& v, int64_t C, const float* J, int64_t ldj
 hipError_t launch_absorb(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
                          int64_t ldh, hipStream_t st) {
     if (C == 0) return hipSuccess;
-    if (!table_mode(v.mode)) return launch_heat_sized<false>(v, C, J, ldj, H, ldh, false, st);
-    return wave_heating_pays(v, C, J, ldj)
-               ? launch_heat_sized<true>(v, C, J, ldj, H, ldh, false, st)
-               : launch_bf16(v, C, J, ldj, H, ldh, st);
+    const bool table = table_mode(v.mode);
+    const bool wave = table && wave_heating_pays(v, C, J, ldj);
+    if (share_memory(J, (C - 1) * ldj + v.NL, H, (C - 1) * ldh + v.S)) {
+        // H over J: one workgroup for a cell's rows, which has read them before
+        // it writes (the direct-load kernel reads a ragged last k-step late)
+        if (table && !wave && v.Sp <= 16 * G_NT && v.S <= v.NL / 32 * 32)
+            return launch_bf16(v, C, J, ldj, H, ldh, st);
+        return table ? launch_tile<DUST_MIXED>(v, C, J, ldj, H, ldh, false, st)
+                     : launch_tile<DUST_PLAIN_FP32>(v, C, J, ldj, H, ldh, false, st);
+    }
+    if (!table) return launch_heat_sized<false>(v, C, J, ldj, H, ldh, false, st);
+    return wave ? launch_heat_sized<true>(v, C, J, ldj, H, ldh, false, st)
+                : launch_bf16(v, C, J, ldj, H, ldh, st);
 }
 
 hipError_t launch_absorb_scaled(const PlanView& v, int64_t C, const float* J, int64_t ldj,

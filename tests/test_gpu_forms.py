@@ -535,3 +535,24 @@ def test_sed_over_the_temperatures(n_cells, n_lambda, n_sizes, mode):
         buf.fill_(-1.0)
         b.launch()
         assert torch.equal(buf, L)
+
+
+@pytest.mark.parametrize("mode", ["plain", "mixed"])
+@pytest.mark.parametrize("n_cells,n_lambda,n_sizes,pad", [
+    (1, 64, 40, 0),
+    (500, 300, 240, 0),       # many grain tiles of few cells
+    (40000, 250, 80, 0),      # 256-cell blocks, J rows aligned
+    (40000, 161, 130, 2),     # and not
+    (40000, 100, 98, 0),      # grains into the ragged last k-step
+    (9000, 320, 300, 1),      # more grains than one pass of the blocked kernel
+])
+def test_heating_over_the_field(n_cells, n_lambda, n_sizes, pad, mode):
+    """H may take the memory of J (the first columns of its rows): the same
+    bits as in memory of its own."""
+    plan, J, _ = _inputs(n_cells, n_lambda, 1, n_sizes, mode, 19, pad)
+    H = plan.absorb(J)
+    for _ in range(3):
+        buf = torch.empty((n_cells, n_lambda + pad), device="cuda")[:, :n_lambda]
+        buf.copy_(J)
+        plan.absorb(buf, buf)
+        assert torch.equal(buf[:, :n_sizes], H) and torch.equal(buf[:, n_sizes:], J[:, n_sizes:])
