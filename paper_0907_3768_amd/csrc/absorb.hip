@@ -4,7 +4,7 @@
 //   DUST_PLAIN_FP32: v_mfma_f32_16x16x4_f32 (exact FP32 products), one wave
 //                    per block of (16 cells, 16 grains) tiles straight from
 //                    device memory (heat_kernel), or a workgroup per 16 cells
-//                    (absorb_tile_kernel: H over J).
+//                    (absorb_tile_kernel: short rows, H over J).
 //   DUST_MIXED, DUST_TABLE_LINEAR:
 //                    v_mfma_f32_16x16x32_bf16 on hi+lo splits,
 //                    J_hi K_hi + J_hi K_lo + J_lo K_hi, FP32 accumulation.
@@ -649,12 +649,33 @@ hipError_t launch_bf16(const PlanView& v, int64_t C, const float* J, int64_t ldj
 // 968 x 81, 128: 41.8 against 45.6), and where J's rows start on odd floats,
 // which the staged kernel loads one by one, unless many grains make it worth
 // that (100003 x 301 x 45 67.6 -> 34.5 us, 1000000 x 251 x 80 607 -> 444, 262144
-// x 501 x 128 323 -> 297; 262144 x 1001 x 240 677 against 801), or on a device
-// that cannot give one workgroup the blocked kernel's 144 KB of LDS.
+// x 501 x 128 323 -> 297; 36000 x 250 x 130 34.5 -> 26.8, but 58000 x 250 x 130
+// 36.4 against 39.8, x 240 41.2 against 51.6) or there is little to load
+// (3000000 x 80 grains, 12 wavelengths 319 us against 451, 40 426 against 492, 64
+// 638 against 613); or on a device that cannot give one workgroup the blocked
+// kernel's 144 KB of LDS.
 bool wave_heating_pays(const PlanView& v, int64_t C, const float* J, int64_t ldj) {
     const int64_t blocks = (C + 255) / 256;
+    const int tiles = v.Sp / 16;
     const bool odd = ((uintptr_t)J & 7u) != 0 || (ldj & 1) != 0;
-    return !gemm_fits() || blocks < 112 || (odd && (v.Sp / 16 <= 8 || blocks < 256));
+    if (!gemm_fits()) return true;
+    if (!odd || tiles == 1) return blocks < 112 || odd;
+    if (tiles <= 8) return v.NL >= 48 || blocks < 64;
+    return blocks < 112 || (v.NL >= 48 && blocks * tiles < 1600);
+}
+
+// FP32 heating.  On short rows the stores of H bind, and where H is far larger
+// than the caches a tile's stores along its rows beat the waves' 64-byte pieces
+// (3000000 x 12 x 240 1653 us against 1817, x 80 594 against 620; 400000 x 12 x
+// 80 70 against 58); so they do where blocks of 2 x heat_width leave a few waves
+// per CU (50000 x 40 x 80 15.5 against 16.7, x 250 37.2 against 35.2).
+hipError_t launch_f32(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* H,
+                      int64_t ldh, bool scaled, hipStream_t st) {
+    const int64_t waves = (C + 15) / 16 * (v.Sp / 16);
+    if ((v.NL < 32 && C * v.S >= 90000000) ||
+        (v.NL >= 16 && v.NL <= 64 && waves > 6144 && waves <= 16384))
+        return launch_tile<DUST_PLAIN_FP32>(v, C, J, ldj, H, ldh, scaled, st);
+    return launch_heat_sized<false>(v, C, J, ldj, H, ldh, scaled, st);
 }
 
 }  // namespace
@@ -672,7 +693,7 @@ hipError_t launch_absorb(const PlanView& v, int64_t C, const float* J, int64_t l
         return table ? launch_tile<DUST_MIXED>(v, C, J, ldj, H, ldh, false, st)
                      : launch_tile<DUST_PLAIN_FP32>(v, C, J, ldj, H, ldh, false, st);
     }
-    if (!table) return launch_heat_sized<false>(v, C, J, ldj, H, ldh, false, st);
+    if (!table) return launch_f32(v, C, J, ldj, H, ldh, false, st);
     return wave ? launch_heat_sized<true>(v, C, J, ldj, H, ldh, false, st)
                 : launch_bf16(v, C, J, ldj, H, ldh, st);
 }
@@ -680,7 +701,7 @@ hipError_t launch_absorb(const PlanView& v, int64_t C, const float* J, int64_t l
 hipError_t launch_absorb_scaled(const PlanView& v, int64_t C, const float* J, int64_t ldj,
                                 float* H, int64_t ldh, hipStream_t st) {
     if (C == 0) return hipSuccess;
-    return launch_heat_sized<false>(v, C, J, ldj, H, ldh, true, st);
+    return launch_f32(v, C, J, ldj, H, ldh, true, st);
 }
 
 }  // namespace dust

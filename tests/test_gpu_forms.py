@@ -556,3 +556,26 @@ def test_heating_over_the_field(n_cells, n_lambda, n_sizes, pad, mode):
         buf.copy_(J)
         plan.absorb(buf, buf)
         assert torch.equal(buf[:, :n_sizes], H) and torch.equal(buf[:, n_sizes:], J[:, n_sizes:])
+
+
+@pytest.mark.parametrize("mode", ["plain", "mixed"])
+@pytest.mark.parametrize("n_cells,n_lambda,n_sizes,pad", [
+    (400000, 12, 240, 0),     # H larger than the caches, short rows
+    (33000, 16, 50, 0), (33000, 64, 50, 0), (32000, 40, 81, 1),
+    (36000, 47, 40, 1), (36000, 48, 40, 1), (16000, 30, 40, 3),  # short rows on odd floats
+    (36000, 60, 130, 1), (50000, 60, 130, 1),                     # many grains
+])
+def test_heating_of_short_rows(n_cells, n_lambda, n_sizes, pad, mode):
+    """The forms that short rows and rows on odd floats take, against the first
+    rows' own call bit for bit and the oracle, with no column past the last
+    grain written."""
+    plan, J, _ = _inputs(n_cells, n_lambda, 1, n_sizes, mode, 23, pad)
+    out = torch.full((n_cells + 1, n_sizes + 2), -1.0, device="cuda")
+    plan.absorb(J, out[:n_cells, :n_sizes])
+    assert bool((out[n_cells] == -1.0).all()) and bool((out[:, n_sizes:] == -1.0).all())
+    for first, rows in ((0, 40), (n_cells - 33, 33), (1, 1700)):
+        assert torch.equal(plan.absorb(J[first:first + rows]),
+                           out[first:first + rows, :n_sizes]), first
+    g = synth.make_grid(n_lambda, 1, n_sizes)
+    ref = oracle.heating(J[:40].cpu().numpy().astype(np.float64), g.c_abs, g.dlam)
+    assert np.abs(out[:40, :n_sizes].cpu().numpy() / ref - 1.0).max() <= 1e-4
