@@ -1103,7 +1103,9 @@ dust_status dust_fluct_emit_sed(dust_fluct_plan* p, int64_t C, const float* P, i
     const hipStream_t st = (hipStream_t)stream;
     const int acc_flag = accumulate ? 1 : 0;
     const int64_t small = (C + 15) / 16 * ((v.NL + 15) / 16);
-    if (small <= (v.K >= 256 ? SMALL_EMIT_WAVES : SMALL_EMIT_WAVES / 2)) {
+    // (L over P: one workgroup for up to 128 wavelengths of a cell)
+    if (small <= (v.K >= 256 ? SMALL_EMIT_WAVES : SMALL_EMIT_WAVES / 2) &&
+        !share_memory(P, (C - 1) * ldp + v.K, L, (C - 1) * ldl + v.NL)) {
         if ((ldp % 4) == 0 && ((uintptr_t)P & 15u) == 0)
             hipLaunchKernelGGL(emit_small_kernel<4>, dim3((unsigned)small), dim3(64), 0, st, v, C, P,
                                ldp, m, L, ldl, acc_flag);

@@ -579,3 +579,22 @@ def test_heating_of_short_rows(n_cells, n_lambda, n_sizes, pad, mode):
     g = synth.make_grid(n_lambda, 1, n_sizes)
     ref = oracle.heating(J[:40].cpu().numpy().astype(np.float64), g.c_abs, g.dlam)
     assert np.abs(out[:40, :n_sizes].cpu().numpy() / ref - 1.0).max() <= 1e-4
+
+
+@pytest.mark.parametrize("n_cells,n_lambda,n_sizes,n_levels", [
+    (1, 128, 4, 40), (300, 100, 3, 64), (500, 17, 1, 33),
+])
+def test_averaged_sed_over_the_distributions(n_cells, n_lambda, n_sizes, n_levels):
+    """L may take the memory of P (the first columns of its rows) up to 128
+    wavelengths: the same bits as in memory of its own."""
+    g = synth.make_species_grid(n_lambda, [2], n_sizes)
+    p = synth.cell_params(n_cells, 13)
+    J = synth.radiation_field(p, g.lam, device="cuda")
+    m = torch.as_tensor(p.m_dust, dtype=torch.float32, device="cuda")
+    plan = dust.FluctPlan(g, *synth.fluct_levels(g, n_levels))
+    P = plan.solve_P(J)
+    L = plan.emit(P, m)
+    for _ in range(3):
+        buf = P.clone()
+        plan.emit(buf, m, buf)
+        assert torch.equal(buf[:, :n_lambda], L) and torch.equal(buf[:, n_lambda:], P[:, n_lambda:])
