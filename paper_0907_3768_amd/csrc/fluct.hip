@@ -356,7 +356,10 @@ __device__ __forceinline__ double upper_halves(double a, double b) {
 // A lane's share of the photon rates: the wavelengths [lane G, (lane + 1) G).
 // GR: G, with the grain's weights and energies kept in registers over the
 // workgroup's cells and the cells' intensities loaded a group ahead; 0: any
-// number of wavelengths, everything loaded where it is used.
+// number of wavelengths, everything loaded where it is used, four wavelengths'
+// loads in flight (a CU holds one to four such waves, so nothing else hides
+// them: 20000 x 4 grains x 8 levels x 4000 wavelengths 6.27 -> 2.66 ms, x 1500
+// 1.15 -> 0.49; 4000 x 4 x 64 x 600 79 -> 68 us).
 template <int GR>
 struct StagedRates {
     static constexpr int N = GR ? GR : 1;
@@ -434,7 +437,9 @@ struct StagedRates {
                 for (int q = 0; q < GR; ++q)
                     if (!write || lb + q < v.NL) one(q);  // (past NL the rates are zero)
             } else {
-                for (int q = 0; q < G && lb + q < v.NL; ++q) one(q);
+                const int n = v.NL - lb < G ? v.NL - lb : G;
+#pragma unroll 4
+                for (int q = 0; q < n; ++q) one(q);
             }
         };
         pass(false);

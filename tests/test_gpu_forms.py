@@ -598,3 +598,29 @@ def test_averaged_sed_over_the_distributions(n_cells, n_lambda, n_sizes, n_level
         buf = P.clone()
         plan.emit(buf, m, buf)
         assert torch.equal(buf[:, :n_lambda], L) and torch.equal(buf[:, n_lambda:], P[:, n_lambda:])
+
+
+@pytest.mark.parametrize("n_lambda,n_sizes,n_levels", [
+    (513, 1, 64), (1500, 2, 16), (2500, 1, 64), (4095, 1, 64), (4095, 2, 5),
+])
+def test_fluctuating_many_wavelengths(n_lambda, n_sizes, n_levels):
+    """The distributions on grids of which a CU holds few cells' prefix sums, to
+    the largest that is taken: against the oracle, and cell by cell the same in
+    calls of one and of all."""
+    g = synth.make_species_grid(n_lambda, [2], n_sizes)
+    lev_T, lev_E = synth.fluct_levels(g, n_levels)
+    p = synth.cell_params(37, 13)
+    J = synth.radiation_field(p, g.lam, device="cuda")
+    J[2] = 0.0
+    J[5, n_lambda - 1] = float("nan")
+    plan = dust.FluctPlan(g, lev_T, lev_E)
+    cnt = dust.new_counters()
+    P = plan.solve_P(J, counters=cnt)
+    ref = oracle.fluct_distribution(J[6:12].cpu().numpy().astype(np.float64), g, lev_T, lev_E)
+    out = P[6:12].cpu().numpy().reshape(ref.shape)
+    seen = ref >= 1e-30
+    assert np.abs(out[seen] / ref[seen] - 1.0).max() <= 1e-6
+    assert bool(P[5].isnan().all()) and int(cnt[0]) == n_sizes
+    for c in (0, 2, 4, 5, 36):
+        one = plan.solve_P(J[c:c + 1])
+        assert torch.equal(one.nan_to_num(-1.0), P[c:c + 1].nan_to_num(-1.0))
