@@ -158,7 +158,8 @@ __global__ __launch_bounds__(256) void prep_etab_kernel(Prep p) {
 }
 
 // ---------------------------------------------------------------------------
-// The distribution of one pair per wave; Q = levels per lane (M <= 64 Q).
+// The distribution of one pair per wave; Q = levels per lane (M <= 64 Q; more
+// than 64 levels).
 //
 // Lanes over the upper level j: acc_j collects sum_{i<j} B[j][i] X_i.  Level
 // i is final once every level below it has been added, so the levels are
@@ -1071,17 +1072,15 @@ dust_status dust_fluct_solve_P(dust_fluct_plan* p, int64_t C, const float* J, in
     const hipStream_t st = (hipStream_t)stream;
     const size_t lds = sizeof(double2) * (size_t)(v.NL + 1);
     hipError_t e;
-    const int w = v.M <= STAGED_MAX_LEVELS ? staged_waves(v.M, v.NL, v.S, C) : 0;
-    if (w > 0) {
+    if (v.M <= STAGED_MAX_LEVELS) {
+        const int w = staged_waves(v.M, v.NL, v.S, C);  // at least one (NL <= 4095)
         if (v.NL <= 256) e = launch_staged<4>(v, C, J, ldj, P, ldp, cnt, w, st);
         else if (v.NL <= 512) e = launch_staged<8>(v, C, J, ldj, P, ldp, cnt, w, st);
         else e = launch_staged<0>(v, C, J, ldj, P, ldp, cnt, w, st);
         return e == hipSuccess ? DUST_OK : hip_error(e, "fluctuating-grain distribution launch");
     }
     const dim3 grid((unsigned)(C * v.S));
-    if (v.M <= 64)
-        hipLaunchKernelGGL(solve_kernel<1>, grid, dim3(64), lds, st, v, C, J, ldj, P, ldp, cnt);
-    else if (v.M <= 128)
+    if (v.M <= 128)
         hipLaunchKernelGGL(solve_kernel<2>, grid, dim3(64), lds, st, v, C, J, ldj, P, ldp, cnt);
     else
         hipLaunchKernelGGL(solve_kernel<4>, grid, dim3(64), lds, st, v, C, J, ldj, P, ldp, cnt);
