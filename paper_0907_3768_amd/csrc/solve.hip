@@ -9,7 +9,8 @@
 // which leaves one evaluation of the full sum as a rule.  T goes back through
 // the same LDS slots; the iterations of the block are counted with one atomic.
 // Mixed and table-linear: a workgroup takes 64 or 256 cells x 16 grains, a
-// wave one grain at a time with a cell per lane: an O(1) lookup in the grain's
+// wave one grain at a time with a cell per lane (few grains of many cells:
+// pairs in row-major order): an O(1) lookup in the grain's
 // inverse table ln T(ln H) (a cubic Hermite in FP64 between FP64 nodes, or in
 // FP32 with the FP32 lookup), or a bracketed search in its table of powers at
 // evenly spaced T and linear interpolation (Sections 2 and 5).
@@ -185,12 +186,114 @@ __global__ __launch_bounds__(256) void solve_table_kernel(PlanView v, int64_t C,
         if (cc < rows && sl < G) T[(c0 + cc) * ldt + g0 + sl] = sX[cc * ST + sl];
 }
 
+// The same for grids whose grains leave much of a 16-grain tile empty, and many
+// cells: PAIRS_PER pairs per thread, 256 apart in row-major order, all looked up
+// before any is stored.  Pairs outside both tables go to an LDS list and are
+// then solved exactly by the workgroup's waves in turn.
+constexpr int PAIRS_PER = 4;
+constexpr int PAIRS_BLOCK = 256 * PAIRS_PER;  // pairs per workgroup
+
+template <int MODE>
+__global__ __launch_bounds__(256) void solve_pairs_kernel(PlanView v, int64_t C,
+                                                          const float* __restrict__ H, int64_t ldh,
+                                                          float* __restrict__ T, int64_t ldt,
+                                                          dust_counters* cnt) {
+    __shared__ int sCount;
+    __shared__ int sList[PAIRS_BLOCK];
+    if (threadIdx.x == 0) sCount = 0;
+    __syncthreads();
+    const int64_t n = C * v.S;
+    const int64_t base = (int64_t)blockIdx.x * PAIRS_BLOCK + threadIdx.x;
+    int64_t c[PAIRS_PER];
+    int s[PAIRS_PER];
+    float hs[PAIRS_PER], t[PAIRS_PER];
+    int st[PAIRS_PER];
+#pragma unroll
+    for (int k = 0; k < PAIRS_PER; ++k) {
+        // past the end, read the last pair again (nothing is stored for it)
+        const int64_t i = (base + k * 256 < n) ? base + k * 256 : n - 1;
+        c[k] = i / v.S;
+        s[k] = (int)(i - c[k] * v.S);
+        float h = H[c[k] * ldh + s[k]];
+        if (v.q) h += v.q[c[k] * v.ldq + s[k]];
+        hs[k] = h * v.hscale[s[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < PAIRS_PER; ++k) {
+        if constexpr (MODE == DUST_MIXED) {
+            st[k] = table_lookup_f64_nb(v, s[k], hs[k], &t[k]);
+        } else if constexpr (MODE == MODE_MIXED_F32) {
+            st[k] = table_lookup_f32_nb(v, s[k], hs[k], &t[k]);
+        } else {
+            st[k] = LOOKUP_OK;
+            if (base + k * 256 < n) {
+                if constexpr (MODE == MODE_MIXED_POLISH) {
+                    if (table_lookup_polish(v, s[k], hs[k], &t[k], cnt) != 0) st[k] = LOOKUP_PENDING;
+                } else {
+                    t[k] = table_linear_T(v, s[k], hs[k], cnt);
+                }
+            }
+        }
+    }
+    int nonfinite = 0;
+#pragma unroll
+    for (int k = 0; k < PAIRS_PER; ++k) {
+        if (base + k * 256 >= n) continue;
+        if (mixed_mode(MODE) && MODE != MODE_MIXED_POLISH && st[k] == LOOKUP_PENDING &&
+            cold_lookup(v, s[k], hs[k], &t[k], cnt))
+            st[k] = LOOKUP_OK;
+        if (st[k] == LOOKUP_PENDING) {
+            sList[atomicAdd(&sCount, 1)] = threadIdx.x + k * 256;
+        } else {
+            nonfinite += st[k] == LOOKUP_NONFINITE;
+            T[c[k] * ldt + s[k]] = t[k];
+        }
+    }
+    if constexpr (mixed_mode(MODE)) {
+        if (cnt) wave_count_add(&cnt->n_nonfinite, nonfinite);
+        __syncthreads();
+        const int np = sCount;
+        for (int e = threadIdx.x >> 6; e < np; e += 4) {
+            const int64_t ip = (int64_t)blockIdx.x * PAIRS_BLOCK + sList[e];
+            const int64_t cp = ip / v.S;
+            const int sp = (int)(ip - cp * v.S);
+            float hf = H[cp * ldh + sp];
+            if (v.q) hf += v.q[cp * v.ldq + sp];
+            const float tp = wave_solve_pending(v, sp, (double)(hf * v.hscale[sp]), cnt);
+            if ((threadIdx.x & 63) == 0) T[cp * ldt + sp] = tp;
+        }
+    }
+}
+
 template <int MODE, int CELLS>
 hipError_t launch_table(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
                         int64_t ldt, dust_counters* cnt, hipStream_t st) {
     hipLaunchKernelGGL((solve_table_kernel<MODE, CELLS>), dim3(heat_blocks<CELLS>(C, v.Sp / 16)),
                        dim3(256), 0, st, v, C, H, ldh, T, ldt, cnt);
     return hipGetLastError();
+}
+
+template <int MODE>
+hipError_t launch_pairs(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
+                        int64_t ldt, dust_counters* cnt, hipStream_t st) {
+    hipLaunchKernelGGL(solve_pairs_kernel<MODE>,
+                       dim3((unsigned)((C * v.S + PAIRS_BLOCK - 1) / PAIRS_BLOCK)), dim3(256), 0, st,
+                       v, C, H, ldh, T, ldt, cnt);
+    return hipGetLastError();
+}
+
+// Whether pairs in row-major order beat 16-grain tiles: where few grains fill
+// little of the last tile and the cells fill the GPU (below, more workgroups
+// hide the gathers).  Tiles against pairs, mixed: 1500000 cells x 1 grain 35.3 us
+// and 8.6, x 4 58 and 34, x 12 81 and 78, x 16 91 and 101, x 20 158 and 124, x 33
+// 300 and 299 (FP32 lookup: 283 and 244), x 45 337 and 417; 400000 x 1 9.1 and
+// 6.1, x 5 and x 8 equal, x 20 51 and 41; 100000 x 20 13.3 and 14.3.  The
+// table-linear search, longer, is bound by its gathers from four grains on.
+bool pairs_pay(const PlanView& v, int64_t C, int km) {
+    if (C < 262144) return false;
+    if (km == DUST_TABLE_LINEAR) return v.S <= 3;
+    if (km == MODE_MIXED_F32) return v.S <= 36;  // (16 grains: 80 us against 74)
+    return v.S <= 12 || (v.S > 16 && v.S <= 24);
 }
 
 // The branch-free lookups take 256 cells per workgroup, four of a grain in
@@ -205,9 +308,11 @@ constexpr int64_t TABLE_BLOCKS = 1024;
 template <int MODE>
 hipError_t launch_table_mode(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
                              int64_t ldt, dust_counters* cnt, hipStream_t st) {
-    if ((MODE == DUST_MIXED || MODE == MODE_MIXED_F32) &&
-        (C + 255) / 256 * (v.Sp / 16) >= TABLE_BLOCKS)
-        return launch_table<MODE, 256>(v, C, H, ldh, T, ldt, cnt, st);
+    if (pairs_pay(v, C, MODE)) return launch_pairs<MODE>(v, C, H, ldh, T, ldt, cnt, st);
+    if constexpr (MODE == DUST_MIXED || MODE == MODE_MIXED_F32) {
+        if ((C + 255) / 256 * (v.Sp / 16) >= TABLE_BLOCKS)
+            return launch_table<MODE, 256>(v, C, H, ldh, T, ldt, cnt, st);
+    }
     return launch_table<MODE, 64>(v, C, H, ldh, T, ldt, cnt, st);
 }
 

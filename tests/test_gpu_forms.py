@@ -624,3 +624,36 @@ def test_fluctuating_many_wavelengths(n_lambda, n_sizes, n_levels):
     for c in (0, 2, 4, 5, 36):
         one = plan.solve_P(J[c:c + 1])
         assert torch.equal(one.nan_to_num(-1.0), P[c:c + 1].nan_to_num(-1.0))
+
+
+@pytest.mark.parametrize("mode,lookup,sizes", [
+    ("mixed", "default", (1, 12, 13, 17, 24, 25)), ("mixed", "f32", (2, 16, 36, 37)),
+    ("mixed", "polish", (3, 24, 33)), ("table", "default", (1, 3, 4, 20)),
+])
+def test_table_solves_of_few_grains(mode, lookup, sizes):
+    """T of many cells of few grains (pairs in row-major order, or 16-grain
+    tiles) equals that of small calls bit for bit, with the same counters, on
+    cells of every kind, a cluster of them hotter than the table among them,
+    and only the grains' columns are written."""
+    n = 262144
+    for S in sizes:
+        plan, J, _ = _inputs(n + 65, 40, 1, S, mode, 9, f32_lookup=lookup == "f32",
+                             newton_polish=lookup == "polish")
+        H = plan.absorb(J)
+        for c, h in ((3, 0.0), (4, float("nan")), (7, -1e-20), (9, 1e-37), (71, 3e-30),
+                     (200, float("inf")), (n - 1, 0.0), (n + 64, 1e3)):
+            H[c] = h
+        H[5000:5100] = 1e3
+        Q = torch.zeros((n + 65, S + 3), device="cuda")
+        Q[::5] = 1e-20
+        for rows in (n - 1, n, n + 65):
+            for q in (None, Q):
+                big, small = dust.new_counters(), dust.new_counters()
+                out = torch.full((rows + 1, S + 2), -7.0, device="cuda")
+                plan.solve(H[:rows], out[:rows, :S], Q=q, counters=big)
+                for c in range(0, rows, 70000):
+                    e = min(rows, c + 70000)
+                    part = plan.solve(H[c:e], Q=None if q is None else q[c:e], counters=small)
+                    assert torch.equal(part.nan_to_num(-3.0), out[c:e, :S].nan_to_num(-3.0)), (S, rows)
+                assert bool((out[rows] == -7.0).all()) and bool((out[:, S:] == -7.0).all())
+                assert torch.equal(big, small) and int(big[0]) == 3 * S
