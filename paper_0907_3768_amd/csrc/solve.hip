@@ -82,44 +82,50 @@ __global__ __launch_bounds__(256) void solve_plain_kernel(PlanView v, int64_t C,
     }
 }
 
-// The table forms: a workgroup takes CELLS cells x 16 grains, its heating (plus
+// The table forms: a workgroup takes 64 Q cells x 16 grains, its heating (plus
 // the extra term) staged in LDS, and each wave four of the grains in turn, a
-// cell per lane and CELLS / 64 lookups of one grain in flight.  A wave's
-// gathers then fall into one grain's table (4 KB of inverse nodes), which L1
-// keeps for the tile's cells, and the grain's constants are scalars; pairs in
-// row-major order gathered 128-byte lines from every grain's table for each
-// pair, and a 64-bit division per pair found its grain.
-// Pairs outside both tables are solved exactly by the wave, one after the
-// other.  Bound by the gathers and, at 64 cells, by the chain of dependent
-// loads: 1048576 x 500 x 128 900 -> 553 us (H and T at copy rate: 225), the
-// table-linear form 100003 x 301 x 45 87 -> 37 us.
+// cell per lane and Q lookups of one grain in flight.  A wave's gathers then
+// fall into one grain's table (4 KB of inverse nodes), which L1 keeps for the
+// tile's cells, and the grain's constants are scalars; pairs in row-major order
+// gather 128-byte lines from every grain's table for each pair, and a 64-bit
+// division per pair finds its grain.
+// Pairs outside both tables are marked in LDS by the sign and, once the lookups
+// are done, solved exactly by the tile's waves, each from its share of the
+// 64-cell blocks; a workgroup's blocks lie far apart, so that a cluster of such
+// cells is spread over many workgroups.  Bound by the gathers and, at 64 cells,
+// by the chain of dependent loads: 1048576 x 500 x 128 900 -> 553 us (H and T at
+// copy rate: 225), the table-linear form 100003 x 301 x 45 87 -> 37 us.
 constexpr int TABLE_GRAINS = 16;
 
-template <int MODE, int CELLS>
+template <int MODE, int Q>
 __global__ __launch_bounds__(256) void solve_table_kernel(PlanView v, int64_t C,
                                                           const float* __restrict__ H, int64_t ldh,
                                                           float* __restrict__ T, int64_t ldt,
                                                           dust_counters* cnt) {
     constexpr int ST = TABLE_GRAINS + 1;  // odd: a grain's column falls on distinct banks
-    constexpr int Q = CELLS / 64;
-    __shared__ float sX[CELLS * ST];      // heating in, T out
-    const HeatTile ht = heat_tile<CELLS>(blockIdx.x, v.Sp / 16);
-    if (ht.c0 >= C) return;
-    const int64_t c0 = ht.c0;
+    constexpr int ROWS = 256 / TABLE_GRAINS, PER = 64 / ROWS;  // cells of one pass, passes of a block
+    __shared__ float sX[64 * Q * ST];     // heating in, T out
+    __shared__ int sPending;
+    const int64_t nb = (C + 64 * Q - 1) / (64 * Q);  // workgroups along the cells
+    const HeatTile ht = heat_tile<1>(blockIdx.x, v.Sp / 16);
+    if (ht.c0 >= nb) return;
     const int g0 = TABLE_GRAINS * ht.tile;
     const int G = v.S - g0 < TABLE_GRAINS ? v.S - g0 : TABLE_GRAINS;
-    const int rows = C - c0 < CELLS ? (int)(C - c0) : CELLS;
+    // block k of the workgroup: 64 cells from this one on
+    auto block = [&](int k) { return 64 * (ht.c0 + k * nb); };
+    if (threadIdx.x == 0) sPending = 0;
+    const int sl0 = threadIdx.x % TABLE_GRAINS, row = threadIdx.x / TABLE_GRAINS;
     {
-        const int sl = threadIdx.x % TABLE_GRAINS;
-        const float hscale = sl < G ? v.hscale[g0 + sl] : 1.0f;
+        const float hscale = sl0 < G ? v.hscale[g0 + sl0] : 1.0f;
 #pragma unroll
-        for (int cc = threadIdx.x / TABLE_GRAINS; cc < CELLS; cc += 256 / TABLE_GRAINS) {
+        for (int n = 0; n < PER * Q; ++n) {
+            const int64_t c = block(n / PER) + ROWS * (n % PER) + row;
             float h = 0.0f;  // (pairs past the tile's end: T = 0, not stored)
-            if (cc < rows && sl < G) {
-                h = H[(c0 + cc) * ldh + g0 + sl];
-                if (v.q) h += v.q[(c0 + cc) * v.ldq + g0 + sl];
+            if (c < C && sl0 < G) {
+                h = H[c * ldh + g0 + sl0];
+                if (v.q) h += v.q[c * v.ldq + g0 + sl0];
             }
-            sX[cc * ST + sl] = h * hscale;
+            sX[(ROWS * n + row) * ST + sl0] = h * hscale;
         }
     }
     __syncthreads();
@@ -140,7 +146,8 @@ __global__ __launch_bounds__(256) void solve_table_kernel(PlanView v, int64_t C,
                 st[k] = table_lookup_f32_nb(v, s, h[k], &t[k]);
             } else {
                 st[k] = LOOKUP_OK;
-                if (64 * k + lane < rows) {
+                t[k] = 0.0f;
+                if (block(k) + lane < C) {
                     if constexpr (MODE == MODE_MIXED_POLISH) {
                         if (table_lookup_polish(v, s, h[k], &t[k], cnt) != 0) st[k] = LOOKUP_PENDING;
                     } else {
@@ -153,37 +160,49 @@ __global__ __launch_bounds__(256) void solve_table_kernel(PlanView v, int64_t C,
             bool pending = false;
 #pragma unroll
             for (int k = 0; k < Q; ++k) {
-                if (64 * k + lane >= rows) st[k] = LOOKUP_OK;
+                if (block(k) + lane >= C) st[k] = LOOKUP_OK;
                 if (MODE != MODE_MIXED_POLISH && st[k] == LOOKUP_PENDING &&
                     cold_lookup(v, s, h[k], &t[k], cnt))
                     st[k] = LOOKUP_OK;
                 nonfinite += st[k] == LOOKUP_NONFINITE;
-                pending = pending || st[k] == LOOKUP_PENDING;
-            }
-            if (__ballot(pending) != 0) {
-#pragma unroll
-                for (int k = 0; k < Q; ++k) {
-                    uint64_t mask = __ballot(st[k] == LOOKUP_PENDING);
-                    while (mask) {
-                        const int src = __builtin_ctzll(mask);
-                        mask &= mask - 1;
-                        const float hp = __int_as_float(
-                            __builtin_amdgcn_readlane(__float_as_int(h[k]), src));
-                        const float tp = wave_solve_pending(v, s, (double)hp, cnt);
-                        if (lane == src) t[k] = tp;
-                    }
+                if (st[k] == LOOKUP_PENDING) {
+                    t[k] = -h[k];
+                    pending = true;
                 }
             }
+            if (pending) sPending = 1;
         }
 #pragma unroll
         for (int k = 0; k < Q; ++k) sX[(64 * k + lane) * ST + sl] = t[k];
     }
     if (mixed_mode(MODE) && cnt) wave_count_add(&cnt->n_nonfinite, nonfinite);
     __syncthreads();
-    const int sl = threadIdx.x % TABLE_GRAINS;
+    if constexpr (mixed_mode(MODE)) {
+        if (sPending) {  // uniform
+            // wave w takes the blocks k of the grains sl with (k + sl) mod 4 = w
+            for (int sl = 0; sl < G; ++sl) {
+                for (int k = (wave - sl) & 3; k < Q; k += 4) {
+                    float* x = &sX[(64 * k + lane) * ST + sl];
+                    const float xl = *x;
+                    uint64_t mask = __ballot(__float_as_int(xl) < 0);
+                    while (mask) {
+                        const int src = __builtin_ctzll(mask);
+                        mask &= mask - 1;
+                        const float hp = -__int_as_float(
+                            __builtin_amdgcn_readlane(__float_as_int(xl), src));
+                        const float tp = wave_solve_pending(v, g0 + sl, (double)hp, cnt);
+                        if (lane == src) *x = tp;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    }
 #pragma unroll
-    for (int cc = threadIdx.x / TABLE_GRAINS; cc < CELLS; cc += 256 / TABLE_GRAINS)
-        if (cc < rows && sl < G) T[(c0 + cc) * ldt + g0 + sl] = sX[cc * ST + sl];
+    for (int n = 0; n < PER * Q; ++n) {
+        const int64_t c = block(n / PER) + ROWS * (n % PER) + row;
+        if (c < C && sl0 < G) T[c * ldt + g0 + sl0] = sX[(ROWS * n + row) * ST + sl0];
+    }
 }
 
 // The same for grids whose grains leave much of a 16-grain tile empty, and many
@@ -265,10 +284,10 @@ __global__ __launch_bounds__(256) void solve_pairs_kernel(PlanView v, int64_t C,
     }
 }
 
-template <int MODE, int CELLS>
+template <int MODE, int Q>
 hipError_t launch_table(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
                         int64_t ldt, dust_counters* cnt, hipStream_t st) {
-    hipLaunchKernelGGL((solve_table_kernel<MODE, CELLS>), dim3(heat_blocks<CELLS>(C, v.Sp / 16)),
+    hipLaunchKernelGGL((solve_table_kernel<MODE, Q>), dim3(heat_blocks<64 * Q>(C, v.Sp / 16)),
                        dim3(256), 0, st, v, C, H, ldh, T, ldt, cnt);
     return hipGetLastError();
 }
@@ -311,9 +330,9 @@ hipError_t launch_table_mode(const PlanView& v, int64_t C, const float* H, int64
     if (pairs_pay(v, C, MODE)) return launch_pairs<MODE>(v, C, H, ldh, T, ldt, cnt, st);
     if constexpr (MODE == DUST_MIXED || MODE == MODE_MIXED_F32) {
         if ((C + 255) / 256 * (v.Sp / 16) >= TABLE_BLOCKS)
-            return launch_table<MODE, 256>(v, C, H, ldh, T, ldt, cnt, st);
+            return launch_table<MODE, 4>(v, C, H, ldh, T, ldt, cnt, st);
     }
-    return launch_table<MODE, 64>(v, C, H, ldh, T, ldt, cnt, st);
+    return launch_table<MODE, 1>(v, C, H, ldh, T, ldt, cnt, st);
 }
 
 }  // namespace
