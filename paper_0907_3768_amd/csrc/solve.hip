@@ -284,21 +284,41 @@ __global__ __launch_bounds__(256) void solve_pairs_kernel(PlanView v, int64_t C,
     }
 }
 
+// A launch holds fewer than 2^32 threads: f(view, first cell, cells) for slices
+// of at most `most` cells.
+template <typename F>
+hipError_t in_slices(const PlanView& v, int64_t C, int64_t most, F&& f) {
+    PlanView w = v;
+    for (int64_t c = 0; c < C; c += most) {
+        if (v.q) w.q = v.q + c * v.ldq;
+        f(w, c, C - c < most ? C - c : most);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+constexpr int64_t MAX_BLOCKS = (1 << 24) - 1;  // of 256 threads
+
 template <int MODE, int Q>
 hipError_t launch_table(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
                         int64_t ldt, dust_counters* cnt, hipStream_t st) {
-    hipLaunchKernelGGL((solve_table_kernel<MODE, Q>), dim3(heat_blocks<64 * Q>(C, v.Sp / 16)),
-                       dim3(256), 0, st, v, C, H, ldh, T, ldt, cnt);
-    return hipGetLastError();
+    const int tiles = v.Sp / 16;
+    return in_slices(v, C, MAX_BLOCKS / (8 * tiles) * 8 * 64 * Q,
+                     [&](const PlanView& w, int64_t c, int64_t n) {
+        hipLaunchKernelGGL((solve_table_kernel<MODE, Q>), dim3(heat_blocks<64 * Q>(n, tiles)),
+                           dim3(256), 0, st, w, n, H + c * ldh, ldh, T + c * ldt, ldt, cnt);
+    });
 }
 
 template <int MODE>
 hipError_t launch_pairs(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
                         int64_t ldt, dust_counters* cnt, hipStream_t st) {
-    hipLaunchKernelGGL(solve_pairs_kernel<MODE>,
-                       dim3((unsigned)((C * v.S + PAIRS_BLOCK - 1) / PAIRS_BLOCK)), dim3(256), 0, st,
-                       v, C, H, ldh, T, ldt, cnt);
-    return hipGetLastError();
+    return in_slices(v, C, MAX_BLOCKS * PAIRS_BLOCK / v.S,
+                     [&](const PlanView& w, int64_t c, int64_t n) {
+        hipLaunchKernelGGL(solve_pairs_kernel<MODE>,
+                           dim3((unsigned)((n * v.S + PAIRS_BLOCK - 1) / PAIRS_BLOCK)), dim3(256), 0,
+                           st, w, n, H + c * ldh, ldh, T + c * ldt, ldt, cnt);
+    });
 }
 
 // Whether pairs in row-major order beat 16-grain tiles: where few grains fill

@@ -657,3 +657,16 @@ def test_table_solves_of_few_grains(mode, lookup, sizes):
                     assert torch.equal(part.nan_to_num(-3.0), out[c:e, :S].nan_to_num(-3.0)), (S, rows)
                 assert bool((out[rows] == -7.0).all()) and bool((out[:, S:] == -7.0).all())
                 assert torch.equal(big, small) and int(big[0]) == 3 * S
+
+
+def test_table_solve_of_more_cells_than_a_launch_holds():
+    """2^30 cells and more of four grains, T in the memory of H: a launch's
+    2^32 threads do not hold them."""
+    k = (1 << 30) // 1000 + 2
+    plan, J, _ = _inputs(1000, 40, 1, 4, "table", 9)
+    H = plan.absorb(J)
+    T = plan.solve(H).reshape(1, 4000)
+    big = H.reshape(1, 4000).expand(k, 4000).contiguous()
+    plan.solve(big.view(k * 1000, 4), big.view(k * 1000, 4))
+    for c in range(0, k, 100000):
+        assert bool((big[c:c + 100000] == T).all()), c
