@@ -46,95 +46,119 @@ __global__ __launch_bounds__(256) void absorb_solve_kernel(PlanView v, int64_t C
                                 reinterpret_cast<int*>(sStage + STAGE_BYTES));
 }
 
-// Absorb + solve for small calls: one wave per 16 cells x 16 grains, the
-// heating straight from device memory (heat_block) and the lookups straight
-// from the accumulators, four pairs of one grain per lane; no LDS and no
-// barrier.  Pairs the table does not take are solved exactly by the wave, one
-// after the other.  The emission kernel follows.
-template <int MODE, bool ALIGNED>
-__global__ __launch_bounds__(64) void heat_solve_kernel(PlanView v, int64_t C,
-                                                        const float* __restrict__ J, int64_t ldj,
-                                                        float* __restrict__ T, int64_t ldt,
-                                                        dust_counters* cnt) {
-    const HeatTile ht = heat_tile<16>(blockIdx.x, v.Sp / 16);
+// Absorb + solve for small calls: one wave per 16 cells x 16 grains, WAVES grain
+// tiles of 16 cells per workgroup, the heating straight from device memory
+// (heat_block) and the lookups straight from the accumulators, four pairs of
+// one grain per lane.  Pairs the table does not take go to an LDS list, which
+// the workgroup's waves (those past the last tile among them) solve exactly in
+// turn.  The emission kernel follows.
+template <int MODE, bool ALIGNED, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void heat_solve_kernel(PlanView v, int64_t C,
+                                                         const float* __restrict__ J, int64_t ldj,
+                                                         float* __restrict__ T, int64_t ldt,
+                                                         dust_counters* cnt) {
+    __shared__ int sCount;
+    __shared__ float sHeat[256 * WAVES];     // the pending pairs' H' and
+    __shared__ uint16_t sPair[256 * WAVES];  // 64 cell + grain of the workgroup's
+    const int tiles = v.Sp / 16;
+    const HeatTile ht = heat_tile<16>(blockIdx.x, (tiles + WAVES - 1) / WAVES);
     if (ht.c0 >= C) return;
-    f32x4 hacc[1][1];
-    heat_block<true, ALIGNED, 1, 1, 4>(v, ht.c0, C, ht.tile, J, ldj, hacc);
-    const f32x4 acc = hacc[0][0];
-    const int lane = threadIdx.x & 63;
-    const int s_raw = 16 * ht.tile + (lane & 15);
-    const int s = s_raw < v.S ? s_raw : v.S - 1;  // a lane past the last grain looks it up unused
-    const int64_t cl = ht.c0 + 4 * (lane >> 4);
-    float h[4], t[4];
-    int st[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        h[r] = acc[r];
-        if (v.q && s_raw < v.S && cl + r < C) h[r] += v.q[(cl + r) * v.ldq + s] * v.hscale[s];
+    if constexpr (mixed_mode(MODE)) {
+        if (threadIdx.x == 0) sCount = 0;
+        __syncthreads();
     }
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = WAVES * ht.tile + wave;
+    if (tile < tiles) {
+        f32x4 hacc[1][1];
+        heat_block<true, ALIGNED, 1, 1, 4>(v, ht.c0, C, tile, J, ldj, hacc);
+        const f32x4 acc = hacc[0][0];
+        const int s_raw = 16 * tile + (lane & 15);
+        const int s = s_raw < v.S ? s_raw : v.S - 1;  // a lane past the last grain looks it up unused
+        const int64_t cl = ht.c0 + 4 * (lane >> 4);
+        float h[4], t[4];
+        int st[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const bool pair = s_raw < v.S && cl + r < C;
-        if constexpr (MODE == DUST_MIXED) {
-            st[r] = table_lookup_f64_nb(v, s, h[r], &t[r]);
-            if (!pair)
+        for (int r = 0; r < 4; ++r) {
+            h[r] = acc[r];
+            if (v.q && s_raw < v.S && cl + r < C) h[r] += v.q[(cl + r) * v.ldq + s] * v.hscale[s];
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const bool pair = s_raw < v.S && cl + r < C;
+            if constexpr (MODE == DUST_MIXED) {
+                st[r] = table_lookup_f64_nb(v, s, h[r], &t[r]);
+                if (!pair)
+                    st[r] = LOOKUP_OK;
+                else if (st[r] == LOOKUP_PENDING && cold_lookup(v, s, h[r], &t[r], cnt))
+                    st[r] = LOOKUP_OK;
+            } else {  // (the fused kernel's lookup: the branch-free FP32 one rounds differently)
                 st[r] = LOOKUP_OK;
-            else if (st[r] == LOOKUP_PENDING && cold_lookup(v, s, h[r], &t[r], cnt))
-                st[r] = LOOKUP_OK;
-        } else {  // (the fused kernel's lookup: the branch-free FP32 one rounds differently)
-            st[r] = LOOKUP_OK;
-            if (pair) {
-                if constexpr (mixed_mode(MODE)) {
-                    if (mixed_lookup<MODE>(v, s, h[r], &t[r], cnt) != 0) st[r] = LOOKUP_PENDING;
-                } else {
-                    t[r] = table_linear_T(v, s, h[r], cnt);
+                if (pair) {
+                    if constexpr (mixed_mode(MODE)) {
+                        if (mixed_lookup<MODE>(v, s, h[r], &t[r], cnt) != 0) st[r] = LOOKUP_PENDING;
+                    } else {
+                        t[r] = table_linear_T(v, s, h[r], cnt);
+                    }
                 }
             }
+            if (pair && st[r] != LOOKUP_PENDING) T[(cl + r) * ldt + s] = t[r];
+            if (mixed_mode(MODE) && st[r] == LOOKUP_PENDING) {
+                const int e = atomicAdd(&sCount, 1);
+                sHeat[e] = h[r];
+                sPair[e] = (uint16_t)(64 * (4 * (lane >> 4) + r) + 16 * wave + (lane & 15));
+            }
         }
-        if (pair && st[r] != LOOKUP_PENDING) T[(cl + r) * ldt + s] = t[r];
-    }
-    if constexpr (mixed_mode(MODE)) {
         if (MODE == DUST_MIXED && cnt) {
             int bad = 0;
 #pragma unroll
             for (int r = 0; r < 4; ++r) bad += st[r] == LOOKUP_NONFINITE;
             wave_count_add(&cnt->n_nonfinite, bad);
         }
-#pragma unroll 1
-        for (int r = 0; r < 4; ++r) {
-            const float hr = r == 0 ? h[0] : (r == 1 ? h[1] : (r == 2 ? h[2] : h[3]));
-            const int sr = r == 0 ? st[0] : (r == 1 ? st[1] : (r == 2 ? st[2] : st[3]));
-            uint64_t mask = __ballot(sr == LOOKUP_PENDING);
-            while (mask) {
-                const int src = __builtin_ctzll(mask);
-                mask &= mask - 1;
-                const float hp = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(hr), src));
-                const int sp = 16 * ht.tile + (src & 15);
-                const float tp = wave_solve_pending(v, sp, (double)hp, cnt);
-                if (lane == 0) T[(ht.c0 + 4 * (src >> 4) + r) * ldt + sp] = tp;
-            }
+    }
+    if constexpr (mixed_mode(MODE)) {
+        __syncthreads();
+        const int np = sCount;
+        for (int e = wave; e < np; e += WAVES) {
+            const int sp = 16 * WAVES * ht.tile + (sPair[e] & 63);
+            const float tp = wave_solve_pending(v, sp, (double)sHeat[e], cnt);
+            if (lane == 0) T[(ht.c0 + (sPair[e] >> 6)) * ldt + sp] = tp;
         }
     }
+}
+
+// Grids of up to three grain tiles take four waves per workgroup, so that some
+// are free to share a tile's exact solves (700 cells x 600 wavelengths x 16
+// grains, every pair outside the table: 1.73 ms with one wave, 0.47 with four;
+// 14.3 us either way with none); more tiles are waves enough, and spread better
+// one by one (32 x 968 x 81 17.0 us against 19.8).
+template <int MODE, bool ALIGNED>
+hipError_t launch_heat_solve_mode(const PlanView& v, int64_t C, const float* J, int64_t ldj,
+                                  float* T, int64_t ldt, dust_counters* cnt, hipStream_t st) {
+    const int tiles = v.Sp / 16;
+    if (mixed_mode(MODE) && tiles <= 3)
+        hipLaunchKernelGGL((heat_solve_kernel<MODE, ALIGNED, 4>), dim3(heat_blocks<16>(C, 1)),
+                           dim3(256), 0, st, v, C, J, ldj, T, ldt, cnt);
+    else
+        hipLaunchKernelGGL((heat_solve_kernel<MODE, ALIGNED, 1>), dim3(heat_blocks<16>(C, tiles)),
+                           dim3(64), 0, st, v, C, J, ldj, T, ldt, cnt);
+    return hipGetLastError();
 }
 
 template <bool ALIGNED>
 hipError_t launch_heat_solve(const PlanView& v, int64_t C, const float* J, int64_t ldj, float* T,
                              int64_t ldt, dust_counters* cnt, hipStream_t st) {
-    const dim3 grid(heat_blocks<16>(C, v.Sp / 16));
-    const int km = kernel_mode(v);
-    if (km == DUST_MIXED)
-        hipLaunchKernelGGL((heat_solve_kernel<DUST_MIXED, ALIGNED>), grid, dim3(64), 0, st, v, C,
-                           J, ldj, T, ldt, cnt);
-    else if (km == MODE_MIXED_F32)
-        hipLaunchKernelGGL((heat_solve_kernel<MODE_MIXED_F32, ALIGNED>), grid, dim3(64), 0, st, v,
-                           C, J, ldj, T, ldt, cnt);
-    else if (km == MODE_MIXED_POLISH)
-        hipLaunchKernelGGL((heat_solve_kernel<MODE_MIXED_POLISH, ALIGNED>), grid, dim3(64), 0, st,
-                           v, C, J, ldj, T, ldt, cnt);
-    else
-        hipLaunchKernelGGL((heat_solve_kernel<DUST_TABLE_LINEAR, ALIGNED>), grid, dim3(64), 0, st,
-                           v, C, J, ldj, T, ldt, cnt);
-    return hipGetLastError();
+    switch (kernel_mode(v)) {
+        case DUST_MIXED:
+            return launch_heat_solve_mode<DUST_MIXED, ALIGNED>(v, C, J, ldj, T, ldt, cnt, st);
+        case MODE_MIXED_F32:
+            return launch_heat_solve_mode<MODE_MIXED_F32, ALIGNED>(v, C, J, ldj, T, ldt, cnt, st);
+        case MODE_MIXED_POLISH:
+            return launch_heat_solve_mode<MODE_MIXED_POLISH, ALIGNED>(v, C, J, ldj, T, ldt, cnt, st);
+        default:
+            return launch_heat_solve_mode<DUST_TABLE_LINEAR, ALIGNED>(v, C, J, ldj, T, ldt, cnt, st);
+    }
 }
 
 template <int NTW>

@@ -670,3 +670,18 @@ def test_table_solve_of_more_cells_than_a_launch_holds():
     plan.solve(big.view(k * 1000, 4), big.view(k * 1000, 4))
     for c in range(0, k, 100000):
         assert bool((big[c:c + 100000] == T).all()), c
+
+
+@pytest.mark.parametrize("lookup", ["default", "f32", "polish"])
+@pytest.mark.parametrize("n_cells,n_lambda,n_sizes", [(1, 400, 16), (37, 600, 16), (50, 250, 65),
+                                                      (20, 300, 131)])
+def test_small_fused_calls_outside_the_table(n_cells, n_lambda, n_sizes, lookup):
+    """A small fused call all of whose pairs are solved exactly (a table that
+    ends below them): T, SED and counters of the one-kernel form, bit for bit."""
+    kw = {"f32_lookup": lookup == "f32", "newton_polish": lookup == "polish", "ltab_tmax": 4.0}
+    plan, J, m = _inputs(n_cells, n_lambda, 1, n_sizes, "mixed", 7, 1, **kw)
+    one = dust.Plan(synth.make_grid(n_lambda, 1, n_sizes), "mixed", fused_kernels=1, **kw)
+    cnt = dust.new_counters(), dust.new_counters()
+    a, b = one.fused(J, m, counters=cnt[0]), plan.fused(J, m, counters=cnt[1])
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    assert torch.equal(*cnt) and int(cnt[0][2]) > 0.9 * n_cells * n_sizes
