@@ -16,6 +16,14 @@ namespace {
 // Workgroups from which on a call's tiles are not split into wavelength columns
 // (16 per CU; the fill of a tile's 1/T is shared by its whole column).
 constexpr int64_t EMIT_WORKGROUPS = 4096;
+// Grains up to which a column's work is short beside its start: two rounds of
+// the waves at least, once such columns are three workgroups per CU (50000 x 250
+// x 16 39.2 us in two columns, 37.3 in one; 6000 x 600 x 2 13.0 in five, 11.8 in
+// three; but 6000 x 250 x 16 10.1 in two, 11.6 in one, and 3000 x 1000 x 16 13.0
+// in eight, 15.1 in four).  Above 16 grains that holds up to 24 blocks (6000 x 600
+// x 24 20.6 us in five columns, 19.2 in three; x 1000 27.5 in eight, 29.0 in four).
+constexpr int EMIT_FEW_GRAINS = 32;
+constexpr int64_t EMIT_FEW_WORKGROUPS = 768;
 
 template <int TC, bool TAIL>
 __global__ __launch_bounds__(256) void emit_kernel(PlanView v, int64_t C,
@@ -52,12 +60,15 @@ __global__ __launch_bounds__(256) void emit_kernel(PlanView v, int64_t C,
     }
 }
 
-// Blocks per column: as few columns as give EMIT_WORKGROUPS workgroups (a column
-// refills the tile's 1/T), each of whole rounds of the four waves.
-int column_blocks(int64_t tiles, int NB) {
+// Blocks per column: as few columns as give EMIT_WORKGROUPS workgroups, each of
+// whole rounds of the four waves.
+int column_blocks(int64_t tiles, int NB, int S) {
     const int64_t want = (EMIT_WORKGROUPS + tiles - 1) / tiles;
     const int cols = want < NB ? (int)want : NB;
-    return ((NB + cols - 1) / cols + 3) / 4 * 4;
+    const int bpc = ((NB + cols - 1) / cols + 3) / 4 * 4;
+    const bool few = (S <= 16 || (S <= EMIT_FEW_GRAINS && NB <= 24)) &&
+                     tiles * ((NB + 7) / 8) >= EMIT_FEW_WORKGROUPS;
+    return few && bpc < 8 ? 8 : bpc;
 }
 
 template <int TC>
@@ -103,10 +114,10 @@ hipError_t launch_emit(const PlanView& v, int64_t C, const float* T, int64_t ldt
     if (share_memory(T, (C - 1) * ldt + v.S, L, (C - 1) * ldl + v.NL))
         return launch_emit_tc<16>(v, C, T, ldt, m, L, ldl, 256 / 32, st);
     if (NB >= 4 && v.S > 32 && tasks <= EMIT_SLOTS * 3 / 2)
-        return launch_emit_tc<4>(v, C, T, ldt, m, L, ldl, column_blocks((C + 3) / 4, NB), st);
+        return launch_emit_tc<4>(v, C, T, ldt, m, L, ldl, column_blocks((C + 3) / 4, NB, v.S), st);
     if (NB >= 4 && v.S > 32 && tasks <= EMIT_SLOTS * 12)
-        return launch_emit_tc<8>(v, C, T, ldt, m, L, ldl, column_blocks((C + 7) / 8, NB), st);
-    return launch_emit_tc<16>(v, C, T, ldt, m, L, ldl, column_blocks((C + 15) / 16, NB), st);
+        return launch_emit_tc<8>(v, C, T, ldt, m, L, ldl, column_blocks((C + 7) / 8, NB, v.S), st);
+    return launch_emit_tc<16>(v, C, T, ldt, m, L, ldl, column_blocks((C + 15) / 16, NB, v.S), st);
 }
 
 }  // namespace dust

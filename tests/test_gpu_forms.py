@@ -685,3 +685,15 @@ def test_small_fused_calls_outside_the_table(n_cells, n_lambda, n_sizes, lookup)
     a, b = one.fused(J, m, counters=cnt[0]), plan.fused(J, m, counters=cnt[1])
     assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     assert torch.equal(*cnt) and int(cnt[0][2]) > 0.9 * n_cells * n_sizes
+
+
+@pytest.mark.parametrize("n_sizes", [1, 16, 17])
+@pytest.mark.parametrize("n_lambda", [250, 1000])
+def test_emission_columns_of_few_grains(n_lambda, n_sizes):
+    """Splitting a tile's wavelengths into columns (by the number of tiles and
+    of grains) does not change a bit."""
+    plan, J, m = _inputs(66000, n_lambda, 1, n_sizes, "table", 11)
+    T = plan.solve(plan.absorb(J))
+    L = plan.emit(T, m)  # one column
+    for rows in (1, 500, 6000, 16384, 16385, 40000):
+        assert torch.equal(plan.emit(T[:rows], m[:rows]), L[:rows]), rows
