@@ -359,6 +359,28 @@ dust_status dust_plan_prepare(dust_plan* p, void* stream) {
     return e == hipSuccess ? DUST_OK : hip_error(e, "plan kernels");
 }
 
+// For the tests of the refresh: fills every table that it derives with NaN (bytes
+// of ones).  Not for the table-linear mode, whose search reads indices.
+__attribute__((visibility("default"))) dust_status dust_test_spoil_tables(dust_plan* p) {
+    g_last_error.clear();
+    if (!p || p->opt.mode == DUST_TABLE_LINEAR) return set_error(DUST_EINVAL, "no plan to spoil");
+    const size_t t = (size_t)p->Sp * p->NLp, S = (size_t)p->S, M = (size_t)p->M;
+    const bool mixed = table_mode(p->opt.mode);
+    const struct { void* d; size_t n; } tables[] = {
+        {p->d_nu, 4 * (size_t)p->NLp}, {p->d_kf, 4 * t}, {p->d_kb, 4 * t}, {p->d_ku, 4 * t},
+        {p->d_em, 4 * t}, {p->d_khi, 2 * t}, {p->d_klo, 2 * t}, {p->d_kdb, 8 * S * p->NL},
+        {p->d_c2l, 8 * (size_t)p->NL}, {p->d_fwd, 8 * S * p->N}, {mixed ? p->d_ylo : nullptr, 8 * S},
+        {mixed ? p->d_yhi : nullptr, 8 * S}, {mixed ? p->d_dyinv : nullptr, 8 * S},
+        {p->d_invd, 16 * S * M}, {p->d_invf, 16 * S * (M - 1)}, {p->d_ylof, 4 * S},
+        {p->d_dyinvf, 4 * S}, {p->d_fwd_c, 8 * S * COLD_P}, {p->d_ylo_c, 8 * S},
+        {p->d_dyinv_c, 8 * S}, {p->d_inv_c, 16 * S * COLD_M}};
+    hipError_t e = hipDeviceSynchronize();
+    for (const auto& x : tables)
+        if (x.d && e == hipSuccess) e = hipMemset(x.d, 0xFF, x.n);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    return e == hipSuccess ? DUST_OK : hip_error(e, "hipMemset");
+}
+
 dust_status dust_plan_info(const dust_plan* p, int32_t* nl, int32_t* ns, int32_t* mode) {
     g_last_error.clear();
     if (!p) return set_error(DUST_EINVAL, "plan is NULL");

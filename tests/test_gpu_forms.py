@@ -4,6 +4,8 @@ Every sum of a cell is taken in the same order whatever the tile, so the rows
 of a small call must equal those rows of a large one exactly (tolerance 0).
 The large call's form is checked against the oracle by the parity tests.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -697,3 +699,55 @@ def test_emission_columns_of_few_grains(n_lambda, n_sizes):
     L = plan.emit(T, m)  # one column
     for rows in (1, 500, 6000, 16384, 16385, 40000):
         assert torch.equal(plan.emit(T[:rows], m[:rows]), L[:rows]), rows
+
+
+def _spoil(plan):
+    """Every table that a refresh derives becomes NaN."""
+    f = dust.lib().dust_test_spoil_tables
+    f.restype, f.argtypes = ctypes.c_int, [ctypes.c_void_p]
+    assert f(plan.handle) == dust.DUST_OK
+
+
+@pytest.mark.parametrize("n_lambda,n_species,n_sizes,ltab_n", [
+    (48, 1, 5, 0), (49, 1, 16, 0),        # one share of the wavelengths, two
+    (96, 2, 17, 0), (97, 1, 40, 0),       # two, four
+    (192, 1, 80, 0), (193, 3, 50, 0),     # four, eight
+    (8, 1, 3, 16), (640, 3, 75, 0),       # the smallest; the most tiles of a workgroup
+])
+def test_refresh_rebuilds_every_table(n_lambda, n_species, n_sizes, ltab_n):
+    """Tables filled with NaN are what they were after a refresh of one plan and
+    after that of a batch, among other plans and with plans enough for each
+    number of grain tiles per workgroup: T, SED and heating bit for bit, on
+    temperatures in the table and below it."""
+    g = _bright_grid(n_lambda, n_species, n_sizes)
+    H = torch.as_tensor(np.maximum(_power(g, np.geomspace(1.5, 1200.0, 97)), 1e-37)
+                        .astype(np.float32), device="cuda")
+    J = torch.rand((97, n_lambda), device="cuda")
+
+    def outputs(p):
+        T = p.solve(H)
+        return p.absorb(J), T, p.emit(T)
+
+    plain = dust.Plan(g, "plain")
+    want = outputs(plain)
+    _spoil(plain)
+    plain.prepare()
+    assert all(torch.equal(a, b) for a, b in zip(outputs(plain), want))
+    plan = dust.Plan(g, "mixed", ltab_n=ltab_n)
+    want = outputs(plan)
+    _spoil(plan)
+    assert not torch.equal(outputs(plan)[0], want[0])
+    plan.prepare()
+    assert all(torch.equal(a, b) for a, b in zip(outputs(plan), want))
+    for others in (0, 3, 12):
+        plans = [plan] + [dust.Plan(synth.make_grid(60 + 70 * k, 1 + k % 3, 30), "mixed")
+                          for k in range(others)]
+        Jb = [torch.rand((5, p.n_lambda), device="cuda") for p in plans]
+        b = dust.Batch(plans, Jb, [None] * len(plans),
+                       [torch.empty((5, p.n_grains), device="cuda") for p in plans],
+                       [torch.empty_like(j) for j in Jb], refresh_plans=True)
+        for p in plans:
+            _spoil(p)
+        b.launch()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outputs(plan), want)), others
