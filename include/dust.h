@@ -74,8 +74,8 @@ typedef enum {
        a cubic Hermite of the inverse evaluated in FP64 between FP64 nodes
        (interpolation error about 1e-9; relative T error about 5e-7,
        dominated by the heating); with `f32_lookup` the same Hermite in FP32
-       from FP32 nodes (about 2e-6).  Below the tabulated range, down to a
-       third of its lowest T, a second FP64 table of the same kind gives ln T
+       from FP32 nodes (about 2e-6).  Below the tabulated range, down to
+       half its lowest T, a second FP64 table of the same kind gives ln T
        to 1e-9 (a grain whose wavelengths are too few for that has none); other
        pairs outside the range are solved exactly in FP64.  FP32 emission. */
     DUST_MIXED = 1,

@@ -22,9 +22,10 @@ constexpr int PAD_S = 16;
 // points are tabulated, every other one a node; the points between them measure
 // the finished table, and a grain whose table misses one by more than COLD_TOL
 // (a hundredth of FP32's rounding) has none: its pairs are solved exactly.
-// The synthetic workloads' coldest grains lie at 2.0 K.
-constexpr int COLD_N = 128, COLD_M = 128, COLD_P = 2 * COLD_N - 1;
-constexpr double COLD_RATIO = 3.0, COLD_TOL = 1e-9;
+// The synthetic workloads' coldest grains lie at 1.9 K; a wider range would cost
+// every refresh its points (three times, 255 points: 5 % of the product).
+constexpr int COLD_N = 80, COLD_M = 96, COLD_P = 2 * COLD_N - 1;
+constexpr double COLD_RATIO = 2.0, COLD_TOL = 1e-9;
 
 // The plain solve's table: ln P' at PLAIN_N log-spaced T, where Newton's first
 // iterations run.  At 0.064 in ln T its cubic interpolation is good to about

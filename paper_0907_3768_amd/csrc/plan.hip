@@ -82,9 +82,9 @@ __device__ __forceinline__ void prep_body(const RefreshJob& j, int bx, int by) {
 
 // y[s][k] = ln sum_l W[s][l] F[k][l] (table-linear: the sum itself): an FP64
 // product on the matrix cores (v_mfma_f64_16x16x4_f64) whose F operand is
-// computed in registers and never stored.  A workgroup takes one block of 16
-// points and up to LT_TILES grain tiles of 16; its LT_WAVES waves split the
-// 16-wavelength steps (wave w takes steps w, w + 8, ...) and their partial
+// computed in registers and never stored.  The 16-wavelength steps of a block of
+// 16 points and up to LT_TILES grain tiles of 16 are split into shares (share w
+// of n takes steps w, w + n, ...; n by the number of wavelengths) whose partial
 // sums meet in LDS.  Per step, lane (row = lane mod 16, q = lane / 16)
 // computes F for point row and wavelengths l0 + 4 q .. + 3 (four FP64
 // exponentials), loads the same wavelengths of each grain tile's row of W
@@ -95,16 +95,35 @@ __device__ __forceinline__ void prep_body(const RefreshJob& j, int bx, int by) {
 // FP64 form interleaves rows).
 //
 // What bounds it is a wave's chain of exponentials and dependent MFMAs (FP64
-// ones, which take as long as the vector unit's), so the steps are spread over
-// eight waves even where many plans share the launch; there, and for a plan
-// with many grains, a wave shares its exponentials among several tiles
-// (product_tiles).  A refresh of all three stages, with four waves, 32
-// wavelengths a step and one tile (many plans: one wave with the whole range
-// and four tiles), and now: 250 x 80 19.8 -> 16.2 us, 968 x 81 42 -> 27, 1000 x
-// 240 62 -> 46, table-linear 1000 x 240 117 -> 62; 64 plans' refresh and solve
-// 14.23 -> 13.97 ms.  Weights loaded before the exponentials cost the registers
-// of a wave per SIMD (1000 x 240: 55 us).
+// ones, which take as long as the vector unit's), so a single plan's shares take
+// a wave each, up to eight; there, and for a plan with many grains, a wave
+// shares its exponentials among several tiles (product_tiles).  Where many plans
+// share a launch workgroups have four waves, which take eight shares two by
+// two, and fewer shares (up to LT_SHORT wavelengths each) leave waves to other
+// point blocks: each wave's start (1/T, addresses, the sums' meeting) is as
+// long as a step or two.  The sums are added in one order for each number of
+// shares, so every launch makes the same table bit for bit.
+// A refresh of all three stages, with four waves, 32 wavelengths a step and one
+// tile, and now: 250 x 80 19.6 -> 15.8 us, 968 x 81 42 -> 27, 1000 x 240 62 -> 46,
+// table-linear 1000 x 240 116 -> 62.  Many plans, with one wave that has the whole
+// range and four tiles, with eight waves and eight shares whatever the length,
+// and now: 64 of 100 - 600 wavelengths x 10 - 240 grains 372, 341, 331 us, 300 of
+// 40 x 80 435, 648, 451, 700 of 130 x 16 334, 631, 447 (a wave with the whole
+// range 381, but 250 x 80 alone 22.6; a sixth is the table below the range).
+// Weights loaded before the exponentials cost the registers of a wave per SIMD
+// (1000 x 240: 55 us).
 constexpr int LT_WAVES = 8, LT_TILES = 4, LT_STEP = 16;
+constexpr int LT_SHORT = 48;
+
+// Shares of a product over NL wavelengths.
+__host__ __device__ inline int product_shares(int NL) {
+    return NL <= LT_SHORT ? 1 : (NL <= 2 * LT_SHORT ? 2 : (NL <= 4 * LT_SHORT ? 4 : LT_WAVES));
+}
+// Point blocks per workgroup of `waves` waves.
+__host__ __device__ inline int product_blocks(int NL, int waves) {
+    const int n = product_shares(NL);
+    return n < waves ? waves / n : 1;
+}
 
 // Grain tiles per workgroup of the product for `blocks` (16-point block, grain
 // tile) pairs in one launch: one as long as the GPU has a place for each
@@ -134,77 +153,100 @@ __device__ __forceinline__ void store_point(const RefreshJob& j, int s, int k, d
         j.fwd_c[(int64_t)s * j.Nc + (k - v.N)] = log(P);
 }
 
+template <int WAVES>
 __device__ __forceinline__ void product_body(const RefreshJob& j, int bx, int by) {
     typedef double f64x4 __attribute__((ext_vector_type(4)));
-    __shared__ f64x4 part[LT_WAVES / 2][LT_TILES][64];
-    constexpr int NF = LT_STEP / 4;
+    constexpr int SLOTS = 4, NF = LT_STEP / 4;
+    static_assert(LT_WAVES == 2 * SLOTS && (WAVES == SLOTS || WAVES == LT_WAVES), "eight shares");
+    __shared__ f64x4 part[SLOTS][LT_TILES][64];
     const PlanView& v = j.v;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane & 15, q = lane >> 4;
-    const int k = bx * 16 + row;
-    const bool k_ok = k < v.N + j.Nc;
-    const double invT = point_inv_T(j, k);
+    const int n = product_shares(v.NL);     // uniform
+    const int per = n < SLOTS ? n : SLOTS;  // slots of a point block
+    const int blocks = product_blocks(v.NL, WAVES);
     const int tiles = (v.S + 15) / 16 - by * j.lt_tiles;
     const int nt = tiles < j.lt_tiles ? tiles : j.lt_tiles;
     const int s0 = by * j.lt_tiles * 16;
     f64x4 acc[LT_TILES];
+    // the sums of share w for the 16 points from k0
+    auto share = [&](int w, int k0) {
+        const double invT = point_inv_T(j, k0 + row);
+        const bool k_ok = k0 + row < v.N + j.Nc;
 #pragma unroll
-    for (int t = 0; t < LT_TILES; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int l0 = LT_STEP * wave; l0 < v.NL; l0 += LT_STEP * LT_WAVES) {
-        const int lq = l0 + NF * q;
-        double f[NF];
+        for (int t = 0; t < LT_TILES; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int l0 = LT_STEP * w; l0 < v.NL; l0 += LT_STEP * n) {
+            const int lq = l0 + NF * q;
+            double f[NF];
 #pragma unroll
-        for (int t = 0; t < NF; ++t) {
-            const int l = lq + t < v.NL ? lq + t : v.NL - 1;
-            const double em = expm1_pos(v.c2l[l] * invT);
-            // 0 once e^x overflows, and past the last wavelength or point
-            f[t] = (em < __builtin_inf() && lq + t < v.NL && k_ok) ? rcp_f64(em) : 0.0;
-        }
-#pragma unroll
-        for (int st = 0; st < LT_TILES; ++st) {
-            if (st >= nt) break;  // uniform
-            const int s = s0 + 16 * st + row;
-            const double* wr = v.kdb + (int64_t)(s < v.S ? s : v.S - 1) * v.NL;
-            double a[NF];
-            if (l0 + LT_STEP <= v.NL) {  // uniform
-#pragma unroll
-                for (int t = 0; t < NF; ++t) a[t] = wr[lq + t];
-            } else {
-#pragma unroll
-                for (int t = 0; t < NF; ++t) a[t] = wr[lq + t < v.NL ? lq + t : v.NL - 1];
+            for (int t = 0; t < NF; ++t) {
+                const int l = lq + t < v.NL ? lq + t : v.NL - 1;
+                const double em = expm1_pos(v.c2l[l] * invT);
+                // 0 once e^x overflows, and past the last wavelength or point
+                f[t] = (em < __builtin_inf() && lq + t < v.NL && k_ok) ? rcp_f64(em) : 0.0;
             }
 #pragma unroll
-            for (int t = 0; t < NF; ++t)
-                acc[st] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], f[t], acc[st], 0, 0, 0);
-        }
-    }
-    // waves 4-7 hand their sums to waves 0-3, whose four then meet in the wave
-    // that stores the tile
-    constexpr int HALF = LT_WAVES / 2;
-    static_assert(HALF == LT_TILES, "wave st finishes tile st");
-    if (wave >= HALF) {
+            for (int st = 0; st < LT_TILES; ++st) {
+                if (st >= nt) break;  // uniform
+                const int s = s0 + 16 * st + row;
+                const double* wr = v.kdb + (int64_t)(s < v.S ? s : v.S - 1) * v.NL;
+                double a[NF];
+                if (l0 + LT_STEP <= v.NL) {  // uniform
 #pragma unroll
-        for (int st = 0; st < LT_TILES; ++st)
-            if (st < nt) part[wave - HALF][st][lane] = acc[st];
-    }
-    __syncthreads();
-    if (wave < HALF) {
+                    for (int t = 0; t < NF; ++t) a[t] = wr[lq + t];
+                } else {
 #pragma unroll
-        for (int st = 0; st < LT_TILES; ++st)
-            if (st < nt) {
-                acc[st] += part[wave][st][lane];
-                part[wave][st][lane] = acc[st];
+                    for (int t = 0; t < NF; ++t) a[t] = wr[lq + t < v.NL ? lq + t : v.NL - 1];
+                }
+#pragma unroll
+                for (int t = 0; t < NF; ++t)
+                    acc[st] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], f[t], acc[st], 0, 0, 0);
             }
+        }
+    };
+    auto put = [&](int slot) {
+#pragma unroll
+        for (int st = 0; st < LT_TILES; ++st)
+            if (st < nt) part[slot][st][lane] = acc[st];
+    };
+    auto add = [&](int slot) {
+#pragma unroll
+        for (int st = 0; st < LT_TILES; ++st)
+            if (st < nt) acc[st] += part[slot][st][lane];
+    };
+    // of eight shares, share w + 4 hands its sums to share w
+    if (WAVES == LT_WAVES) {
+        share(wave, 16 * bx);
+        if (wave >= SLOTS) put(wave - SLOTS);
+        __syncthreads();
+        if (wave < SLOTS) {
+            add(wave);
+            put(wave);
+        }
+    } else if (n > SLOTS) {  // (each lane meets its own values)
+        share(wave + SLOTS, 16 * bx);
+        put(wave);
+        share(wave, 16 * bx);
+        add(wave);
+        put(wave);
+    } else {
+        share(wave & (n - 1), 16 * (bx * blocks + wave / n));
+        put(wave);
     }
     __syncthreads();
-    if (wave < nt) {
-        const f64x4 sum = (part[0][wave][lane] + part[1][wave][lane]) +
-                          (part[2][wave][lane] + part[3][wave][lane]);
+    for (int i = wave; i < blocks * nt; i += WAVES) {
+        const int pb = i / nt, st = i - pb * nt;
+        const f64x4* p = &part[pb * per][st][lane];
+        constexpr int NEXT = LT_TILES * 64;  // the next slot
+        f64x4 sum = p[0];
+        if (per > 1) sum += p[NEXT];
+        if (per > 2) sum += p[2 * NEXT] + p[3 * NEXT];
+        const int k = 16 * (bx * blocks + pb) + row;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
-            const int sr = s0 + 16 * wave + q + 4 * jj;
-            if (sr < v.S && k_ok) store_point(j, sr, k, sum[jj]);
+            const int sr = s0 + 16 * st + q + 4 * jj;
+            if (sr < v.S && k < v.N + j.Nc) store_point(j, sr, k, sum[jj]);
         }
     }
 }
@@ -340,12 +382,12 @@ __device__ __forceinline__ void cold_inv_body(const RefreshJob& job, int s, doub
 // The stages of a refresh (0 prep, 2 table product, 3 inverse table or search
 // brackets; stage 1 is empty since the product computes its Planck factors
 // itself): one block of a stage's grid.
-template <int STAGE>
+template <int STAGE, int WAVES>
 __device__ __forceinline__ void refresh_stage(const RefreshJob& j, int bx, int by) {
     if constexpr (STAGE == 0) {
         prep_body(j, bx, by);
     } else if constexpr (STAGE == 2) {
-        product_body(j, bx, by);
+        product_body<WAVES>(j, bx, by);
     } else {
         __shared__ __align__(16) double sF[FWD_LDS];
         if (j.v.mode == DUST_TABLE_LINEAR) kidx_body(j, bx, by, sF);
@@ -354,20 +396,17 @@ __device__ __forceinline__ void refresh_stage(const RefreshJob& j, int bx, int b
     }
 }
 
-// Threads of a stage's workgroup.
-constexpr int stage_threads(int stage) { return stage == 2 ? 64 * LT_WAVES : 256; }
-
 // One plan: the job by value, the stage's 2-D grid.
-template <int STAGE>
-__global__ __launch_bounds__(stage_threads(STAGE)) void refresh_kernel(RefreshJob j) {
-    refresh_stage<STAGE>(j, blockIdx.x, blockIdx.y);
+template <int STAGE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void refresh_kernel(RefreshJob j) {
+    refresh_stage<STAGE, WAVES>(j, blockIdx.x, blockIdx.y);
 }
 
 // Many plans in one launch: the flat block index is located among the plans'
 // consecutive ranges (starts[p] = first block of plan p, ascending) and
 // unfolded into that plan's 2-D grid of x extent gx.
 template <int STAGE>
-__global__ __launch_bounds__(stage_threads(STAGE)) void refresh_batched_kernel(const RefreshJob* __restrict__ jobs,
+__global__ __launch_bounds__(256) void refresh_batched_kernel(const RefreshJob* __restrict__ jobs,
                                                               const int* __restrict__ starts,
                                                               int n_jobs) {
     const int b = blockIdx.x;
@@ -379,13 +418,13 @@ __global__ __launch_bounds__(stage_threads(STAGE)) void refresh_batched_kernel(c
     const RefreshJob& j = jobs[lo];
     const int local = b - starts[lo];
     const int gx = j.gx[STAGE];
-    refresh_stage<STAGE>(j, local % gx, local / gx);
+    refresh_stage<STAGE, 4>(j, local % gx, local / gx);
 }
 
-template <int STAGE>
+template <int STAGE, int WAVES = 4>
 hipError_t launch_stage(const RefreshJob& j, hipStream_t st) {
-    hipLaunchKernelGGL(refresh_kernel<STAGE>, dim3(j.gx[STAGE], j.gy[STAGE]),
-                       dim3(stage_threads(STAGE)), 0, st, j);
+    hipLaunchKernelGGL((refresh_kernel<STAGE, WAVES>), dim3(j.gx[STAGE], j.gy[STAGE]),
+                       dim3(64 * WAVES), 0, st, j);
     return hipGetLastError();
 }
 
@@ -393,8 +432,8 @@ template <int STAGE>
 hipError_t launch_batched_stage(const RefreshJob* d_jobs, const int* d_starts, int n_jobs,
                                 int blocks, hipStream_t st) {
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(refresh_batched_kernel<STAGE>, dim3(blocks), dim3(stage_threads(STAGE)), 0,
-                       st, d_jobs, d_starts, n_jobs);
+    hipLaunchKernelGGL(refresh_batched_kernel<STAGE>, dim3(blocks), dim3(256), 0, st, d_jobs,
+                       d_starts, n_jobs);
     return hipGetLastError();
 }
 
@@ -429,7 +468,8 @@ void make_refresh_job(const dust_plan* p, RefreshJob* j) {
     }
     j->gx[0] = (v.NLp + 255) / 256;  j->gy[0] = v.Sp;
     j->gx[1] = 1;                    j->gy[1] = 0;
-    j->gx[2] = (v.N + j->Nc + 15) / 16;
+    const int pb = product_blocks(v.NL, 4);  // (of eight shares one, also with eight waves)
+    j->gx[2] = ((v.N + j->Nc + 15) / 16 + pb - 1) / pb;
     set_product_tiles(j, product_pairs(*j));
     // (mixed: one more column for the table below the range)
     j->gx[3] = (v.M + 255) / 256 + (j->Nc > 0); j->gy[3] = tab ? v.S : 0;
@@ -440,7 +480,7 @@ hipError_t launch_prepare(const dust_plan* p, hipStream_t st) {
     make_refresh_job(p, &j);
     hipError_t e = launch_stage<0>(j, st);
     if (e != hipSuccess) return e;
-    e = launch_stage<2>(j, st);
+    e = product_shares(j.v.NL) == LT_WAVES ? launch_stage<2, LT_WAVES>(j, st) : launch_stage<2>(j, st);
     if (e != hipSuccess || !table_mode(j.v.mode)) return e;
     return launch_stage<3>(j, st);
 }
