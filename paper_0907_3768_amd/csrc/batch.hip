@@ -131,6 +131,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NTW <= 2 ? 
     const int gx = __builtin_amdgcn_readfirstlane(items[it].x);
     const int ty = __builtin_amdgcn_readfirstlane(items[it].y);
     const GridArgs& g = grids[gx];
+    // a part past the last round of its own grid's blocks has nothing to emit
+    if (PARTS && blockIdx.y > 0 && 4 * 32 * (int)blockIdx.y >= g.v.NL) return;
     fused_tile<DUST_MIXED, TC, NTW, true, BATCH_KC>(
         g.v, (int64_t)ty * TC, g.C, g.J, g.ldj, g.m, g.T, g.ldt, g.L, g.ldl,
         PARTS && blockIdx.y > 0 ? nullptr : cnt, sTile, PARTS ? (int)blockIdx.y : 0,

@@ -751,3 +751,40 @@ def test_refresh_rebuilds_every_table(n_lambda, n_species, n_sizes, ltab_n):
         b.launch()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip(outputs(plan), want)), others
+
+
+@pytest.mark.parametrize("specs", [
+    [(1, 600, 40)],                                  # five parts
+    [(40, 128, 30), (33, 129, 17), (17, 1000, 50)],  # a part that only some grids need
+    [(16, 100, 20)] * 40 + [(16, 600, 80)],          # nor most of them
+    [(50, 257, 140), (9, 96, 250)],                  # many grains
+])
+def test_batch_parts_write_everything(specs):
+    """With T, L and the counters reset before each launch: a batch of few tiles
+    (replayed, without autotuning, and one-shot) gives the one-kernel fused
+    call's results bit for bit and counts each event once."""
+    plans, J, m, ref = [], [], [], []
+    want = dust.new_counters()
+    for k, (n, nl, S) in enumerate(specs):
+        p, j, d = _inputs(n, nl, 1, S, "mixed", 5 + k, fused_kernels=1)
+        for c, f in ((3, 0.0), (4, float("nan")), (9, 1e-14)):
+            if c < n:
+                j[c] *= f
+        plans.append(p), J.append(j), m.append(d)
+        ref.append(p.fused(j, d, counters=want))
+    T = [torch.empty_like(r[0]) for r in ref]
+    L = [torch.empty_like(r[1]) for r in ref]
+    cnt = dust.new_counters()
+    tuned = dust.Batch(plans, J, m, T, L, counters=cnt)
+    plain = dust.Batch(plans, J, m, T, L, counters=cnt, autotune=False)
+    for call in (tuned.launch, plain.launch, tuned.launch,
+                 lambda: dust.batch_run(plans, J, m, T, L, counters=cnt),
+                 lambda: dust.batch_run(plans, J, m, T, L, counters=cnt, no_alloc=True)):
+        for x in T + L:
+            x.fill_(-7.0)
+        cnt.zero_()
+        call()
+        for r, t, l in zip(ref, T, L):
+            assert torch.equal(t.nan_to_num(-3.0), r[0].nan_to_num(-3.0))
+            assert torch.equal(l.nan_to_num(-3.0), r[1].nan_to_num(-3.0))
+        assert torch.equal(cnt, want)
