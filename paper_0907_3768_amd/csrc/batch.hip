@@ -307,6 +307,7 @@ struct dust_batch {
     int* d_starts;  // [4][n_jobs]
     int n_jobs;
     int refresh_blocks[4];
+    bool long_product;
     hipGraph_t graph;
     hipGraphExec_t exec;
 };
@@ -571,6 +572,7 @@ dust_status dust_batch_create(dust_plan* const* plans, int32_t n_grids, const in
             b->refresh_blocks[st] = (int)total[st];
         }
         b->n_jobs = nj;
+        b->long_product = long_product(jobs.data(), nj);
         if ((e = hipMalloc(&b->d_jobs, sizeof(RefreshJob) * nj)) != hipSuccess ||
             (e = hipMalloc(&b->d_starts, sizeof(int) * starts.size())) != hipSuccess ||
             (e = hipMemcpy(b->d_jobs, jobs.data(), sizeof(RefreshJob) * nj, hipMemcpyHostToDevice)) != hipSuccess ||
@@ -587,7 +589,8 @@ dust_status dust_batch_create(dust_plan* const* plans, int32_t n_grids, const in
         if (refresh) {
             const int* starts[4];
             for (int st = 0; st < 4; ++st) starts[st] = b->d_starts + (size_t)st * b->n_jobs;
-            le = launch_prepare_batched(b->d_jobs, starts, b->n_jobs, b->refresh_blocks, cs);
+            le = launch_prepare_batched(b->d_jobs, starts, b->n_jobs, b->refresh_blocks,
+                                        b->long_product, cs);
         }
         if (le == hipSuccess) le = enqueue(b, best, cs);
         e = hipStreamEndCapture(cs, &b->graph);

@@ -200,7 +200,10 @@ void set_product_tiles(RefreshJob* j, int64_t pairs);
 // The refresh of many plans as four launches (one per stage); d_starts[k]
 // holds, per plan, the first block of its range in stage k (ascending).
 hipError_t launch_prepare_batched(const RefreshJob* d_jobs, const int* const d_starts[4],
-                                  int n_jobs, const int blocks[4], hipStream_t st);
+                                  int n_jobs, const int blocks[4], bool long_prod,
+                                  hipStream_t st);
+// Whether the plans' product takes workgroups of eight waves.
+bool long_product(const RefreshJob* jobs, int n_jobs);
 hipError_t launch_absorb(const PlanView& v, int64_t C, const float* J, int64_t ldj,
                          float* H, int64_t ldh, hipStream_t st);
 // Plain: the scaled heating H' (the plan's units), and the solve of either.  H

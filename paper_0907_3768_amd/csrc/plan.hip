@@ -98,7 +98,7 @@ __device__ __forceinline__ void prep_body(const RefreshJob& j, int bx, int by) {
 // ones, which take as long as the vector unit's), so a single plan's shares take
 // a wave each, up to eight; there, and for a plan with many grains, a wave
 // shares its exponentials among several tiles (product_tiles).  Where many plans
-// share a launch workgroups have four waves, which take eight shares two by
+// share a launch workgroups have four waves as a rule (long_product), which take eight shares two by
 // two, and fewer shares (up to LT_SHORT wavelengths each) leave waves to other
 // point blocks: each wave's start (1/T, addresses, the sums' meeting) is as
 // long as a step or two.  The sums are added in one order for each number of
@@ -119,10 +119,10 @@ constexpr int LT_SHORT = 48;
 __host__ __device__ inline int product_shares(int NL) {
     return NL <= LT_SHORT ? 1 : (NL <= 2 * LT_SHORT ? 2 : (NL <= 4 * LT_SHORT ? 4 : LT_WAVES));
 }
-// Point blocks per workgroup of `waves` waves.
-__host__ __device__ inline int product_blocks(int NL, int waves) {
+// Point blocks per workgroup: of four waves, each with a share of one.
+__host__ __device__ inline int product_blocks(int NL) {
     const int n = product_shares(NL);
-    return n < waves ? waves / n : 1;
+    return n < 4 ? 4 / n : 1;
 }
 
 // Grain tiles per workgroup of the product for `blocks` (16-point block, grain
@@ -158,6 +158,7 @@ __device__ __forceinline__ void product_body(const RefreshJob& j, int bx, int by
     typedef double f64x4 __attribute__((ext_vector_type(4)));
     constexpr int SLOTS = 4, NF = LT_STEP / 4;
     static_assert(LT_WAVES == 2 * SLOTS && (WAVES == SLOTS || WAVES == LT_WAVES), "eight shares");
+    // (eight waves: four of them are left over where there are four shares or fewer)
     __shared__ f64x4 part[SLOTS][LT_TILES][64];
     const PlanView& v = j.v;
     const int lane = threadIdx.x & 63;
@@ -165,7 +166,7 @@ __device__ __forceinline__ void product_body(const RefreshJob& j, int bx, int by
     const int row = lane & 15, q = lane >> 4;
     const int n = product_shares(v.NL);     // uniform
     const int per = n < SLOTS ? n : SLOTS;  // slots of a point block
-    const int blocks = product_blocks(v.NL, WAVES);
+    const int blocks = product_blocks(v.NL);
     const int tiles = (v.S + 15) / 16 - by * j.lt_tiles;
     const int nt = tiles < j.lt_tiles ? tiles : j.lt_tiles;
     const int s0 = by * j.lt_tiles * 16;
@@ -216,7 +217,7 @@ __device__ __forceinline__ void product_body(const RefreshJob& j, int bx, int by
             if (st < nt) acc[st] += part[slot][st][lane];
     };
     // of eight shares, share w + 4 hands its sums to share w
-    if (WAVES == LT_WAVES) {
+    if (WAVES == LT_WAVES && n == LT_WAVES) {  // uniform
         share(wave, 16 * bx);
         if (wave >= SLOTS) put(wave - SLOTS);
         __syncthreads();
@@ -230,7 +231,7 @@ __device__ __forceinline__ void product_body(const RefreshJob& j, int bx, int by
         share(wave, 16 * bx);
         add(wave);
         put(wave);
-    } else {
+    } else if (WAVES == SLOTS || wave < SLOTS) {
         share(wave & (n - 1), 16 * (bx * blocks + wave / n));
         put(wave);
     }
@@ -405,10 +406,9 @@ __global__ __launch_bounds__(64 * WAVES) void refresh_kernel(RefreshJob j) {
 // Many plans in one launch: the flat block index is located among the plans'
 // consecutive ranges (starts[p] = first block of plan p, ascending) and
 // unfolded into that plan's 2-D grid of x extent gx.
-template <int STAGE>
-__global__ __launch_bounds__(256) void refresh_batched_kernel(const RefreshJob* __restrict__ jobs,
-                                                              const int* __restrict__ starts,
-                                                              int n_jobs) {
+template <int STAGE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void refresh_batched_kernel(
+    const RefreshJob* __restrict__ jobs, const int* __restrict__ starts, int n_jobs) {
     const int b = blockIdx.x;
     int lo = 0, hi = n_jobs - 1;
     while (lo < hi) {
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(256) void refresh_batched_kernel(const RefreshJob* 
     const RefreshJob& j = jobs[lo];
     const int local = b - starts[lo];
     const int gx = j.gx[STAGE];
-    refresh_stage<STAGE, 4>(j, local % gx, local / gx);
+    refresh_stage<STAGE, WAVES>(j, local % gx, local / gx);
 }
 
 template <int STAGE, int WAVES = 4>
@@ -428,12 +428,12 @@ hipError_t launch_stage(const RefreshJob& j, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int STAGE>
+template <int STAGE, int WAVES = 4>
 hipError_t launch_batched_stage(const RefreshJob* d_jobs, const int* d_starts, int n_jobs,
                                 int blocks, hipStream_t st) {
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(refresh_batched_kernel<STAGE>, dim3(blocks), dim3(256), 0, st, d_jobs,
-                       d_starts, n_jobs);
+    hipLaunchKernelGGL((refresh_batched_kernel<STAGE, WAVES>), dim3(blocks), dim3(64 * WAVES), 0, st,
+                       d_jobs, d_starts, n_jobs);
     return hipGetLastError();
 }
 
@@ -468,7 +468,7 @@ void make_refresh_job(const dust_plan* p, RefreshJob* j) {
     }
     j->gx[0] = (v.NLp + 255) / 256;  j->gy[0] = v.Sp;
     j->gx[1] = 1;                    j->gy[1] = 0;
-    const int pb = product_blocks(v.NL, 4);  // (of eight shares one, also with eight waves)
+    const int pb = product_blocks(v.NL);
     j->gx[2] = ((v.N + j->Nc + 15) / 16 + pb - 1) / pb;
     set_product_tiles(j, product_pairs(*j));
     // (mixed: one more column for the table below the range)
@@ -485,11 +485,30 @@ hipError_t launch_prepare(const dust_plan* p, hipStream_t st) {
     return launch_stage<3>(j, st);
 }
 
+// Eight waves where the plans' wavelengths are many, and where a launch that is
+// over soon waits for one long plan (six of 120 x 20 and one of 1000 x 80: 133 us
+// with the batch, 145 with four waves).
+bool long_product(const RefreshJob* jobs, int n_jobs) {
+    double pairs = 0.0, steps = 0.0, workgroups = 0.0;
+    int longest = 0;
+    for (int k = 0; k < n_jobs; ++k) {
+        const double p = (double)product_pairs(jobs[k]) * product_blocks(jobs[k].v.NL);
+        pairs += p;
+        steps += p * jobs[k].v.NL;
+        workgroups += (double)jobs[k].gx[2] * jobs[k].gy[2];
+        longest = longest > jobs[k].v.NL ? longest : jobs[k].v.NL;
+    }
+    return steps >= 700.0 * pairs || (longest >= 600 && workgroups <= 1024.0);
+}
+
 hipError_t launch_prepare_batched(const RefreshJob* d_jobs, const int* const d_starts[4],
-                                  int n_jobs, const int blocks[4], hipStream_t st) {
+                                  int n_jobs, const int blocks[4], bool long_prod,
+                                  hipStream_t st) {
     hipError_t e;
     if ((e = launch_batched_stage<0>(d_jobs, d_starts[0], n_jobs, blocks[0], st)) != hipSuccess) return e;
-    if ((e = launch_batched_stage<2>(d_jobs, d_starts[2], n_jobs, blocks[2], st)) != hipSuccess) return e;
+    e = long_prod ? launch_batched_stage<2, LT_WAVES>(d_jobs, d_starts[2], n_jobs, blocks[2], st)
+                  : launch_batched_stage<2>(d_jobs, d_starts[2], n_jobs, blocks[2], st);
+    if (e != hipSuccess) return e;
     return launch_batched_stage<3>(d_jobs, d_starts[3], n_jobs, blocks[3], st);
 }
 
