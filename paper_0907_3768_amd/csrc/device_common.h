@@ -877,21 +877,16 @@ constexpr int PENDING_CAP = 256;
 //
 // For each (8-grain group, cell) the wave picks one evaluation, uniformly, by
 // comparing the group's hottest grain at the wave's longest wavelength
-// (smallest t over the wave's lanes) with four thresholds.  With y = 2^-t,
+// (smallest t over the wave's lanes) with three thresholds.  With y = 2^-t,
 // 1/(2^t - 1) = y / (1 - y) = y + y^2 + ..., and cutting the series after
 // y^n leaves the relative error y^n / (1 - y):
 //   t >= 150      every term is exactly 0 in FP32 (2^-150 underflows): skip;
 //   24 <= t       use y (relative error <= 2^-24);
 //   12 <= t < 24  use y + y^2 (relative error <= 2^-24 (1 + 2^-12));
-//   8 <= t < 12   use y + y^2 + y^3 (relative error <= 2^-24 (1 + 2^-8));
 //   otherwise     the exact form rcp(2^t - 1).
 // The comparisons are on the float bit patterns of non-negative values (their
 // order is that of unsigned integers), so they run on the scalar unit.
-// Costs per term: 0, 2 VALU + 1 exp, 3 VALU + 1 exp, 4 VALU + 1 exp, 3 VALU +
-// exp + rcp (a VALU instruction 4 cycles of a SIMD, exp and rcp 8).
-// The cubic saves 4 of 28 cycles on a twentieth of the terms: 4194304 x 1000 x 240
-// 101.5 -> 100.6 ms, 64 uneven grids 14.03 -> 13.97; a quartic to t = 6
-// would cost what the exact form does.
+// Costs per term: 0, 2 VALU + 1 exp, 3 VALU + 1 exp, 3 VALU + exp + rcp.
 // ---------------------------------------------------------------------------
 constexpr int EMIT_GROUP = 8;  // grains per class decision
 
@@ -960,7 +955,6 @@ __device__ __forceinline__ void emit_accumulate(const float* __restrict__ em, in
     const uint32_t thr_skip = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_uint(150.0f * ru));
     const uint32_t thr_y = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_uint(24.0f * ru));
     const uint32_t thr_y2 = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_uint(12.0f * ru));
-    const uint32_t thr_y3 = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f * ru));
 #pragma unroll
     for (int cc = 0; cc < TC; ++cc) acc[cc] = 0.0f;
     for (int s = 0; s < S; s += EMIT_GROUP) {
@@ -997,12 +991,6 @@ __device__ __forceinline__ void emit_accumulate(const float* __restrict__ em, in
                     for (int g = 0; g < EMIT_GROUP; ++g) {
                         const float y = __builtin_amdgcn_exp2f(nu * it[g]);
                         acc[c4 + k] = fmaf(e[g], fmaf(y, y, y), acc[c4 + k]);
-                    }
-                } else if (cm >= thr_y3) {
-#pragma unroll
-                    for (int g = 0; g < EMIT_GROUP; ++g) {
-                        const float y = __builtin_amdgcn_exp2f(nu * it[g]);
-                        acc[c4 + k] = fmaf(e[g], fmaf(fmaf(y, y, y), y, y), acc[c4 + k]);
                     }
                 } else {
 #pragma unroll
@@ -1080,7 +1068,7 @@ constexpr int EMIT_ROWS = 2;  // rows of a wave in the block emission
 template <int GRr, int NC>
 __device__ __forceinline__ void emit_step(const float* emp, int NLp, const float* itp, int Sp,
                                           float nu, const uint32_t* cmA, const uint32_t* cmB,
-                                          uint32_t thr_skip, uint32_t thr_y, uint32_t thr_y2, uint32_t thr_y3,
+                                          uint32_t thr_skip, uint32_t thr_y, uint32_t thr_y2,
                                           float (&acc)[NC]) {
     float e[GRr];
 #pragma unroll
@@ -1124,12 +1112,6 @@ __device__ __forceinline__ void emit_step(const float* emp, int NLp, const float
                     const float y = __builtin_amdgcn_exp2f(nu * it[k][g]);
                     acc[c4 + k] = fmaf(e[g], fmaf(y, y, y), acc[c4 + k]);
                 }
-            } else if (cm >= thr_y3) {
-#pragma unroll
-                for (int g = 0; g < GRr; ++g) {
-                    const float y = __builtin_amdgcn_exp2f(nu * it[k][g]);
-                    acc[c4 + k] = fmaf(e[g], fmaf(fmaf(y, y, y), y, y), acc[c4 + k]);
-                }
             } else {
 #pragma unroll
                 for (int g = 0; g < GRr; ++g)
@@ -1157,7 +1139,6 @@ __device__ __forceinline__ void emit_block(const PlanView& v, int lb, const floa
     const uint32_t thr_skip = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_uint(150.0f * ru));
     const uint32_t thr_y = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_uint(24.0f * ru));
     const uint32_t thr_y2 = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_uint(12.0f * ru));
-    const uint32_t thr_y3 = (uint32_t)__builtin_amdgcn_readfirstlane(__float_as_uint(8.0f * ru));
     const float* emp = v.em + (int64_t)(GR * r) * v.NLp + l;
     const float* itp = sInvT + GR * r;
 #pragma unroll
@@ -1204,12 +1185,6 @@ __device__ __forceinline__ void emit_block(const PlanView& v, int lb, const floa
                         const float y = __builtin_amdgcn_exp2f(nu * it[k][g]);
                         acc[c4 + k] = fmaf(e[g], fmaf(y, y, y), acc[c4 + k]);
                     }
-                } else if (cm >= thr_y3) {
-#pragma unroll
-                    for (int g = 0; g < GR; ++g) {
-                        const float y = __builtin_amdgcn_exp2f(nu * it[k][g]);
-                        acc[c4 + k] = fmaf(e[g], fmaf(fmaf(y, y, y), y, y), acc[c4 + k]);
-                    }
                 } else {
 #pragma unroll
                     for (int g = 0; g < GR; ++g)
@@ -1227,7 +1202,7 @@ __device__ __forceinline__ void emit_block(const PlanView& v, int lb, const floa
         constexpr int GT = EMIT_GROUP / ROWS;
         const int s_row = s_pairs + GT * r;
         emit_step<GT, NC>(v.em + l + (int64_t)s_row * v.NLp, v.NLp, sInvT + s_row, v.Sp, nu,
-                      sChunk + (s_pairs / EMIT_GROUP) * TCS, nullptr, thr_skip, thr_y, thr_y2, thr_y3,
+                      sChunk + (s_pairs / EMIT_GROUP) * TCS, nullptr, thr_skip, thr_y, thr_y2,
                       acc);
     }
     // the rows hold partial sums over different grains
