@@ -111,3 +111,15 @@ def test_batched_calls_need_one_entry_per_grid():
         dust.batch_run([], [FakeCuda((4, 8))], [None], [], [])
     with pytest.raises(ValueError):
         dust.Batch([], [FakeCuda((4, 8))], [None], [], [])
+
+
+def test_current_stream_without_torchs_handle_getter(monkeypatch):
+    """The getter is private to torch: without it the public stream serves."""
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: Stream)
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert dust._current_stream() == 1234
+    assert dust._stream(None).value == 1234
