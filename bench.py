@@ -296,7 +296,7 @@ def run_reheat_leg(torch, synth, dust, grid, params, J0, m, T, L, cnt, n_passes=
     for name, plan, warm, fused in (("plain_warm", pp, True, False), ("plain_cold", pp, False, False),
                                     ("mixed_fused", pm, False, True)):
         evals, times = loop(plan, warm, fused)
-        out[name] = {"newton_evals_per_pair": [e / (C * S) for e in evals],
+        out[name] = {"newton_iterations_per_pair": [e / (C * S) for e in evals],
                      "path_ms_per_pass": [t[1] for t in times],
                      "j_update_ms_per_pass": [t[0] for t in times]}
         if name == "plain_warm":
@@ -915,7 +915,7 @@ def main():
         "plain_fp32": {"value": plain_value, "ms_per_step": plain_ms, "stages_ms": plain_k,
                        "sed_cells_per_s": C / (plain_ms * 1e-3), "errors": plain_err,
                        "counters": dict(zip(COUNTER_NAMES, plain_cnt)),
-                       "newton_evals_per_pair": plain_cnt[3] / pairs,
+                       "newton_iterations_per_pair": plain_cnt[3] / pairs,
                        "dtype": "f32",
                        "emit_Gterm_per_s": terms / (plain_k["emit"] * 1e-3) / 1e9},
         "mixed_fused_two_kernels": {"ms_per_step": f2_ms, "stages_ms": f2_k,
