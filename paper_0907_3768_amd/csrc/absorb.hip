@@ -659,7 +659,7 @@ bool wave_heating_pays(const PlanView& v, int64_t C, const float* J, int64_t ldj
     const int tiles = v.Sp / 16;
     const bool odd = ((uintptr_t)J & 7u) != 0 || (ldj & 1) != 0;
     if (!gemm_fits()) return true;
-    if (!odd || tiles == 1) return blocks < 112 || odd;
+    if (!odd || tiles <= 2) return blocks < 112 || odd;
     if (tiles <= 8) return v.NL >= 48 || blocks < 64;
     return blocks < 112 || (v.NL >= 48 && blocks * tiles < 1600);
 }
