@@ -248,12 +248,13 @@ bool split_pays(const PlanView& v, int64_t C) {
 // grains 857 and 927 us at 24 wavelengths, 937 and 950 at 32, 1145 and 1033 at
 // 48; 6000 x 200 80 and 69 us at 24.  Up to 16 grains a tile's solve is one
 // round of its threads: 6000 x 16 18.0 and 23.5 us at 100 wavelengths, 30.8 and
-// 28.4 at 250; 700 x 16 16.3 and 17.1 at 100, 21.2 and 17.4 at 160; 400000 x 16
-// 226 and 223 at 32, 303 and 255 at 64.  Few cells of more than 32 grains have
+// 28.4 at 250; 700 x 16 16.3 and 17.1 at 100, 21.2 and 17.4 at 160; 50000 x 16 37
+// and 42 at 32, 49 and 48 at 64; 400000 x 16 209 and 225 at 24, 226 and 223 at 32; x
+// 5 156 and 139 at 8.  Few cells of more than 32 grains have
 // rounds enough at any length: 40 x 80 28.8 and 21.1 us at 24 wavelengths, 700 x
 // 40 18.8 and 17.0.
 bool plain_split_pays(const PlanView& v, int64_t C) {
-    if (v.S <= 16) return v.NL >= (C < 32768 ? 128 : 64);
+    if (v.S <= 16) return v.NL >= (C < 32768 ? 128 : (C < 262144 ? 64 : (v.S <= 8 ? 8 : 32)));
     return v.NL >= (v.S > 32 && C <= 4096 ? 8 : 32);
 }
 
