@@ -83,9 +83,9 @@ __device__ __forceinline__ float newton_start(const PlanView& v, int s, float ln
 
 // ln(P / H): of the ratio once it is near 1, since ln P and ln H apart carry the
 // rounding of values up to 80 (4e-6 in the residual, half a microkelvin per
-// kelvin in T).
-__device__ __forceinline__ float newton_residual(float p, float hs, float lnH) {
-    const float q = p / hs;
+// kelvin in T).  hinv = 1 / H (infinite for the smallest: the logarithms then).
+__device__ __forceinline__ float newton_residual(float p, float hinv, float lnH) {
+    const float q = p * hinv;
     return (q > 0.5f && q < 2.0f) ? logf(q) : logf(p) - lnH;
 }
 
@@ -117,10 +117,11 @@ __device__ __forceinline__ float solve_newton_f32(const PlanView& v, int s, floa
     float lnT = newton_start(
         v, s, lnH, (tstart > 0.0f && tstart < INFINITY) ? logf(tstart) : guess_lnT(hs, gs),
         &on_table);
-    float lo = -INFINITY, hi = INFINITY, T = 0.0f;
+    const float hinv = 1.0f / hs;
+    float lo = -INFINITY, hi = INFINITY, invT = 1.0f;
     bool done = false;
     for (; it < maxit; ++it) {
-        const float invT = expf(-lnT);
+        invT = expf(-lnT);
         float p0 = 0.f, p1 = 0.f, d0 = 0.f, d1 = 0.f;
         int l = 0;
         for (; l + 1 < NL; l += 2) {
@@ -164,12 +165,12 @@ __device__ __forceinline__ float solve_newton_f32(const PlanView& v, int s, floa
             lnT = (hi < INFINITY) ? 0.5f * (lo + hi) : fmaxf(lnT + 1.0f, guess_lnT(hs, gs));
             continue;
         }
-        const float r = newton_residual(P, hs, lnH);
-        const float slope = -0.69314718f * D / P;  // d ln P / d ln T
+        const float r = newton_residual(P, hinv, lnH);
+        const float step = r * (P / (-0.69314718f * D));  // over the slope d ln P / d ln T
         if (r < 0.0f) lo = lnT; else hi = lnT;
-        float next = lnT - r / slope;
+        float next = lnT - step;
         if (fabsf(r) <= tol) {
-            T = expf(-r / slope) / invT;  // (ln T itself would round to 2e-7)
+            lnT = -step;  // over the last T (ln T itself would round to 2e-7)
             done = true;
             break;
         }
@@ -180,7 +181,8 @@ __device__ __forceinline__ float solve_newton_f32(const PlanView& v, int s, floa
     }
     *evals = on_table + (done ? it + 1 : it);
     if (!done && cnt) count(&cnt->n_unconverged);
-    return done ? T : expf(lnT);
+    const float T = expf(lnT);
+    return done ? T / invT : T;
 }
 
 // ---------------------------------------------------------------------------
@@ -283,7 +285,8 @@ __device__ inline float solve_newton_wave(const PlanView& v, int s, bool live, f
         }
     }
     const bool solving = active;
-    float lo = -INFINITY, hi = INFINITY;
+    const float hinv = 1.0f / hs;
+    float lo = -INFINITY, hi = INFINITY, last = 1.0f;  // 1/T of the accepted step
     bool done = false;
     for (;;) {
         active = active && nev < maxit;
@@ -347,12 +350,13 @@ __device__ inline float solve_newton_wave(const PlanView& v, int s, bool live, f
                 lo = lnT;
                 lnT = (hi < INFINITY) ? 0.5f * (lo + hi) : fmaxf(lnT + 1.0f, guess_lnT(hs, gs));
             } else {
-                const float r = newton_residual(p, hs, lnH);
-                const float slope = 0.69314718f * invT * d / p;  // d ln P / d ln T
+                const float r = newton_residual(p, hinv, lnH);
+                const float step = r * (p / (0.69314718f * invT * d));  // over d ln P / d ln T
                 if (r < 0.0f) lo = lnT; else hi = lnT;
-                float next = lnT - r / slope;
+                float next = lnT - step;
                 if (fabsf(r) <= tol) {
-                    result = expf(-r / slope) / invT;  // (ln T itself would round to 2e-7)
+                    lnT = -step;  // over the last T (ln T itself would round to 2e-7)
+                    last = invT;
                     done = true;
                     active = false;
                 } else {
@@ -365,9 +369,9 @@ __device__ inline float solve_newton_wave(const PlanView& v, int s, bool live, f
         }
     }
     *evals = q == 0 ? on_table + nev : 0;
-    if (solving && !done) {
-        if (cnt && q == 0) count(&cnt->n_unconverged);
-        result = expf(lnT);
+    if (solving) {
+        if (!done && cnt && q == 0) count(&cnt->n_unconverged);
+        result = expf(lnT) / last;
     }
     return result;
 }
