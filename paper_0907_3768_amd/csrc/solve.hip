@@ -1,6 +1,6 @@
 // Temperature solve, Eq. 7 (Section 4.3).
 //
-// Plain FP32: a workgroup takes a tile of 64 (or 16) cells x 4 grains.  The
+// Plain FP32: a workgroup takes a tile of 64 (or 16) cells x 4 (or 16) grains.  The
 // tile's heating (plus the extra term) is staged in LDS; each wave then solves
 // one grain for the tile's cells (a cell per lane, or per four lanes), as the
 // paper's third kernel gives a block one species, so the grain's Planck
@@ -9,44 +9,43 @@
 // which leaves one evaluation of the full sum as a rule.  T goes back through
 // the same LDS slots; the iterations of the block are counted with one atomic.
 // Mixed and table-linear: a workgroup takes 64 or 256 cells x 16 grains, a
-// wave one grain at a time with a cell per lane (few grains of many cells:
-// pairs in row-major order): an O(1) lookup in the grain's
-// inverse table ln T(ln H) (a cubic Hermite in FP64 between FP64 nodes, or in
-// FP32 with the FP32 lookup), or a bracketed search in its table of powers at
-// evenly spaced T and linear interpolation (Sections 2 and 5).
+// wave one grain at a time with a cell per lane (few grains of many cells: pairs
+// in row-major order): an O(1) lookup in the grain's inverse table ln T(ln H) (a
+// cubic Hermite in FP64 between FP64 nodes, or in FP32 with the FP32 lookup), or
+// a bracketed search in its table of powers at evenly spaced T and linear
+// interpolation (Sections 2 and 5).
 // Every form adds the optional extra heating Q to H first.
 #include "wave_heat.h"
 
 namespace dust {
 namespace {
 
-constexpr int PLAIN_GRAINS = 4;  // grains per workgroup: one per wave
-
-// Plain: a workgroup takes 64 / R cells x 4 grains, a wave one grain for all
-// the cells.  One grain per wave rather than several in turn: more workgroups
-// hide the loads of the weights better and end more evenly (with vector loads,
-// 32768 x 968 x 81: 655 us, 799 with four grains per wave).
+// Plain: a workgroup takes 64 / R cells x GRAINS grains, a wave one grain at a
+// time for all the cells.  One grain per wave (GRAINS = 4) rather than several in
+// turn: more workgroups hide the loads of the weights better and end more evenly
+// (with vector loads, 32768 x 968 x 81: 655 us, 799 with four grains per wave);
+// on short rows of large calls four in turn (SHORT_ROWS).
 // scaled: H holds the plan's scaled H' (the fused call's own).
 // 32768 x 968 x 81: 1479 us with every iteration on the full sum, 382 with the
 // first ones on the table and the weights as scalar loads; bound by the VALU
 // and transcendental issue of the one evaluation of the full sum that is left
 // (6.7e12 terms/s, a third of them in the cheaper forms).
-template <int R>
+template <int R, int GRAINS>
 __global__ __launch_bounds__(256) void solve_plain_kernel(PlanView v, int64_t C,
                                                           const float* H, int64_t ldh, float* T,
                                                           int64_t ldt, bool scaled,
                                                           dust_counters* cnt) {
     constexpr int CELLS = 64 / R;
-    constexpr int ST = PLAIN_GRAINS + 1;  // odd: a grain's column falls on distinct banks
+    constexpr int ST = GRAINS + 1;        // odd: a grain's column falls on distinct banks
     __shared__ float sX[CELLS * ST];      // heating in, T out
     __shared__ int sEvals[4];
     const int64_t c0 = (int64_t)blockIdx.x * CELLS;
-    const int g0 = blockIdx.y * PLAIN_GRAINS;
-    const int G = (v.S - g0 < PLAIN_GRAINS) ? v.S - g0 : PLAIN_GRAINS;
+    const int g0 = blockIdx.y * GRAINS;
+    const int G = (v.S - g0 < GRAINS) ? v.S - g0 : GRAINS;
     const int rows = (C - c0 < CELLS) ? (int)(C - c0) : CELLS;
     // (H may be T: every element is read here before its T is written)
-    for (int i = threadIdx.x; i < rows * PLAIN_GRAINS; i += 256) {
-        const int cc = i / PLAIN_GRAINS, sl = i - cc * PLAIN_GRAINS;
+    for (int i = threadIdx.x; i < rows * GRAINS; i += 256) {
+        const int cc = i / GRAINS, sl = i - cc * GRAINS;
         if (sl >= G) continue;
         const int64_t c = c0 + cc;
         const float h = H[c * ldh + g0 + sl], q = v.q ? v.q[c * v.ldq + g0 + sl] : 0.0f;
@@ -58,12 +57,14 @@ __global__ __launch_bounds__(256) void solve_plain_kernel(PlanView v, int64_t C,
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool live = cell < rows;
     int evals = 0;
-    if (wave < G) {
-        const int s = g0 + wave;  // wave-uniform: the grain's weights come as scalars
+    for (int sl = wave; sl < G; sl += 4) {
+        const int s = g0 + sl;  // wave-uniform: the grain's weights come as scalars
         const float t0 = (live && v.warm) ? T[(c0 + cell) * ldt + s] : 0.0f;
-        const float t = solve_newton_wave<R>(v, s, live, live ? sX[cell * ST + wave] : 0.0f, t0,
-                                             &evals, cnt);
-        if (live) sX[cell * ST + wave] = t;  // (the R lanes of a cell hold the same)
+        int ev;
+        const float t = solve_newton_wave<R>(v, s, live, live ? sX[cell * ST + sl] : 0.0f, t0, &ev,
+                                             cnt);
+        if (live) sX[cell * ST + sl] = t;  // (the R lanes of a cell hold the same)
+        evals += ev;
     }
     if (cnt) {
 #pragma unroll
@@ -76,8 +77,8 @@ __global__ __launch_bounds__(256) void solve_plain_kernel(PlanView v, int64_t C,
         if (n) atomicAdd(reinterpret_cast<unsigned long long*>(&cnt->n_newton_evals),
                          (unsigned long long)n);
     }
-    for (int i = threadIdx.x; i < rows * PLAIN_GRAINS; i += 256) {
-        const int cc = i / PLAIN_GRAINS, sl = i - cc * PLAIN_GRAINS;
+    for (int i = threadIdx.x; i < rows * GRAINS; i += 256) {
+        const int cc = i / GRAINS, sl = i - cc * GRAINS;
         if (sl < G) T[(c0 + cc) * ldt + g0 + sl] = sX[cc * ST + sl];
     }
 }
@@ -90,8 +91,7 @@ __global__ __launch_bounds__(256) void solve_plain_kernel(PlanView v, int64_t C,
 // gather 128-byte lines from every grain's table for each pair, and a 64-bit
 // division per pair finds its grain.
 // Pairs outside both tables are marked in LDS by the sign and, once the lookups
-// are done, solved exactly by the tile's waves, each from its share of the
-// 64-cell blocks; a workgroup's blocks lie far apart, so that a cluster of such
+// are done, solved exactly by the tile's waves, a quarter each; a workgroup's blocks lie far apart, so that a cluster of such
 // cells is spread over many workgroups.  Bound by the gathers and, at 64 cells,
 // by the chain of dependent loads: 1048576 x 500 x 128 900 -> 553 us (H and T at
 // copy rate: 225), the table-linear form 100003 x 301 x 45 87 -> 37 us.
@@ -179,11 +179,12 @@ __global__ __launch_bounds__(256) void solve_table_kernel(PlanView v, int64_t C,
     __syncthreads();
     if constexpr (mixed_mode(MODE)) {
         if (sPending) {  // uniform
-            // wave w takes the blocks k of the grains sl with (k + sl) mod 4 = w
+            // wave w takes the pairs whose lane, block and grain add up to w mod 4
+            // (a quarter of a cell's grains, and of a grain's cells)
             for (int sl = 0; sl < G; ++sl) {
-                for (int k = (wave - sl) & 3; k < Q; k += 4) {
+                for (int k = 0; k < Q; ++k) {
                     float* x = &sX[(64 * k + lane) * ST + sl];
-                    const float xl = *x;
+                    const float xl = ((lane + k + sl) & 3) == wave ? *x : 0.0f;
                     uint64_t mask = __ballot(__float_as_int(xl) < 0);
                     while (mask) {
                         const int src = __builtin_ctzll(mask);
@@ -206,29 +207,29 @@ __global__ __launch_bounds__(256) void solve_table_kernel(PlanView v, int64_t C,
 }
 
 // The same for grids whose grains leave much of a 16-grain tile empty, and many
-// cells: PAIRS_PER pairs per thread, 256 apart in row-major order, all looked up
-// before any is stored.  Pairs outside both tables go to an LDS list and are
+// cells: PER pairs per thread, 256 apart in row-major order, all looked up before
+// any is stored (the table-linear search, with branches, takes one).  Pairs outside both tables go to an LDS list and are
 // then solved exactly by the workgroup's waves in turn.
-constexpr int PAIRS_PER = 4;
-constexpr int PAIRS_BLOCK = 256 * PAIRS_PER;  // pairs per workgroup
+constexpr int pairs_per_thread(int mode) { return mixed_mode(mode) ? 4 : 1; }
 
 template <int MODE>
 __global__ __launch_bounds__(256) void solve_pairs_kernel(PlanView v, int64_t C,
                                                           const float* __restrict__ H, int64_t ldh,
                                                           float* __restrict__ T, int64_t ldt,
                                                           dust_counters* cnt) {
+    constexpr int PER = pairs_per_thread(MODE), PAIRS_BLOCK = 256 * PER;
     __shared__ int sCount;
     __shared__ int sList[PAIRS_BLOCK];
     if (threadIdx.x == 0) sCount = 0;
     __syncthreads();
     const int64_t n = C * v.S;
     const int64_t base = (int64_t)blockIdx.x * PAIRS_BLOCK + threadIdx.x;
-    int64_t c[PAIRS_PER];
-    int s[PAIRS_PER];
-    float hs[PAIRS_PER], t[PAIRS_PER];
-    int st[PAIRS_PER];
+    int64_t c[PER];
+    int s[PER];
+    float hs[PER], t[PER];
+    int st[PER];
 #pragma unroll
-    for (int k = 0; k < PAIRS_PER; ++k) {
+    for (int k = 0; k < PER; ++k) {
         // past the end, read the last pair again (nothing is stored for it)
         const int64_t i = (base + k * 256 < n) ? base + k * 256 : n - 1;
         c[k] = i / v.S;
@@ -238,7 +239,7 @@ __global__ __launch_bounds__(256) void solve_pairs_kernel(PlanView v, int64_t C,
         hs[k] = h * v.hscale[s[k]];
     }
 #pragma unroll
-    for (int k = 0; k < PAIRS_PER; ++k) {
+    for (int k = 0; k < PER; ++k) {
         if constexpr (MODE == DUST_MIXED) {
             st[k] = table_lookup_f64_nb(v, s[k], hs[k], &t[k]);
         } else if constexpr (MODE == MODE_MIXED_F32) {
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(256) void solve_pairs_kernel(PlanView v, int64_t C,
     }
     int nonfinite = 0;
 #pragma unroll
-    for (int k = 0; k < PAIRS_PER; ++k) {
+    for (int k = 0; k < PER; ++k) {
         if (base + k * 256 >= n) continue;
         if (mixed_mode(MODE) && MODE != MODE_MIXED_POLISH && st[k] == LOOKUP_PENDING &&
             cold_lookup(v, s[k], hs[k], &t[k], cnt))
@@ -313,6 +314,7 @@ hipError_t launch_table(const PlanView& v, int64_t C, const float* H, int64_t ld
 template <int MODE>
 hipError_t launch_pairs(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
                         int64_t ldt, dust_counters* cnt, hipStream_t st) {
+    constexpr int PAIRS_BLOCK = 256 * pairs_per_thread(MODE);
     return in_slices(v, C, MAX_BLOCKS * PAIRS_BLOCK / v.S,
                      [&](const PlanView& w, int64_t c, int64_t n) {
         hipLaunchKernelGGL(solve_pairs_kernel<MODE>,
@@ -375,18 +377,32 @@ hipError_t launch_solve(const PlanView& v, int64_t C, const float* H, int64_t ld
 // waves) 33.0 -> 29.2; at 2000 waves (1600 x 250 x 80) 13.9 against 15.6, at
 // 3807 (3000 x 968 x 81) 51.6 against 72.1.
 constexpr int64_t PLAIN_FEW_WAVES = 1536;
+// Short rows of more pairs than the caches hold: four grains per workgroup are 16
+// bytes of every row of H and T, and the sums are too short to hide that (2000000
+// x 45: 3 wavelengths 4.34 ms with four grains, 4.11 with 16, 64 wavelengths 1.97
+// and 1.74; 400000 x 80, 64 wavelengths 595 us and 583, 100 731 and 754; 50000 x 45
+// fit the caches, 119 and 142 us at 3).
+constexpr int SHORT_ROWS = 64;
+constexpr int64_t SHORT_PAIRS = 30000000;
+
+template <int R, int GRAINS>
+hipError_t launch_plain(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
+                        int64_t ldt, bool scaled, dust_counters* cnt, hipStream_t st) {
+    const dim3 grid((unsigned)((C + 64 / R - 1) / (64 / R)),
+                    (unsigned)((v.S + GRAINS - 1) / GRAINS));
+    hipLaunchKernelGGL((solve_plain_kernel<R, GRAINS>), grid, dim3(256), 0, st, v, C, H, ldh, T, ldt,
+                       scaled, cnt);
+    return hipGetLastError();
+}
 
 hipError_t launch_solve_plain(const PlanView& v, int64_t C, const float* H, int64_t ldh, float* T,
                               int64_t ldt, bool scaled, dust_counters* cnt, hipStream_t st) {
     if (C == 0) return hipSuccess;
-    const unsigned gy = (unsigned)((v.S + PLAIN_GRAINS - 1) / PLAIN_GRAINS);
-    if ((C + 63) / 64 * v.S <= PLAIN_FEW_WAVES)
-        hipLaunchKernelGGL(solve_plain_kernel<4>, dim3((unsigned)((C + 15) / 16), gy), dim3(256), 0,
-                           st, v, C, H, ldh, T, ldt, scaled, cnt);
-    else
-        hipLaunchKernelGGL(solve_plain_kernel<1>, dim3((unsigned)((C + 63) / 64), gy), dim3(256), 0,
-                           st, v, C, H, ldh, T, ldt, scaled, cnt);
-    return hipGetLastError();
+    const int64_t waves = (C + 63) / 64 * v.S;
+    if (waves <= PLAIN_FEW_WAVES) return launch_plain<4, 4>(v, C, H, ldh, T, ldt, scaled, cnt, st);
+    if (v.NL <= SHORT_ROWS && v.S >= 16 && C * v.S >= SHORT_PAIRS)
+        return launch_plain<1, 16>(v, C, H, ldh, T, ldt, scaled, cnt, st);
+    return launch_plain<1, 4>(v, C, H, ldh, T, ldt, scaled, cnt, st);
 }
 
 }  // namespace dust

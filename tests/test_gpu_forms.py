@@ -788,3 +788,35 @@ def test_batch_parts_write_everything(specs):
             assert torch.equal(t.nan_to_num(-3.0), r[0].nan_to_num(-3.0))
             assert torch.equal(l.nan_to_num(-3.0), r[1].nan_to_num(-3.0))
         assert torch.equal(cnt, want)
+
+
+@pytest.mark.parametrize("n_lambda,n_sizes", [(5, 17), (64, 16), (40, 45)])
+def test_plain_solve_of_short_rows(n_lambda, n_sizes):
+    """Sixteen grains per workgroup (short rows of many pairs) solve as four do:
+    the rows of a smaller call, whose waves hold the same cells, bit for bit,
+    cold and warm, with the same iterations, no column past the last grain
+    written."""
+    n = 64 * (30000000 // n_sizes // 64 + 1) + 70
+    plan, J, _ = _inputs(64 * 1000, n_lambda, 1, n_sizes, "plain", 3)
+    H1 = plan.absorb(J)
+    H1[7] = 0.0
+    H1[9] = float("nan")
+    reps = (n + len(H1) - 1) // len(H1)
+    H = H1.repeat(reps, 1)[:n]
+    c1, c0 = dust.new_counters(), dust.new_counters()
+    T1 = plan.solve(H1, counters=c1)
+    out = torch.full((n + 1, n_sizes + 2), -7.0, device="cuda")
+    plan.solve(H, out[:n, :n_sizes], counters=c0)
+    for c in range(0, n, len(H1)):
+        e = min(n, c + len(H1)) // 64 * 64  # (whole waves)
+        assert torch.equal(out[c:e, :n_sizes].nan_to_num(-3.0), T1[:e - c].nan_to_num(-3.0)), c
+    assert bool((out[n] == -7.0).all()) and bool((out[:, n_sizes:] == -7.0).all())
+    whole = n // len(H1)
+    assert int(c0[3]) >= whole * int(c1[3]) and int(c0[0]) >= whole * int(c1[0])
+    warm = (out[:n, :n_sizes] * 1.01).contiguous()
+    plan.solve(H, T=warm, warm_start=True)
+    part = (T1[:64 * 50] * 1.01).contiguous()
+    plan.solve(H1[:64 * 50], T=part, warm_start=True)
+    T0 = T1[:64 * 50].nan_to_num(0.0)
+    assert torch.allclose(warm[:64 * 50].nan_to_num(0.0), T0, rtol=1e-5, atol=0.0)
+    assert torch.allclose(part.nan_to_num(0.0), T0, rtol=1e-5, atol=0.0)
