@@ -26,6 +26,9 @@
  *    when the plan was created, 4-byte aligned; the caller owns them.
  *    Leading dimensions (ldj, ldh, ldt, ldl) count elements and must be at
  *    least the row width (NL for J and L, S for H and T).
+ *  - An output may take the memory of an input, row for row (equal leading
+ *    dimensions, both at the rows' start): H that of J, T that of H, L that of J
+ *    in a fused or batched call, and that of T up to 256 wavelengths.
  *  - `stream` is a hipStream_t (NULL = the null stream).  Calls only enqueue
  *    work: they neither allocate nor synchronise, except dust_plan_create,
  *    dust_plan_destroy, dust_batch_create, dust_batch_destroy and
@@ -116,7 +119,9 @@ typedef struct {
     int32_t ltab_n;    /* table points per grain: mixed default 1024 (>= 16),
                           table-linear default 2000 (>= 16) */
     int32_t fused_kernels; /* dust_run_fused: 0 = library choice by the call's
-                              size (the same results), 1 = one kernel
+                              size (table modes: the same results bit for bit;
+                              plain: to FP32 rounding, as the forms add their
+                              sums in different orders), 1 = one kernel
                               (absorb, solve and emit per cell tile), 2 = two
                               kernels (absorb + solve per tile, T written once;
                               then emit). */
@@ -139,8 +144,9 @@ typedef struct {
     int64_t n_nonfinite;
     int64_t n_unconverged;
     int64_t n_out_of_table;
-    int64_t n_newton_evals;  /* DUST_PLAIN_FP32: pairs x Newton iterations
-                                (on the table and on the exact sum) */
+    int64_t n_newton_evals;  /* DUST_PLAIN_FP32: pairs x Newton iterations, on
+                                the table and on the exact sum (one of the
+                                latter per pair as a rule) */
 } dust_counters;
 
 /* Optional inputs of the temperature step (dust_solve_T_ext,
@@ -215,9 +221,10 @@ dust_status dust_emit_sed(dust_plan* plan, int64_t n_cells,
                           float* L, int64_t ldl, void* stream);
 
 /* Eqs. 6, 7, 9-10 in one call, as one launch over cell tiles or, where that
- * is faster (few cells, and DUST_PLAIN_FP32), as one per step; no H array is
- * needed (the plain form rests it in T or L before they are written).  Same
- * results as absorb -> solve -> emit. */
+ * is faster (few cells, and DUST_PLAIN_FP32 on all but short grids), as one per
+ * step; no H array is needed (the plain form rests it in T or L before they are
+ * written).  Same results as absorb -> solve -> emit (plain: to FP32 rounding; T
+ * of a cell may differ in its last bits with the number of cells in the call). */
 dust_status dust_run_fused(dust_plan* plan, int64_t n_cells,
                            const float* J, int64_t ldj, const float* m_dust,
                            float* T, int64_t ldt, float* L, int64_t ldl,

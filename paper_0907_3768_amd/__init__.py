@@ -288,8 +288,8 @@ class Plan:
 
     def fused(self, J, m_dust=None, T=None, L=None, counters=None, stream=None, Q=None,
               warm_start=False):
-        """absorb -> solve -> emit in one launch per tile; Q and warm_start as
-        in ``solve``."""
+        """absorb -> solve -> emit in one call; Q and warm_start as in
+        ``solve``."""
         n = J.shape[0]
         if warm_start and T is None:
             raise ValueError("warm_start needs T holding the previous temperatures")

@@ -159,9 +159,9 @@ dust_status set_error(dust_status code, const std::string& msg);
 void clear_error();
 dust_status hip_error(hipError_t e, const char* what);
 
-// Whether two arrays of a and b floats share memory.  A call whose input shares
-// memory with an output keeps to one kernel and one workgroup for a tile, which
-// reads the tile's rows before it writes them.
+// Whether two arrays of a and b floats share memory.  A call whose output takes
+// the memory of an input (or the fused call's L that of its T) keeps to a form in
+// which one workgroup owns a tile's rows and has read them before it writes them.
 inline bool share_memory(const float* x, int64_t a, const float* y, int64_t b) {
     const uintptr_t px = (uintptr_t)x, py = (uintptr_t)y;
     return px < py + 4 * (uintptr_t)b && py < px + 4 * (uintptr_t)a;
