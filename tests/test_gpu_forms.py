@@ -820,3 +820,21 @@ def test_plain_solve_of_short_rows(n_lambda, n_sizes):
     T0 = T1[:64 * 50].nan_to_num(0.0)
     assert torch.allclose(warm[:64 * 50].nan_to_num(0.0), T0, rtol=1e-5, atol=0.0)
     assert torch.allclose(part.nan_to_num(0.0), T0, rtol=1e-5, atol=0.0)
+
+
+@pytest.mark.parametrize("mode", ["plain", "mixed", "table"])
+@pytest.mark.parametrize("n_cells,n_lambda,n_sizes", [(40, 100, 20), (5000, 250, 80),
+                                                      (300000, 40, 5), (40000, 64, 130)])
+def test_temperatures_over_the_heating_and_sed_over_the_field(n_cells, n_lambda, n_sizes, mode):
+    """T may take the memory of H, and a fused call's L that of J: the same bits
+    as in memory of their own (plain fused: as the one-kernel form)."""
+    plan, J, m = _inputs(n_cells, n_lambda, 1, n_sizes, mode, 29)
+    H = plan.absorb(J)
+    T = plan.solve(H)
+    plan.solve(H, H)
+    assert torch.equal(H, T)
+    one = dust.Plan(synth.make_grid(n_lambda, 1, n_sizes), mode, fused_kernels=1)
+    Tf, Lf = one.fused(J, m)
+    buf, T2 = J.clone(), torch.empty_like(T)
+    plan.fused(buf, m, T2, buf)
+    assert torch.equal(T2, Tf) and torch.equal(buf, Lf)
