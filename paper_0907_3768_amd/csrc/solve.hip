@@ -91,10 +91,11 @@ __global__ __launch_bounds__(256) void solve_plain_kernel(PlanView v, int64_t C,
 // gather 128-byte lines from every grain's table for each pair, and a 64-bit
 // division per pair finds its grain.
 // Pairs outside both tables are marked in LDS by the sign and, once the lookups
-// are done, solved exactly by the tile's waves, a quarter each; a workgroup's blocks lie far apart, so that a cluster of such
-// cells is spread over many workgroups.  Bound by the gathers and, at 64 cells,
-// by the chain of dependent loads: 1048576 x 500 x 128 900 -> 553 us (H and T at
-// copy rate: 225), the table-linear form 100003 x 301 x 45 87 -> 37 us.
+// are done, solved exactly by the tile's waves, a quarter each; a workgroup's
+// blocks lie far apart, so that a cluster of such cells is spread over many
+// workgroups.  Bound by the gathers and, at 64 cells, by the chain of dependent
+// loads: 1048576 x 500 x 128 900 -> 553 us (H and T at copy rate: 225), the
+// table-linear form 100003 x 301 x 45 87 -> 37 us.
 constexpr int TABLE_GRAINS = 16;
 
 template <int MODE, int Q>
@@ -208,8 +209,9 @@ __global__ __launch_bounds__(256) void solve_table_kernel(PlanView v, int64_t C,
 
 // The same for grids whose grains leave much of a 16-grain tile empty, and many
 // cells: PER pairs per thread, 256 apart in row-major order, all looked up before
-// any is stored (the table-linear search, with branches, takes one).  Pairs outside both tables go to an LDS list and are
-// then solved exactly by the workgroup's waves in turn.
+// any is stored (the table-linear search, with branches, takes one).  Pairs
+// outside both tables go to an LDS list and are then solved exactly by the
+// workgroup's waves in turn.
 constexpr int pairs_per_thread(int mode) { return mixed_mode(mode) ? 4 : 1; }
 
 template <int MODE>
